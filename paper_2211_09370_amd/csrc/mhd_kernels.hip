@@ -618,7 +618,8 @@ __global__ void __launch_bounds__(kCellThreads) k_fluid(const TR *rho, const TU 
 
 // -------------------------------------------------------------------------------------------
 // Lorentz force and fluid update in one plane-marching kernel (single boxes, float32 storage).
-// A workgroup owns a 64 x 4 column of cells and marches along z over a chunk of planes. Each
+// A workgroup owns a TX x TY column of cells (64 x 4, or 32 x 8, 16 x 16, 8 x 32 on boxes narrower
+// in x, so that its 256 work-items hold cells) and marches along z over a chunk of planes. Each
 // plane of b is staged in LDS with a two-cell halo, each plane of rho and u with a one-cell
 // halo; the force of a plane is formed in LDS on the one-cell halo from the three b planes
 // around it (lorentz_force), and the fluid update of the plane before takes its neighbours'
@@ -629,17 +630,16 @@ __global__ void __launch_bounds__(kCellThreads) k_fluid(const TR *rho, const TU 
 // cell arithmetic is the same code as k_lorentz and k_fluid, so the results are the same bit
 // for bit.
 // -------------------------------------------------------------------------------------------
-constexpr int kLfTX = 64, kLfTY = 4;                         // output tile (256 work-items)
-constexpr int kLfBX = kLfTX + 4, kLfBY = kLfTY + 4;          // b with a two-cell halo
-constexpr int kLfFX = kLfTX + 2, kLfFY = kLfTY + 2;          // F, rho, u with a one-cell halo
-constexpr int kLfBN = kLfBX * kLfBY, kLfFN = kLfFX * kLfFY;  // 544, 396 cells per plane
-constexpr int kLfBS = (kLfBN + kCellThreads - 1) / kCellThreads;  // b cells staged per work-item
-constexpr int kLfFS = (kLfFN + kCellThreads - 1) / kCellThreads;  // F / rho-u cells per work-item
-
 __device__ __forceinline__ int ring5(int p) { return ((p % 5) + 5) % 5; }
 
-template <bool Q27>
+template <int kLfTX, bool Q27>
 __global__ void __launch_bounds__(kCellThreads) k_lorentz_fluid(LfArgs a) {
+    constexpr int kLfTY = kCellThreads / kLfTX;
+    constexpr int kLfBX = kLfTX + 4, kLfBY = kLfTY + 4;          // b with a two-cell halo
+    constexpr int kLfFX = kLfTX + 2, kLfFY = kLfTY + 2;          // F, rho, u with a one-cell halo
+    constexpr int kLfBN = kLfBX * kLfBY, kLfFN = kLfFX * kLfFY;  // 544, 396 cells per plane (64 x 4)
+    constexpr int kLfBS = (kLfBN + kCellThreads - 1) / kCellThreads;  // b cells staged per work-item
+    constexpr int kLfFS = (kLfFN + kCellThreads - 1) / kCellThreads;  // F / rho-u cells per work-item
     __shared__ float sb[4][3][kLfBN];
     __shared__ float sF[4][3][kLfFN];
     __shared__ float sr[5][4][kLfFN];
@@ -1157,19 +1157,36 @@ hipError_t launch_fluid(hipStream_t s, int kinds, const void *rho, const void *u
                         void *u_o, void *u_copy, StepConst c) {
     return fluid_kinds<false>(s, kinds, rho, u, F, rho_o, u_o, u_copy, c, nullptr, nullptr, 0);
 }
-hipError_t launch_lorentz_fluid(hipStream_t s, const LfArgs &a0) {
-    LfArgs a = a0;
-    a.tiles_x = (a.c.nx + kLfTX - 1) / kLfTX;
-    a.tiles_y = (a.c.ny + kLfTY - 1) / kLfTY;
-    const int64_t cols = (int64_t)a.tiles_x * a.tiles_y;
-    a.zchunk = cols * ((a.c.nz + 15) / 16) >= 512 ? 16 : 8;  // 16-plane chunks when they fill the chip
-    a.nblocks = (int)(cols * ((a.c.nz + a.zchunk - 1) / a.zchunk));
+template <int TX>
+static hipError_t lorentz_fluid_t(hipStream_t s, const LfArgs &a) {
     const dim3 grid((unsigned)(((a.nblocks + 7) / 8) * 8));
     if (a.c.lattice == 27)
-        hipLaunchKernelGGL(k_lorentz_fluid<true>, grid, dim3(kCellThreads), 0, s, a);
+        hipLaunchKernelGGL((k_lorentz_fluid<TX, true>), grid, dim3(kCellThreads), 0, s, a);
     else
-        hipLaunchKernelGGL(k_lorentz_fluid<false>, grid, dim3(kCellThreads), 0, s, a);
+        hipLaunchKernelGGL((k_lorentz_fluid<TX, false>), grid, dim3(kCellThreads), 0, s, a);
     return hipGetLastError();
+}
+hipError_t launch_lorentz_fluid(hipStream_t s, const LfArgs &a0) {
+    LfArgs a = a0;
+    const int tx = a.c.nx > 32 ? 64 : a.c.nx > 16 ? 32 : a.c.nx > 8 ? 16 : 8;
+    a.tiles_x = (a.c.nx + tx - 1) / tx;
+    a.tiles_y = (a.c.ny + kCellThreads / tx - 1) / (kCellThreads / tx);
+    const int64_t cols = (int64_t)a.tiles_x * a.tiles_y;
+    auto blocks = [&](int zc) { return cols * ((a.c.nz + zc - 1) / zc); };
+    // The march is a serial chain of 4-6 us per plane, so boxes that cannot fill the chip with
+    // 8-plane chunks take the longest shorter chunk that gives one workgroup per CU, down to one
+    // plane (the extra halo planes run on CUs that would idle). With the narrow tiles, per step
+    // against 64 x 4 tiles and 8 planes: 8 x 32 x 32 63 us less of 83, 5 x 83 x 83 44 less of 71;
+    // 100 x 75 x 75 keeps 8 planes (380 workgroups).
+    a.zchunk = blocks(16) >= 512 ? 16 : 8;
+    while (a.zchunk > 1 && blocks(a.zchunk) < 256) a.zchunk /= 2;
+    a.nblocks = (int)blocks(a.zchunk);
+    switch (tx) {
+        case 64: return lorentz_fluid_t<64>(s, a);
+        case 32: return lorentz_fluid_t<32>(s, a);
+        case 16: return lorentz_fluid_t<16>(s, a);
+        default: return lorentz_fluid_t<8>(s, a);
+    }
 }
 
 hipError_t launch_fluid_batch(hipStream_t s, int kinds, const PipeStep *tab, const BlockMap *map, int nblocks,

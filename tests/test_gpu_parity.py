@@ -863,3 +863,24 @@ def test_line_tables_are_refused_where_the_wall_has_no_lines(monkeypatch):
             sim.set_markers(X)
         assert ei.value.status == MHD_ERR_UNSUPPORTED, name
         sim.close()
+
+
+@pytest.mark.parametrize("shape", [(5, 35, 3), (9, 17, 2), (17, 9, 1), (33, 6, 5), (8, 64, 300)])
+def test_fused_lorentz_fluid_narrow_tiles_and_short_chunks(shape, monkeypatch):
+    """Tile widths 8, 16, 32 and 64 with ragged edges in y, chunks of one plane, and a chunk that
+    does not divide n_z: the fused launch equals the two kernels bit for bit."""
+    from paper_2211_09370_amd import Sim
+
+    print("case fused narrow", shape, flush=True)
+    w = random_box(*shape, key=226, n_mag=1)
+    out = []
+    for fused in ("1", "0"):
+        monkeypatch.setenv("MHD_FUSED_LF", fused)
+        sim = Sim(w.nx, w.ny, w.nz, 0)
+        sim.set_params(w.params)
+        for f in ("rho", "u", "b"):
+            sim.set_field(f, getattr(w, f))
+        sim.step(2)
+        out.append([sim.get_field(f) for f in ("rho", "u", "b")])
+        sim.close()
+    assert all(np.array_equal(x, y) for x, y in zip(*out)), shape

@@ -1,0 +1,82 @@
+// Resident magnetic iteration (mhd_resident.hip): plan, tile tables and launch arguments.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <vector>
+
+namespace mhd {
+
+constexpr int kResMaxThreads = 1024;
+constexpr int kResMaxStaged = 5 * kResMaxThreads;  // staged cells (tile and halo) of a workgroup
+constexpr int kResNoRow = 1 << 20;               // first row of a work-item that takes none
+constexpr size_t kResMaxLds = 160 * 1024 - 256;  // LDS of a CU less the kernel's own words
+constexpr int kResMaxTiles = 256;                // flags reserved in the workspace
+// table words reserved in the workspace (a box whose tables need more has no resident iteration)
+constexpr size_t resident_tab_ints(int ny, int nz) {
+    const size_t rows = (size_t)ny * nz;
+    return (rows < 9000 ? 40 * rows : 360000) + 4096;
+}
+
+// words of the synchronisation area; flags stand 64 bytes apart
+enum { kResCount = 0, kResState = 1, kResStalled = 2, kResFlags = 16, kResFlagStride = 16 };
+enum { kResCounting = 0, kResGo = 1, kResGivenUp = 2 };
+constexpr size_t kResSyncInts = kResFlags + (size_t)kResFlagStride * kResMaxTiles;
+constexpr long long kResRollTicks = 2000000;     // roll call: 20 ms of the 100 MHz clock
+constexpr long long kResStallTicks = 1000000000; // a wait after it: 10 s
+constexpr int kStatusStalled = 2;                // DevCtrl::status bit
+
+// header of a tile's table: counts and offsets (in words from the table's start). Places in LDS are
+// given in words, ready to use: 3 n_x times the local row or the marker's index.
+enum {
+    kResNLoad, kResOLoad,  // rows read each iteration: (place, first cell n_x (y + n_y z))
+    kResNMk, kResOMk,      // markers' lines: places of 9 taps, line, 9 weights, padding
+    kResNCor, kResOCor,    // corrected rows: places of km4 corrections, km4 weights, place of the row, padding
+    kResNNb, kResONb,      // tiles exchanged with
+    kResOExp,              // ty x tz words: 1 if another tile reads the row
+    kResHeader = 12
+};
+constexpr int kResTaps = 9, kResMkInts = 20;  // taps of a line's marker, words of its entry
+
+struct ResArgs {
+    const float *u;
+    float *b[2];           // b before the iteration, and the other buffer
+    const float *bext, *bext_yz;
+    const float *sj, *wall;
+    int64_t M;
+    int km4;
+    int nx, ny, nz;
+    int ty, tz, gy, nwg;   // tile of the cross-section, tiles in y, tiles
+    int slots, mk_max;     // rows of b in LDS (tile, halo, extra), markers' lines of a tile at most
+    int n_mag;
+    float kappa, omega;
+    const int *tab, *tab_off;
+    int *sync;
+    int32_t *status;
+    long long roll_ticks;
+};
+
+struct ResPlan {
+    bool ok = false;
+    int ty = 0, tz = 0, gy = 0, gz = 0, nwg = 0;
+    int ns = 0, cz = 0, threads = 0;
+    int slots = 0, mk_max = 0, km4 = 0;
+    size_t lds_bytes = 0;
+    std::vector<int> tab, tab_off;  // until uploaded
+};
+
+// A wall made of lines along x: each line's taps (rows y + ny z, weights; tm a line) and each band
+// row's entries (km lines and weights, padding repeats the first line with weight 0).
+struct ResWall {
+    int tm = 1, km = 1;
+    std::vector<int> tap_row, band_row, band_line;
+    std::vector<float> tap_w, band_w;
+};
+
+// Tiles, tables and launch shape of a box for at most max_wg workgroups; ok = false if it does not fit.
+ResPlan make_resident_plan(int nx, int ny, int nz, const ResWall &wall, int max_wg);
+
+hipError_t launch_mag_resident(hipStream_t s, const ResArgs &a, const ResPlan &p, bool q27);
+
+}  // namespace mhd

@@ -1,0 +1,189 @@
+// Host side of the resident magnetic iteration: tiles of the cross-section, the rows, markers and
+// neighbours of each tile, and the launch shape (mhd_resident.hip describes the kernel).
+#include <algorithm>
+#include <cstring>
+#include <set>
+
+#include "mhd_resident.h"
+
+namespace mhd {
+
+namespace {
+
+int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// Launch shape for tiles of ty x tz rows: the shortest column per work-item (CZ; each column also
+// takes the two planes around it) whose columns fit the workgroup, unless taller ones cost fewer
+// vector instructions in all: a plane of a column is about 800 cycles of latency for a lone wave of
+// a SIMD and 140 vector instructions of 4 cycles (140 cycles of a CU's four SIMDs) per wave. The
+// workgroup is as large as the rows read and staged can use.
+bool launch_shape(int nx, int ty, int tz, ResPlan &p) {
+    const int gr = (ty + 2) * (tz + 2);
+    const int forms[5][2] = {{1, 1}, {2, 1}, {5, 2}, {5, 4}, {5, 6}};
+    long best = -1;
+    for (const auto &f : forms) {
+        const int ns = f[0], cz = f[1], cols = nx * ty * ceil_div(tz, cz);
+        int nt = std::max({nx * ceil_div(gr, ns), cols, 64});
+        nt = ceil_div(nt, 64) * 64;
+        if (nt > kResMaxThreads) continue;
+        const long t = (long)(cz + 2) * std::max<long>(800, 140L * ceil_div(cols, 64));
+        if (best < 0 || t < best) {
+            best = t;
+            p.ns = ns;
+            p.cz = cz;
+            // a round of rows read from memory costs more than the barriers of a larger workgroup
+            p.threads = std::max(nt, std::min(kResMaxThreads, ceil_div(nx * ceil_div(gr, 2), 64) * 64));
+        }
+    }
+    return best >= 0;
+}
+
+bool build(int nx, int ny, int nz, const ResWall &w, ResPlan &p) {
+    const int ty = p.ty, tz = p.tz, PY = ty + 2, GR = PY * (tz + 2), nrows = ny * nz;
+    auto owner = [&](int row) { return (row % ny) / ty + p.gy * ((row / ny) / tz); };
+    std::vector<int> band((size_t)nrows, -1);
+    for (size_t r = 0; r < w.band_row.size(); ++r) band[(size_t)w.band_row[r]] = (int)r;
+    std::vector<char> exported((size_t)nrows, 0);
+    std::vector<std::set<int>> nb((size_t)p.nwg);
+    struct Tile {
+        std::vector<int> load, mk, cor;
+        int n_mk = 0, n_cor = 0;
+    };
+    std::vector<Tile> tiles((size_t)p.nwg);
+    std::vector<int> slot_of((size_t)nrows), mk_of(w.tap_row.size() / (size_t)w.tm);
+    p.slots = GR;
+    p.mk_max = 0;
+    p.km4 = (w.km + 3) & ~3;
+    if (w.tm > kResTaps) return false;
+    for (int t = 0; t < p.nwg; ++t) {
+        Tile &T = tiles[(size_t)t];
+        const int y0 = (t % p.gy) * ty, z0 = (t / p.gy) * tz;
+        const int th = std::min(ty, ny - y0), tw = std::min(tz, nz - z0);
+        std::fill(slot_of.begin(), slot_of.end(), -1);
+        std::fill(mk_of.begin(), mk_of.end(), -1);
+        auto row_at = [&](int hy, int hz) {
+            return (y0 - 1 + hy + ny) % ny + ny * ((z0 - 1 + hz + nz) % nz);
+        };
+        for (int hz = 1; hz <= tw; ++hz)  // the tile's own rows first: their b* is in LDS
+            for (int hy = 1; hy <= th; ++hy) slot_of[(size_t)row_at(hy, hz)] = hy + PY * hz;
+        std::vector<std::pair<int, int>> load;  // (slot, row)
+        for (int hz = 0; hz < tw + 2; ++hz)
+            for (int hy = 0; hy < th + 2; ++hy) {
+                if (hy >= 1 && hy <= th && hz >= 1 && hz <= tw) continue;
+                const int row = row_at(hy, hz);
+                load.push_back({hy + PY * hz, row});
+                if (slot_of[(size_t)row] < 0) slot_of[(size_t)row] = hy + PY * hz;
+            }
+        int extra = GR;
+        for (int hz = 0; hz < tw + 2; ++hz)
+            for (int hy = 0; hy < th + 2; ++hy) {
+                const int r = band[(size_t)row_at(hy, hz)];
+                if (r < 0) continue;
+                std::vector<int> line((size_t)p.km4), wt((size_t)p.km4, 0);
+                for (int q = 0; q < p.km4; ++q) {  // padding: the first line with weight 0
+                    const int k = q < w.km ? q : 0, l = w.band_line[(size_t)r * w.km + k];
+                    if (mk_of[(size_t)l] < 0) {
+                        mk_of[(size_t)l] = T.n_mk++;
+                        std::vector<int> e((size_t)kResMkInts, 0);
+                        for (int i = 0; i < kResTaps; ++i) {
+                            const int row = w.tap_row[(size_t)l * w.tm + (i < w.tm ? i : 0)];
+                            if (slot_of[(size_t)row] < 0) {
+                                slot_of[(size_t)row] = extra;
+                                load.push_back({extra++, row});
+                            }
+                            e[(size_t)i] = 3 * nx * slot_of[(size_t)row];
+                            if (i < w.tm) std::memcpy(&e[(size_t)(kResTaps + 1 + i)], &w.tap_w[(size_t)l * w.tm + i], 4);
+                        }
+                        e[kResTaps] = l;
+                        T.mk.insert(T.mk.end(), e.begin(), e.end());
+                    }
+                    line[(size_t)q] = 3 * nx * mk_of[(size_t)l];
+                    if (q < w.km) std::memcpy(&wt[(size_t)q], &w.band_w[(size_t)r * w.km + q], 4);
+                }
+                T.n_cor += 1;
+                T.cor.insert(T.cor.end(), line.begin(), line.end());
+                T.cor.insert(T.cor.end(), wt.begin(), wt.end());
+                T.cor.insert(T.cor.end(), {3 * nx * (hy + PY * hz), 0, 0, 0});
+            }
+        for (const auto &l : load) {
+            T.load.push_back(3 * nx * l.first);
+            T.load.push_back(nx * l.second);
+            exported[(size_t)l.second] = 1;
+            const int o = owner(l.second);
+            if (o != t) {  // a reader and its source wait for each other
+                nb[(size_t)t].insert(o);
+                nb[(size_t)o].insert(t);
+            }
+        }
+        p.slots = std::max(p.slots, extra);
+        p.mk_max = std::max(p.mk_max, T.n_mk);
+    }
+    p.tab.clear();
+    p.tab_off.assign(1, 0);
+    size_t longest = 0, most_nb = 0;
+    for (int t = 0; t < p.nwg; ++t) {
+        const Tile &T = tiles[(size_t)t];
+        const int y0 = (t % p.gy) * ty, z0 = (t / p.gy) * tz;
+        std::vector<int> v(kResHeader, 0);
+        auto put = [&](int at, const std::vector<int> &x) {
+            v.resize((v.size() + 3) & ~size_t(3));  // 16-byte aligned lists
+            v[(size_t)at] = (int)v.size();
+            v.insert(v.end(), x.begin(), x.end());
+        };
+        v[kResNLoad] = (int)T.load.size() / 2;
+        put(kResOLoad, T.load);
+        v[kResNMk] = T.n_mk;
+        put(kResOMk, T.mk);
+        v[kResNCor] = T.n_cor;
+        put(kResOCor, T.cor);
+        v[kResNNb] = (int)nb[(size_t)t].size();
+        put(kResONb, std::vector<int>(nb[(size_t)t].begin(), nb[(size_t)t].end()));
+        std::vector<int> e((size_t)ty * tz, 0);
+        for (int z = 0; z < std::min(tz, nz - z0); ++z)
+            for (int y = 0; y < std::min(ty, ny - y0); ++y)
+                e[(size_t)(y + ty * z)] = exported[(size_t)(y0 + y + ny * (z0 + z))];
+        put(kResOExp, e);
+        p.tab.insert(p.tab.end(), v.begin(), v.end());
+        p.tab_off.push_back((int)p.tab.size());
+        longest = std::max(longest, v.size());
+        most_nb = std::max(most_nb, nb[(size_t)t].size());
+    }
+    p.lds_bytes = 4 * (3 * (size_t)(p.slots + std::max(GR, p.mk_max)) * nx + 3 * (size_t)GR + 3 + longest);
+    return p.lds_bytes <= kResMaxLds && p.tab.size() + p.tab_off.size() <= resident_tab_ints(ny, nz) && (int)most_nb <= p.threads;
+}
+
+}  // namespace
+
+ResPlan make_resident_plan(int nx, int ny, int nz, const ResWall &wall, int max_wg) {
+    struct Cand {
+        long staged;
+        int nwg, ty, tz;
+    };
+    std::vector<Cand> cand;
+    max_wg = std::min(max_wg, kResMaxTiles);
+    // Tiles of at least 4 x 4 rows (or the whole cross-section): smaller ones read more rows than
+    // they own. The fewest staged cells first: the busiest workgroup sets the pace.
+    for (int ty = std::min(4, ny); ty <= std::min(ny, 24); ++ty)
+        for (int tz = std::min(4, nz); tz <= std::min(nz, 24); ++tz) {
+            const long nwg = (long)ceil_div(ny, ty) * ceil_div(nz, tz), gr = (long)(ty + 2) * (tz + 2);
+            if (nwg > max_wg || 24 * gr * nx > (long)kResMaxLds || gr * nx > kResMaxStaged) continue;
+            cand.push_back({gr * nx, (int)nwg, ty, tz});
+        }
+    std::stable_sort(cand.begin(), cand.end(), [](const Cand &a, const Cand &b) {
+        return a.staged != b.staged ? a.staged < b.staged : a.nwg < b.nwg;
+    });
+    ResPlan p;
+    for (size_t i = 0; i < cand.size() && i < 6; ++i) {
+        p.ty = cand[i].ty;
+        p.tz = cand[i].tz;
+        p.gy = ceil_div(ny, p.ty);
+        p.gz = ceil_div(nz, p.tz);
+        p.nwg = p.gy * p.gz;
+        if (!launch_shape(nx, p.ty, p.tz, p) || !build(nx, ny, nz, wall, p)) continue;
+        p.ok = true;
+        return p;
+    }
+    return ResPlan{};
+}
+
+}  // namespace mhd

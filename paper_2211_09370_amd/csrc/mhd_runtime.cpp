@@ -9,12 +9,14 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <new>
 #include <string>
 #include <utility>
 #include <vector>
 
 #include "mhd_internal.h"
+#include "mhd_resident.h"
 
 using namespace mhd;
 
@@ -58,6 +60,7 @@ struct Layout {
     size_t rho[2], u[2], b[2], bh[2], u16, F, bext, bext_yz, ctrl, tap_cell, tap_w, s_u, s_b, uwall, bwall, delta;
     size_t band_cell, band_mk, band_w, red_part, flow_part, ring, res, total;
     size_t ring_tap, ring_tw, row_off, row_mk, row_w;  // line-structured walls
+    size_t res_tab, res_sync;  // resident magnetic iteration (float32 single boxes)
 };
 
 Layout make_layout(const mhd_grid_desc &g, int64_t M) {
@@ -102,6 +105,10 @@ Layout make_layout(const mhd_grid_desc &g, int64_t M) {
     L.flow_part = take((size_t)kRedBlocks * sizeof(double));
     L.ring = take((size_t)kRingCap * sizeof(mhd_budget));
     L.res = take((size_t)kResCap * sizeof(double));
+    if (g.b_storage == MHD_STORE_F32 && g.u_storage == MHD_STORE_F32) {
+        L.res_tab = take(resident_tab_ints(g.ny, g.nz) * sizeof(int));
+        L.res_sync = take(kResSyncInts * sizeof(int));
+    }
     L.total = off;
     return L;
 }
@@ -183,6 +190,16 @@ struct mhd_sim {
     };
     std::vector<StepGraph> graphs;
     bool graph_on = true;
+    // Resident magnetic iteration (mhd_resident.hip): the wall as lines along x (empty tap_row: no
+    // wall; wall_lines false: markers of another form), and the plan for it, made before the first step
+    // that uses it. MHD_RESIDENT at mhd_set_params: 0 = never, 1 (default) = where the box fits,
+    // 2 = its one-workgroup form always.
+    ResWall res_wall;
+    bool wall_lines = true;
+    ResPlan res_plan;
+    bool res_planned = false, res_now = false;
+    int res_mode = 1, cus = 0;
+    hipEvent_t res_event = nullptr;  // end of this box's last steps with resident launches
     bool fused_lf = true;  // Lorentz + fluid in one launch where the storage allows (MHD_FUSED_LF=0: two)
     // Scratch of the step kernels taken from elsewhere than the workspace while set (the
     // allocation-free entry point): Lorentz force F, wall corrections, flow and budget partials.
@@ -463,12 +480,52 @@ mhd_status mag_iteration(mhd_sim *s, const StepConst &c, int m) {
     return MHD_OK;
 }
 
+// All sweeps of a step and their wall corrections in one launch (and its one-workgroup stand-in).
+mhd_status resident_iteration(mhd_sim *s, const StepConst &c) {
+    const ResPlan &p = s->res_plan;
+    ResArgs a{};
+    a.u = static_cast<const float *>(s->u(s->cu));
+    a.b[0] = static_cast<float *>(s->b(s->cb));
+    a.b[1] = static_cast<float *>(s->b(1 - s->cb));
+    a.bext = s->at<float>(s->L.bext);
+    a.bext_yz = s->byz();
+    a.sj = s->at<float>(s->L.s_b);
+    a.wall = s->at<float>(s->L.bwall);
+    a.M = s->M;
+    a.km4 = p.km4;
+    a.nx = c.nx;
+    a.ny = c.ny;
+    a.nz = c.nz;
+    a.ty = p.ty;
+    a.tz = p.tz;
+    a.gy = p.gy;
+    a.nwg = p.nwg;
+    a.slots = p.slots;
+    a.mk_max = p.mk_max;
+    a.n_mag = s->prm.n_mag;
+    a.kappa = c.kappa;
+    a.omega = c.omega;
+    a.tab_off = s->at<int>(s->L.res_tab);
+    a.tab = a.tab_off + p.nwg + 1;
+    a.sync = s->at<int>(s->L.res_sync);
+    a.status = c.status;
+    a.roll_ticks = s->res_mode == 2 ? -1 : kResRollTicks;
+    const hipError_t e = launch_mag_resident(s->stream, a, p, c.lattice == 27);
+    if (e != hipSuccess) return fail(MHD_ERR_HIP, "launch of the magnetic iteration failed: %s", hipGetErrorString(e));
+    if ((s->prm.n_mag & 1) == 0) s->cb = 1 - s->cb;  // the result is in b[1 - (n_mag & 1)]
+    return MHD_OK;
+}
+
 mhd_status one_step(mhd_sim *s) {
     const StepConst c = step_const(s);
     hipStream_t st = s->stream;
     STEPCHK(timed(s, MHD_K_CONTROL, "ctrl_begin", [&] { return launch_ctrl_begin(st, s->ctrl(), c); }));
     // 1. magnetic iteration, wall correction after every sweep
-    for (int m = 0; m < s->prm.n_mag; ++m) STEPCHK(mag_iteration(s, c, m));
+    if (s->res_now) {
+        STEPCHK(resident_iteration(s, c));
+    } else {
+        for (int m = 0; m < s->prm.n_mag; ++m) STEPCHK(mag_iteration(s, c, m));
+    }
     // 2. Lorentz + body force from the new b, 3. fluid predictor (one launch for float32 boxes:
     // the force then stays in LDS), 4. velocity wall correction
     const int nr = 1 - s->cr, nu = 1 - s->cu;
@@ -521,6 +578,12 @@ mhd_status record_budget(mhd_sim *s) {
 mhd_status read_ctrl(mhd_sim *s, DevCtrl *h) {
     HIPCHK(hipMemcpyAsync(h, s->ctrl(), sizeof(DevCtrl), hipMemcpyDeviceToHost, s->stream));
     HIPCHK(hipStreamSynchronize(s->stream));
+    return MHD_OK;
+}
+
+mhd_status state_status(const DevCtrl &h) {
+    if (h.status & kStatusStalled) return fail(MHD_ERR_HIP, "the magnetic iteration of a step stalled on the GPU: the state is lost");
+    if (h.status & 1) return fail(MHD_ERR_UNSTABLE, "a fluid step or a budget pass found non-finite values or |u| >= c_s");
     return MHD_OK;
 }
 
@@ -584,6 +647,89 @@ SweepLaunch default_tiles(const mhd_grid_desc &g) {
     L.zchunk = std::max(1, env_int("MHD_SWEEP_ZCHUNK", L.zchunk));
     return L;
 }
+
+// One call that steps a box: decides whether its steps run the resident iteration, and orders such
+// calls of one process on one GPU. Workgroups of a resident launch wait for each other, so those
+// in flight at once must fit the chip together: a call whose workgroups would not fit beside the
+// unfinished ones of other boxes waits for them on the GPU (the roll call in the kernel covers what
+// this process cannot see). Held from the decision to the last launch.
+struct ResidentUse {
+    mhd_sim *sim;
+    int device, nwg;
+};
+std::mutex g_res_mu;
+std::vector<ResidentUse> g_res_use;  // boxes whose last call had resident launches
+
+class ResidentCall {
+  public:
+    explicit ResidentCall(mhd_sim *sim) : s(sim) {}
+    ~ResidentCall() {
+        if (s->res_now) (void)end();  // an error left the call early: what it launched is in flight
+    }
+    mhd_status begin() {
+        s->res_now = false;
+        if (s->res_mode == 0 || s->prof || !s->L.res_sync || !s->wall_lines) return MHD_OK;
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s->stream, &cap) != hipSuccess) {
+            (void)hipGetLastError();
+            return MHD_OK;
+        }
+        if (cap != hipStreamCaptureStatusNone) return MHD_OK;  // a caller's graph: replayed at times unknown here
+        if (!s->res_planned) STEPCHK(plan());
+        if (!s->res_plan.ok) return MHD_OK;
+        if (!s->res_event) HIPCHK(hipEventCreateWithFlags(&s->res_event, hipEventDisableTiming));
+        lock = std::unique_lock<std::mutex>(g_res_mu);
+        int others = 0;
+        for (const ResidentUse &x : g_res_use)
+            if (x.sim != s && x.device == s->device && hipEventQuery(x.sim->res_event) == hipErrorNotReady) others += x.nwg;
+        (void)hipGetLastError();
+        if (others > 0 && others + s->res_plan.nwg > s->cus)
+            for (const ResidentUse &x : g_res_use)
+                if (x.sim != s && x.device == s->device) HIPCHK(hipStreamWaitEvent(s->stream, x.sim->res_event, 0));
+        s->res_now = true;
+        return MHD_OK;
+    }
+    mhd_status end() {
+        if (!s->res_now) return MHD_OK;
+        s->res_now = false;
+        const hipError_t e = hipEventRecord(s->res_event, s->stream);
+        auto at = std::find_if(g_res_use.begin(), g_res_use.end(), [&](const ResidentUse &x) { return x.sim == s; });
+        if (at == g_res_use.end())
+            g_res_use.push_back({s, s->device, s->res_plan.nwg});
+        else
+            at->nwg = s->res_plan.nwg;
+        lock.unlock();
+        if (e != hipSuccess) return fail(MHD_ERR_HIP, "hipEventRecord failed: %s", hipGetErrorString(e));
+        return MHD_OK;
+    }
+    static void forget(mhd_sim *s) {
+        std::lock_guard<std::mutex> g(g_res_mu);
+        g_res_use.erase(std::remove_if(g_res_use.begin(), g_res_use.end(), [&](const ResidentUse &x) { return x.sim == s; }),
+                        g_res_use.end());
+    }
+
+  private:
+    mhd_sim *s;
+    std::unique_lock<std::mutex> lock;
+
+    mhd_status plan() {
+        HIPCHK(hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, s->device));
+        drop_step_graphs(s);
+        s->res_plan = make_resident_plan(s->g.nx, s->g.ny, s->g.nz, s->res_wall, s->cus);
+        ResPlan &p = s->res_plan;
+        if (p.ok) {
+            HIPCHK(hipMemcpyAsync(s->ws + s->L.res_tab, p.tab_off.data(), p.tab_off.size() * sizeof(int), hipMemcpyHostToDevice,
+                                  s->stream));
+            HIPCHK(hipMemcpyAsync(s->ws + s->L.res_tab + p.tab_off.size() * sizeof(int), p.tab.data(),
+                                  p.tab.size() * sizeof(int), hipMemcpyHostToDevice, s->stream));
+            HIPCHK(hipStreamSynchronize(s->stream));
+            p.tab = std::vector<int>();
+            p.tab_off = std::vector<int>();
+        }
+        s->res_planned = true;
+        return MHD_OK;
+    }
+};
 
 // The tile choice a launch really uses (the paired form needs nx % 128 == 0).
 SweepLaunch effective_tiles(const SweepLaunch &L, int nx) {
@@ -804,7 +950,7 @@ mhd_status mhd_set_markers(mhd_sim *s, const double *xyz, int64_t M, const doubl
     //     same taps and entries in the same order.
     const int64_t nlines = lines ? M / nx : 0;
     const int64_t nrows = lines ? nband / nx : 0;
-    bool ring = lines && nx % 64 == 0 && nband % nx == 0;
+    bool ring = lines && nband % nx == 0;
     std::vector<int> ring_tap, row_off, row_mk;
     std::vector<float> ring_tw, row_w;
     if (ring) {
@@ -840,8 +986,19 @@ mhd_status mhd_set_markers(mhd_sim *s, const double *xyz, int64_t M, const doubl
                 ring = band_mk[(size_t)q * nband + e] == row_mk[(size_t)(r * km + q)] * nx + x &&
                        band_w[(size_t)q * nband + e] == row_w[(size_t)(r * km + q)];
         }
-        ring = ring && nlines * tm <= s->Mcap && nrows <= s->Mcap && nrows * km <= s->Mcap;
     }
+    ResWall rw;  // the same tables in rows y + ny z for the resident iteration (any n_x)
+    if (ring) {
+        rw.tm = tm;
+        rw.km = km;
+        rw.tap_w = ring_tw;
+        rw.band_w = row_w;
+        rw.band_line = row_mk;
+        for (int v : ring_tap) rw.tap_row.push_back(v / nx);
+        for (int v : row_off) rw.band_row.push_back(v / nx);
+    }
+    const bool wall_lines = ring || M == 0;
+    ring = ring && nx % 64 == 0 && nlines * tm <= s->Mcap && nrows <= s->Mcap && nrows * km <= s->Mcap;
     // 5. wall values in internal order
     std::vector<float> uw((size_t)(3 * M), 0.f), bw((size_t)(3 * M), 0.f);
     for (int64_t i = 0; i < M; ++i)
@@ -876,6 +1033,9 @@ mhd_status mhd_set_markers(mhd_sim *s, const double *xyz, int64_t M, const doubl
     HIPCHK(hipStreamSynchronize(s->stream));
     s->lines = ring;
     s->ring_on = ring && ring_mode != 0;
+    s->res_wall = std::move(rw);
+    s->wall_lines = wall_lines && ring_mode != 0;
+    s->res_planned = false;
     s->M = M;
     s->nband = nband;
     s->tm = tm;
@@ -886,6 +1046,8 @@ mhd_status mhd_set_markers(mhd_sim *s, const double *xyz, int64_t M, const doubl
     if (st != MHD_OK) {  // the wall is dropped rather than left half-configured
         s->M = 0;
         s->nband = 0;
+        s->res_wall = ResWall{};
+        s->wall_lines = true;
         return st;
     }
     return MHD_OK;
@@ -923,6 +1085,7 @@ mhd_status mhd_set_params(mhd_sim *s, const mhd_params *p) {
     const mhd_params old = s->prm;
     drop_step_graphs(s);
     s->fused_lf = env_int("MHD_FUSED_LF", 1) != 0;
+    s->res_mode = env_int("MHD_RESIDENT", 1);
     s->prm = *p;
     s->have_params = true;
     if (s->owner) batch_touch(s->owner);
@@ -999,8 +1162,7 @@ mhd_status mhd_get_field(mhd_sim *s, mhd_field f, double *host) {
     }
     DevCtrl h;
     STEPCHK(read_ctrl(s, &h));
-    if (h.status & 1) return fail(MHD_ERR_UNSTABLE, "a fluid step or a budget pass found non-finite values or |u| >= c_s");
-    return MHD_OK;
+    return state_status(h);
 }
 
 mhd_status mhd_get_time(mhd_sim *s, int64_t *t, double *G) {
@@ -1031,12 +1193,14 @@ mhd_status mhd_set_time(mhd_sim *s, int64_t t, double G) {
 mhd_status mhd_step(mhd_sim *s, int64_t n_steps, int32_t budget_every) {
     g_err.clear();
     STEPCHK(step_checks(s, n_steps));
+    ResidentCall resident(s);
+    STEPCHK(resident.begin());
     // On a caller stream the step is captured once per buffer state and replayed as a HIP graph
     // (one launch call per step instead of about 3 n_mag + 6); profiling steps launch directly.
     const bool graph = s->graph_on && s->stream != nullptr && !s->prof;
     for (int64_t i = 0; i < n_steps; ++i) {
         if (graph) {
-            const int key = s->cb | (s->cr << 1) | (s->cu << 2) | (s->ch << 3);
+            const int key = s->cb | (s->cr << 1) | (s->cu << 2) | (s->ch << 3) | (s->res_now ? 16 : 0);
             auto it = std::find_if(s->graphs.begin(), s->graphs.end(), [&](const mhd_sim::StepGraph &g) { return g.key == key; });
             if (it == s->graphs.end()) {
                 const int cb = s->cb, cr = s->cr, cu = s->cu, ch = s->ch;
@@ -1073,7 +1237,7 @@ mhd_status mhd_step(mhd_sim *s, int64_t n_steps, int32_t budget_every) {
         }
         if (budget_every > 0 && s->t_host % budget_every == 0) STEPCHK(record_budget(s));
     }
-    return MHD_OK;
+    return resident.end();
 }
 
 }  // extern "C"
@@ -1108,13 +1272,14 @@ mhd_status step_in_scratch(mhd_sim *s, int64_t n_steps, int32_t budget_every, vo
     s->scr.delta = reinterpret_cast<float *>(base + off[1]);
     s->scr.flow = reinterpret_cast<double *>(base + off[2]);
     s->scr.red = reinterpret_cast<double *>(base + off[3]);
-    mhd_status st = MHD_OK;
+    ResidentCall resident(s);
+    mhd_status st = resident.begin();
     for (int64_t i = 0; i < n_steps && st == MHD_OK; ++i) {  // direct launches: no graph holds these pointers
         st = one_step(s);
         if (st == MHD_OK && budget_every > 0 && s->t_host % budget_every == 0) st = record_budget(s);
     }
     s->scr = mhd_sim::Scratch{};
-    return st;
+    return st == MHD_OK ? resident.end() : st;
 }
 
 mhd_status step_checks(mhd_sim *s, int64_t n_steps) {
@@ -1284,8 +1449,7 @@ mhd_status mhd_get_budgets(mhd_sim *s, mhd_budget *out, int64_t cap, int64_t *n_
     HIPCHK(launch_reset_records(s->stream, s->ctrl()));
     HIPCHK(hipStreamSynchronize(s->stream));
     *n_out = n;
-    if (h.status & 1) return fail(MHD_ERR_UNSTABLE, "a fluid step or a budget pass found non-finite values or |u| >= c_s");
-    return MHD_OK;
+    return state_status(h);
 }
 
 mhd_status mhd_set_profiling(mhd_sim *s, int32_t enable) {
@@ -1318,6 +1482,8 @@ mhd_status mhd_destroy(mhd_sim *s) {
     if (s->owner) return fail(MHD_ERR_STATE, "this box belongs to a batch: free it with mhd_batch_destroy");
     drop_step_graphs(s);
     (void)hipStreamSynchronize(s->stream);
+    ResidentCall::forget(s);
+    if (s->res_event) (void)hipEventDestroy(s->res_event);
     for (int k = 0; k < MHD_K_COUNT; ++k)
         for (auto &e : s->ev_pool[k]) {
             (void)hipEventDestroy(e.a);

@@ -6,23 +6,9 @@
 #include <type_traits>
 
 #include "mhd_device.h"
+#include "mhd_sweep_math.h"
 
 namespace mhd {
-
-// Weights of the plane decomposition: a0f, a0c = in-plane face and corner neighbours of the
-// cell's own plane; a1c, a1f, a1k = centre, face and corner of a neighbouring plane.
-// D3Q19: 1/18, 1/36 | 1/18, 1/36, 0.  D3Q27 (the product of the 1D weights 2/3, 1/6, 1/6):
-// 2/27, 1/54 | 2/27, 1/54, 1/216. Both give a neighbouring plane the total weight 1/6.
-template <bool Q27>
-struct Lat {
-    static constexpr float A0F = 1.0f / 18.0f, A0C = 1.0f / 36.0f, A1C = 1.0f / 18.0f, A1F = 1.0f / 36.0f,
-                           A1K = 0.0f;
-};
-template <>
-struct Lat<true> {
-    static constexpr float A0F = 2.0f / 27.0f, A0C = 1.0f / 54.0f, A1C = 2.0f / 27.0f, A1F = 1.0f / 54.0f,
-                           A1K = 1.0f / 216.0f;
-};
 
 // -------------------------------------------------------------------------------------------
 // Magnetic sweep (Sec. 5.7): tau_m = 1, particle speed c = 6 eta, so c_i / c_s^2 = e_i / (2 eta).
@@ -62,7 +48,8 @@ struct Lat<true> {
 // increment into a new hi = fp16(v) and lo = fp16(v - hi).
 // -------------------------------------------------------------------------------------------
 template <int TX, int TY, typename TU, typename TB, bool BATCH, bool SPLIT, bool BYZ, bool Q27>
-__global__ void __launch_bounds__(TX *TY) k_mag_sweep(SweepArgs a, const PipeStep *tab, const BlockMap *map,
+__global__ void __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(std::is_same<TB, float>::value && !BYZ ? 4 : 1)))
+k_mag_sweep(SweepArgs a, const PipeStep *tab, const BlockMap *map,
                                                       int which, int nbatch) {
     using LW = Lat<Q27>;
     constexpr int NT = TX * TY, HX = TX + 2, HY = TY + 2, HN = HX * HY;
@@ -161,6 +148,9 @@ __global__ void __launch_bounds__(TX *TY) k_mag_sweep(SweepArgs a, const PipeSte
     };
 
     const int c0 = (ly + 1) * HX + (lx + 1);
+    constexpr bool F32 = std::is_same<TB, float>::value;  // shared float32 arithmetic (mhd_sweep_math.h)
+    const SweepWeights W = sweep_weights<Q27>(a.kappa, a.omega);
+    March<1> march;
     const float kap = a.kappa * a.u_scale;
     constexpr float W6 = 1.0f / 6.0f;  // total weight of a neighbouring plane (both lattices)
     // running sums of the plane contributions (difference form), and the column's own values
@@ -199,9 +189,13 @@ __global__ void __launch_bounds__(TX *TY) k_mag_sweep(SweepArgs a, const PipeSte
                 s_pl[S][0][i] = bx;
                 s_pl[S][1][i] = by;
                 s_pl[S][2][i] = bz;
-                s_pl[S][3][i] = kap * (uy * Bx - ux * By);
-                s_pl[S][4][i] = kap * (uz * Bx - ux * Bz);
-                s_pl[S][5][i] = kap * (uz * By - uy * Bz);
+                if constexpr (F32) {
+                    sweep_flux(Bx, By, Bz, ux, uy, uz, s_pl[S][3][i], s_pl[S][4][i], s_pl[S][5][i]);
+                } else {
+                    s_pl[S][3][i] = kap * (uy * Bx - ux * By);
+                    s_pl[S][4][i] = kap * (uz * Bx - ux * Bz);
+                    s_pl[S][5][i] = kap * (uz * By - uy * Bz);
+                }
             }
         }
     };
@@ -242,7 +236,24 @@ __global__ void __launch_bounds__(TX *TY) k_mag_sweep(SweepArgs a, const PipeSte
         const int cur = P;
         const float *s_bx = s_pl[cur][0], *s_by = s_pl[cur][1], *s_bz = s_pl[cur][2];
         const float *s_lxy = s_pl[cur][3], *s_lxz = s_pl[cur][4], *s_lyz = s_pl[cur][5];
-        if (own) {
+        if constexpr (F32) {
+            if (own) {
+                float S[1][3], B[1][3], Pz[1][2], cen[1][3], out[1][3];
+                auto rows = [&](int k, float (&v)[3][3]) {
+#pragma unroll
+                    for (int r = 0; r < 3; ++r)
+#pragma unroll
+                        for (int j = 0; j < 3; ++j) v[r][j] = s_pl[cur][k][c0 + (r - 1) * HX + (j - 1)];
+                };
+                plane_terms<1, Q27>(rows, W, S, B, Pz, cen);
+                march.take(W, S, B, Pz, cen, out);
+                if (p >= z0 + 1) {
+                    st_off(o0, ko, out[0][0]);
+                    st_off(o1, ko, out[0][1]);
+                    st_off(o2, ko, out[0][2]);
+                }
+            }
+        } else if (own) {
             // b components: centre value and in-plane sums of differences to it
             //   dP0 = sum_faces a0f (f - c) + sum_corners a0c (f - c),
             //   dP1 = sum_faces a1f (f - c) [+ sum_corners a1k (f - c) on D3Q27]
@@ -405,10 +416,10 @@ struct Pair<__hip_bfloat16> {
 // Neighbouring lane's value across the whole wave (DPP wave rotation): lane l receives the value
 // of lane l - 1 (ror) or l + 1 (rol), lane 0 that of lane 63 and lane 63 that of lane 0.
 __device__ __forceinline__ float wave_ror1(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x13C, 0xf, 0xf, false));
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x13C, 0xf, 0xf, true));
 }
 __device__ __forceinline__ float wave_rol1(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x134, 0xf, 0xf, false));
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x134, 0xf, 0xf, true));
 }
 
 // The halo form (without the six-magnet table) is held to three waves per SIMD (at most 168
@@ -471,6 +482,9 @@ k_mag_sweep_pair(SweepArgs a, const PipeStep *tab, const BlockMap *map,
     const float b0f = LW::A0F * om, b0c = LW::A0C * om, b1f = LW::A1F * om, b1k = LW::A1K * om;
     const float l0f = LW::A0F * ko, l0c = LW::A0C * ko, l1c = LW::A1C * ko, l1f = LW::A1F * ko, l1k = LW::A1K * ko;
     const float w6 = (1.0f / 6.0f) * om;  // total weight of a neighbouring plane (both lattices)
+    constexpr bool F32 = std::is_same<TB, float>::value;  // shared float32 arithmetic (mhd_sweep_math.h)
+    const SweepWeights W = sweep_weights<Q27>(a.kappa, a.omega);
+    March<2> march;
 
     // Staging (float32 with XWRAP: QUAD below, 16-byte loads staging two rows per wave): wave w
     // stages row hy = w (its own pair of cells per lane). With 4-row tiles the
@@ -598,9 +612,13 @@ k_mag_sweep_pair(SweepArgs a, const PipeStep *tab, const BlockMap *map,
         s_pl[buf][0][idx] = bx;
         s_pl[buf][1][idx] = by;
         s_pl[buf][2][idx] = bz;
-        s_pl[buf][3][idx] = uy * Bx - ux * By;
-        s_pl[buf][4][idx] = uz * Bx - ux * Bz;
-        s_pl[buf][5][idx] = uz * By - uy * Bz;
+        if constexpr (F32) {
+            sweep_flux(Bx, By, Bz, ux, uy, uz, s_pl[buf][3][idx], s_pl[buf][4][idx], s_pl[buf][5][idx]);
+        } else {
+            s_pl[buf][3][idx] = uy * Bx - ux * By;
+            s_pl[buf][4][idx] = uz * Bx - ux * Bz;
+            s_pl[buf][5][idx] = uz * By - uy * Bz;
+        }
     };
     auto stage = [&](auto bufc) {
         constexpr int S = decltype(bufc)::value;
@@ -752,6 +770,11 @@ k_mag_sweep_pair(SweepArgs a, const PipeStep *tab, const BlockMap *map,
                     }
                 }
             };
+            float out[2][3];
+            if constexpr (F32) {
+                plane_terms<2, Q27>(rows, W, S, B, Pz, cen);
+                march.take(W, S, B, Pz, cen, out);
+            } else {
             // b components: face and corner sums of differences to each centre, taken against
             // the first centre r0 and shifted by 4 (c1 - r0) for the second cell; the column
             // sums t_j of rows y-1 and y+1 serve both cells
@@ -841,7 +864,6 @@ k_mag_sweep_pair(SweepArgs a, const PipeStep *tab, const BlockMap *map,
                     if constexpr (Q27) S[e][2] = fmaf(-l1k, cdy, S[e][2]);
                 }
             }
-            float out[2][3];
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
 #pragma unroll
@@ -858,6 +880,7 @@ k_mag_sweep_pair(SweepArgs a, const PipeStep *tab, const BlockMap *map,
                     cc[e][k] = cen[e][k];
                     dz[e][k] = dzc;
                 }
+            }
             }
             if (p >= z0 + 1) {
                 RB *oo[3] = {reinterpret_cast<RB *>(o0), reinterpret_cast<RB *>(o1), reinterpret_cast<RB *>(o2)};

@@ -1,0 +1,138 @@
+"""The resident magnetic iteration (all sweeps of a step and their wall corrections in one launch)
+against the launch sequence of a sweep, an interpolation and a spreading per iteration: the same
+fields bit for bit. MHD_RESIDENT at mhd_set_params selects the form: 0 = launch sequence, 1 = resident
+where the box fits, 2 = its one-workgroup stand-in, which a launch whose workgroups do not all
+become resident leaves the work to (roll call given up by the first workgroup)."""
+import threading
+
+import numpy as np
+import pytest
+
+import workloads as W
+from tests.test_gpu_parity import TOL, compare, oracle_run, random_box
+
+pytestmark = pytest.mark.gpu
+
+
+def box(case):
+    """(workload, parameter overrides, use the wall)"""
+    if case == "pipe_walls":  # nonzero wall values, odd count
+        return W.small_pipe(rho_amp=1e-3, b_amp=1e-3, n_mag=5), {}, True
+    if case == "cube_even":
+        return random_box(32, 32, 32, key=400, n_mag=4, R=13.0), {}, True
+    if case == "ragged_tiles":  # tiles that do not divide the cross-section, a box shorter than a wave
+        return random_box(5, 47, 53, key=401, n_mag=3, R=20.0), {}, True
+    if case == "one_sweep":
+        return random_box(37, 21, 13, key=402, n_mag=1, R=5.0), {}, True
+    if case == "no_wall":
+        return random_box(9, 14, 30, key=403, n_mag=4), {}, False
+    if case == "one_cell_wide":  # every halo row wraps onto the tile itself
+        return random_box(1, 24, 1, key=404, n_mag=3), {}, False
+    if case == "six_magnets":
+        return W.pipe_workload("six", 405, 16, 33, 33, 14.0, 50.0, 10.0, 1e-2, bext_kind=W.BEXT_SIX_MAGNETS, n_mag=4,
+                               b_amp=1e-3, noise=1e-2), {}, True
+    if case == "q27_accelerated":
+        return random_box(20, 26, 22, key=406, n_mag=4, R=8.0), dict(lattice=27, alpha=0.5), True
+    if case == "long_rows":  # several staged rows and a tall column per work-item
+        return random_box(100, 40, 44, key=407, n_mag=3, R=15.0), {}, True
+    if case == "pair_width":  # n_x = 128: the launch sequence is the paired sweep
+        return random_box(128, 20, 22, key=408, n_mag=3, R=7.0), {}, True
+    if case == "wall_through_the_faces":  # markers whose taps wrap around the box
+        w = random_box(12, 24, 24, key=409, n_mag=3, R=11.9)
+        return w, {}, True
+    raise KeyError(case)
+
+
+CASES = ("pipe_walls", "cube_even", "ragged_tiles", "one_sweep", "no_wall", "one_cell_wide", "six_magnets",
+         "q27_accelerated", "long_rows", "pair_width", "wall_through_the_faces")
+
+
+def make(w, over, wall, mode, monkeypatch):
+    from paper_2211_09370_amd import Sim
+
+    monkeypatch.setenv("MHD_RESIDENT", mode)
+    M = w.markers.shape[1] if wall else 0
+    sim = Sim(w.nx, w.ny, w.nz, M)
+    if M:
+        g = np.random.default_rng(77)
+        sim.set_markers(w.markers, u_wall=g.uniform(-1e-4, 1e-4, (3, M)), b_wall=g.uniform(-1e-4, 1e-4, (3, M)))
+    sim.set_params(w.params, **over)
+    for f in ("rho", "u", "b"):
+        sim.set_field(f, getattr(w, f))
+    return sim
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_resident_equals_the_launch_sequence_bitwise(case, monkeypatch):
+    print("case resident", case, flush=True)
+    w, over, wall = box(case)
+    out = {}
+    for mode in ("0", "1", "2"):
+        sim = make(w, over, wall, mode, monkeypatch)
+        sim.step(3)  # captured and replayed
+        sim.set_graph(False)
+        sim.step(1)
+        sim.step_noalloc(1)
+        out[mode] = [sim.get_field(f) for f in ("rho", "u", "b")]
+        sim.close()
+    for mode in ("1", "2"):
+        for f, x, y in zip(("rho", "u", "b"), out["0"], out[mode]):
+            assert np.array_equal(x, y), (case, mode, f, float(np.abs(x - y).max()))
+
+
+def test_resident_matches_the_oracle(monkeypatch):
+    print("case resident oracle", flush=True)
+    w = W.quarter_fringe_pipe(n_mag=24)
+    from paper_2211_09370_amd import Sim
+
+    sim = Sim(w.nx, w.ny, w.nz, w.markers.shape[1])
+    sim.set_markers(w.markers)
+    sim.set_params(w.params)
+    for f in ("rho", "u", "b"):
+        sim.set_field(f, getattr(w, f))
+    sim.step(4)
+    compare(sim, oracle_run(w, 4), tol=TOL, label="resident")
+    sim.close()
+
+
+def test_resident_boxes_on_several_streams_and_threads(monkeypatch):
+    """Four boxes whose workgroups would not fit the chip together, each stepped by a thread of its
+    own on its own stream, then all from one thread in turn: the fields of each equal those of a
+    box stepped alone."""
+    print("case resident threads", flush=True)
+    w, over, wall = box("ragged_tiles")
+    ref = make(w, over, wall, "0", monkeypatch)
+    ref.step(44)
+    want = [ref.get_field(f) for f in ("rho", "u", "b")]
+    ref.close()
+    sims = [make(w, over, wall, "1", monkeypatch) for _ in range(4)]
+    threads = [threading.Thread(target=lambda s=s: [s.step(4) for _ in range(10)]) for s in sims]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for s in sims:
+        s.step(4)
+    for s in sims:
+        assert all(np.array_equal(s.get_field(f), x) for f, x in zip(("rho", "u", "b"), want))
+        s.close()
+
+
+def test_new_markers_and_parameters_between_steps(monkeypatch):
+    """The plan follows the wall: markers replaced, then removed, between steps."""
+    print("case resident replan", flush=True)
+    w, over, wall = box("cube_even")
+    other = W.pipe_markers(32, 9.0, 16.0, 16.0)
+    out = []
+    for mode in ("0", "1"):
+        sim = make(w, over, wall, mode, monkeypatch)
+        sim.step(2)
+        sim.set_markers(other)
+        sim.step(1)
+        sim.set_params(w.params, n_mag=7)
+        sim.step(1)
+        sim.set_markers(np.zeros((3, 0)))
+        sim.step(1)
+        out.append([sim.get_field(f) for f in ("rho", "u", "b")])
+        sim.close()
+    assert all(np.array_equal(x, y) for x, y in zip(*out))

@@ -163,6 +163,9 @@ struct BlockMap {             // (box, workgroup within the box) of workgroup i 
 };
 hipError_t launch_ctrl_begin_batch(hipStream_t s, const PipeStep *tab, int n);
 hipError_t launch_step_end_batch(hipStream_t s, const PipeStep *tab, int n);
+// The float32 sweep of tiles of 128 cells and 8 rows (mhd_sweep_rows.hip), single box or batched.
+hipError_t launch_sweep_rows(hipStream_t s, bool batch, const SweepArgs &a, SweepLaunch L, const PipeStep *tab,
+                             const BlockMap *map, int which, int nblocks, hipEvent_t e0, hipEvent_t e1);
 hipError_t launch_mag_sweep_batch(hipStream_t s, int kinds, SweepLaunch L, const PipeStep *tab, const BlockMap *map,
                                   int parity, int nblocks, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 hipError_t launch_ib_interp_batch(hipStream_t s, int kind, const PipeStep *tab, const BlockMap *map, int which,

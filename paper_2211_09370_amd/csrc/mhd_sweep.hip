@@ -972,21 +972,25 @@ static hipError_t sweep_typed(hipStream_t s, const SweepArgs &a, SweepLaunch L, 
     if (L.pair) {
         if constexpr (!BATCH) {
             if (a.nx == 128) {  // one tile per row: x neighbours by wave rotation
-                if (L.ty >= 8)
-                    hipExtLaunchKernelGGL(k_mag_sweep_pair<8, TU, TB, false, SPLIT, BYZ, Q27, true>, grid, dim3(512), 0, s, e0, e1,
-                                          0, a, tab, map, which, nblocks);
-                else
-                    hipExtLaunchKernelGGL(k_mag_sweep_pair<4, TU, TB, false, SPLIT, BYZ, Q27, true>, grid, dim3(256), 0, s, e0, e1,
-                                          0, a, tab, map, which, nblocks);
+                if constexpr (!std::is_same<TB, float>::value)
+                    if (L.ty >= 8) {
+                        hipExtLaunchKernelGGL(k_mag_sweep_pair<8, TU, TB, false, SPLIT, BYZ, Q27, true>, grid, dim3(512), 0, s, e0,
+                                              e1, 0, a, tab, map, which, nblocks);
+                        return hipGetLastError();
+                    }
+                hipExtLaunchKernelGGL(k_mag_sweep_pair<4, TU, TB, false, SPLIT, BYZ, Q27, true>, grid, dim3(256), 0, s, e0, e1, 0, a,
+                                      tab, map, which, nblocks);
                 return hipGetLastError();
             }
         }
-        if (L.ty >= 8)
-            hipExtLaunchKernelGGL(k_mag_sweep_pair<8, TU, TB, BATCH, SPLIT, BYZ, Q27, false>, grid, dim3(512), 0, s, e0, e1, 0, a, tab, map,
-                                  which, nblocks);
-        else
-            hipExtLaunchKernelGGL(k_mag_sweep_pair<4, TU, TB, BATCH, SPLIT, BYZ, Q27, false>, grid, dim3(256), 0, s, e0, e1, 0, a, tab, map,
-                                  which, nblocks);
+        if constexpr (!std::is_same<TB, float>::value)
+            if (L.ty >= 8) {
+                hipExtLaunchKernelGGL(k_mag_sweep_pair<8, TU, TB, BATCH, SPLIT, BYZ, Q27, false>, grid, dim3(512), 0, s, e0, e1, 0, a,
+                                      tab, map, which, nblocks);
+                return hipGetLastError();
+            }
+        hipExtLaunchKernelGGL(k_mag_sweep_pair<4, TU, TB, BATCH, SPLIT, BYZ, Q27, false>, grid, dim3(256), 0, s, e0, e1, 0, a, tab, map,
+                              which, nblocks);
         return hipGetLastError();
     }
     switch (L.tx) {
@@ -1015,6 +1019,10 @@ template <bool BATCH, bool BYZ>
 static hipError_t sweep_kinds_yz(hipStream_t s, int kinds, const SweepArgs &a, SweepLaunch L, const PipeStep *tab,
                                  const BlockMap *map, int which, int nblocks, hipEvent_t e0, hipEvent_t e1) {
     const int ku = (kinds >> 4) & 15, kb = (kinds >> 8) & 15;
+    // float32 tiles of 8 rows have a kernel of their own; those of 4 rows are faster here (both measured
+    // there)
+    if (L.pair && L.ty >= 8 && ku == MHD_KIND_F32 && kb == MHD_KIND_F32)
+        return launch_sweep_rows(s, BATCH, a, L, tab, map, which, nblocks, e0, e1);
     if (L.q27) {  // D3Q27: float32 and the split form
         if (ku == MHD_KIND_F32 && kb == MHD_KIND_F32)
             return sweep_typed<float, float, BATCH, false, BYZ, true>(s, a, L, tab, map, which, nblocks, e0, e1);

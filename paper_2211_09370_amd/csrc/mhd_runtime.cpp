@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -45,6 +46,12 @@ mhd_status fail(mhd_status st, const char *fmt, ...) {
     do {                                                                                               \
         hipError_t e_ = (call);                                                                        \
         if (e_ != hipSuccess) return fail(MHD_ERR_HIP, "%s failed: %s", #call, hipGetErrorString(e_)); \
+    } while (0)
+
+#define STEPCHK(x)                     \
+    do {                               \
+        mhd_status st_ = (x);          \
+        if (st_ != MHD_OK) return st_; \
     } while (0)
 
 size_t kind_bytes(int k) { return k == MHD_STORE_F32 ? 4 : 2; }
@@ -152,6 +159,25 @@ struct Event2 {
     hipEvent_t a, b;
 };
 
+// Host copies of fields go through pinned chunks of this many floats; several are in flight.
+constexpr size_t kIoChunk = size_t(1) << 18;
+constexpr int kIoSlots = 4;
+
+// Pinned staging of the field copies, allocated by the first one (at most kIoSlots chunks, 4 MB) and
+// freed with the solver, and the events that say when a chunk's copy has ended. Held by one copy at a
+// time.
+struct HostIo {
+    std::mutex mu;
+    float *buf = nullptr;
+    size_t chunk = 0, slots = 0;
+    hipEvent_t ev[kIoSlots] = {};
+    ~HostIo() {
+        for (hipEvent_t e : ev)
+            if (e) (void)hipEventDestroy(e);
+        if (buf) (void)hipHostFree(buf);
+    }
+};
+
 }  // namespace
 
 struct mhd_sim {
@@ -200,6 +226,7 @@ struct mhd_sim {
     bool res_planned = false, res_now = false;
     int res_mode = 1, cus = 0;
     hipEvent_t res_event = nullptr;  // end of this box's last steps with resident launches
+    std::shared_ptr<HostIo> io = std::make_shared<HostIo>();  // one for all boxes of a batch
     bool fused_lf = true;  // Lorentz + fluid in one launch where the storage allows (MHD_FUSED_LF=0: two)
     // Scratch of the step kernels taken from elsewhere than the workspace while set (the
     // allocation-free entry point): Lorentz force F, wall corrections, flow and budget partials.
@@ -370,7 +397,63 @@ mhd_status upload_bext(mhd_sim *s) {
     return MHD_OK;
 }
 
-mhd_status fill_field(mhd_sim *s, mhd_field f, const double *host, bool zero) {
+// Pinned chunks for copies of up to n floats, and 64 floats behind them for the control block.
+mhd_status io_buffers(HostIo &io, size_t n) {
+    const size_t chunk = std::min(n, kIoChunk), slots = n > kIoChunk ? kIoSlots : 1;
+    if (io.chunk >= chunk && io.slots >= slots) return MHD_OK;
+    if (io.buf) (void)hipHostFree(io.buf);
+    io.buf = nullptr;
+    io.chunk = io.slots = 0;
+    void *p = nullptr;
+    HIPCHK(hipHostMalloc(&p, (slots * chunk + 64) * sizeof(float), hipHostMallocDefault));
+    io.buf = static_cast<float *>(p);
+    io.chunk = chunk;
+    io.slots = slots;
+    for (size_t k = 0; k < slots; ++k)
+        if (!io.ev[k]) HIPCHK(hipEventCreateWithFlags(&io.ev[k], hipEventDisableTiming));
+    return MHD_OK;
+}
+
+// n floats at dev (device) to the host through pinned chunks (io_buffers has been called and the
+// staging is held): convert(pinned, first, count) of each, while the copies of the next ones run.
+// Threads that shared the conversion were slower (a pass of a 16-pipe batch 355 ms with the caller's
+// thread alone, 440 to 460 with 2 to 8 threads).
+template <typename Fn>
+mhd_status read_floats(mhd_sim *s, const float *dev, size_t n, Fn convert) {
+    HostIo &io = *s->io;
+    const size_t ch = io.chunk, K = io.slots, chunks = (n + ch - 1) / ch;
+    auto count = [&](size_t c) { return std::min(ch, n - c * ch); };
+    size_t issued = 0;
+    for (size_t c = 0; c < chunks; ++c) {
+        for (; issued < chunks && issued < c + K; ++issued) {
+            HIPCHK(hipMemcpyAsync(io.buf + (issued % K) * ch, dev + issued * ch, count(issued) * sizeof(float),
+                                  hipMemcpyDeviceToHost, s->stream));
+            HIPCHK(hipEventRecord(io.ev[issued % K], s->stream));
+        }
+        HIPCHK(hipEventSynchronize(io.ev[c % K]));
+        convert(io.buf + (c % K) * ch, c * ch, count(c));
+    }
+    return MHD_OK;
+}
+
+// n floats from the host to dev: convert(pinned, first, count) fills each chunk.
+template <typename Fn>
+mhd_status write_floats(mhd_sim *s, float *dev, size_t n, Fn convert) {
+    HostIo &io = *s->io;
+    const size_t ch = io.chunk, K = io.slots, chunks = (n + ch - 1) / ch;
+    for (size_t c = 0; c < chunks; ++c) {
+        const size_t count = std::min(ch, n - c * ch);
+        float *slot = io.buf + (c % K) * ch;
+        if (c >= K) HIPCHK(hipEventSynchronize(io.ev[c % K]));  // the copy of chunk c - K has ended
+        convert(slot, c * ch, count);
+        HIPCHK(hipMemcpyAsync(dev + c * ch, slot, count * sizeof(float), hipMemcpyHostToDevice, s->stream));
+        HIPCHK(hipEventRecord(io.ev[c % K], s->stream));
+    }
+    HIPCHK(hipStreamSynchronize(s->stream));
+    return MHD_OK;
+}
+
+mhd_status fill_field(mhd_sim *s, mhd_field f, const double *host) {
     const int64_t N = s->N;
     const int ncomp = f == MHD_FIELD_RHO ? 1 : 3;
     const int64_t n = ncomp * N;
@@ -390,20 +473,27 @@ mhd_status fill_field(mhd_sim *s, mhd_field f, const double *host, bool zero) {
         if (kind != MHD_STORE_F32) scale = s->g.b_scale;
         dst = s->b(s->cb);
     }
-    std::vector<float> tmp((size_t)n);
-    for (int64_t i = 0; i < n; ++i) tmp[i] = zero ? 0.f : (float)((host[i] - offset) / scale);
+    std::lock_guard<std::mutex> held(s->io->mu);
+    STEPCHK(io_buffers(*s->io, (size_t)(3 * N)));
+    auto scaled = [&](float *p, size_t first, size_t count) {
+        for (size_t i = 0; i < count; ++i) p[i] = (float)((host[first + i] - offset) / scale);
+    };
     float *stage = s->at<float>(s->L.F);  // 3N floats, free between steps
-    HIPCHK(hipMemcpyAsync(stage, tmp.data(), n * sizeof(float), hipMemcpyHostToDevice, s->stream));
-    if (f == MHD_FIELD_B_INDUCED && s->split()) {
-        HIPCHK(launch_store_split(s->stream, stage, s->bh(s->ch), dst, n));
+    if (kind == MHD_STORE_F32) {
+        STEPCHK(write_floats(s, static_cast<float *>(dst), (size_t)n, scaled));
     } else {
-        HIPCHK(launch_store_kind(s->stream, kind, stage, dst, n));
+        STEPCHK(write_floats(s, stage, (size_t)n, scaled));
+        if (f == MHD_FIELD_B_INDUCED && s->split()) {
+            HIPCHK(launch_store_split(s->stream, stage, s->bh(s->ch), dst, n));
+        } else {
+            HIPCHK(launch_store_kind(s->stream, kind, stage, dst, n));
+        }
     }
     if (f == MHD_FIELD_U && s->split()) {  // float16 copy u / u_scale read by the sweeps
-        HIPCHK(hipStreamSynchronize(s->stream));
         const double inv = 1.0 / s->g.u_scale;
-        for (int64_t i = 0; i < n; ++i) tmp[i] = zero ? 0.f : (float)(host[i] * inv);
-        HIPCHK(hipMemcpyAsync(stage, tmp.data(), n * sizeof(float), hipMemcpyHostToDevice, s->stream));
+        STEPCHK(write_floats(s, stage, (size_t)n, [&](float *p, size_t first, size_t count) {
+            for (size_t i = 0; i < count; ++i) p[i] = (float)(host[first + i] * inv);
+        }));
         HIPCHK(launch_store_kind(s->stream, MHD_STORE_F16, stage, s->u16(), n));
     }
     HIPCHK(hipStreamSynchronize(s->stream));
@@ -433,12 +523,6 @@ mhd_status timed(mhd_sim *s, int k, const char *what, Fn fn) {
     if (e) HIPCHK(hipEventRecord(e->b, s->stream));
     return MHD_OK;
 }
-
-#define STEPCHK(x)                     \
-    do {                               \
-        mhd_status st_ = (x);          \
-        if (st_ != MHD_OK) return st_; \
-    } while (0)
 
 IbArgs ib_args(mhd_sim *s, const float *sj, const float *wall);
 
@@ -1123,7 +1207,7 @@ mhd_status mhd_set_field(mhd_sim *s, mhd_field f, const double *host) {
     for (int64_t i = 0; i < n; ++i)
         if (!std::isfinite(host[i])) return fail(MHD_ERR_INVALID_ARG, "non-finite value at index %lld", (long long)i);
     HIPCHK(hipStreamSynchronize(s->stream));
-    return fill_field(s, f, host, false);
+    return fill_field(s, f, host);
 }
 
 mhd_status mhd_get_field(mhd_sim *s, mhd_field f, double *host) {
@@ -1149,19 +1233,27 @@ mhd_status mhd_get_field(mhd_sim *s, mhd_field f, double *host) {
         src = s->b(s->cb);
     }
     float *stage = s->at<float>(s->L.F);
-    HIPCHK(launch_load_kind(s->stream, kind, src, stage, n));
-    std::vector<float> tmp((size_t)n);
-    HIPCHK(hipMemcpyAsync(tmp.data(), stage, n * sizeof(float), hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(hipStreamSynchronize(s->stream));
-    for (int64_t i = 0; i < n; ++i) host[i] = (double)tmp[i] * scale + offset;
-    if (f == MHD_FIELD_B_INDUCED && s->split()) {  // b = (hi + lo) b_scale
-        HIPCHK(launch_load_kind(s->stream, MHD_STORE_F16, s->bh(s->ch), stage, n));
-        HIPCHK(hipMemcpyAsync(tmp.data(), stage, n * sizeof(float), hipMemcpyDeviceToHost, s->stream));
-        HIPCHK(hipStreamSynchronize(s->stream));
-        for (int64_t i = 0; i < n; ++i) host[i] += (double)tmp[i] * scale;
+    const float *from = static_cast<const float *>(src);  // float32 storage: straight from the field
+    if (kind != MHD_STORE_F32) {
+        HIPCHK(launch_load_kind(s->stream, kind, src, stage, n));
+        from = stage;
     }
     DevCtrl h;
-    STEPCHK(read_ctrl(s, &h));
+    std::lock_guard<std::mutex> held(s->io->mu);
+    STEPCHK(io_buffers(*s->io, (size_t)(3 * s->N)));
+    // read with the field: one wait for both
+    DevCtrl *pinned = reinterpret_cast<DevCtrl *>(s->io->buf + s->io->slots * s->io->chunk);
+    HIPCHK(hipMemcpyAsync(pinned, s->ctrl(), sizeof h, hipMemcpyDeviceToHost, s->stream));
+    STEPCHK(read_floats(s, from, (size_t)n, [&](const float *p, size_t first, size_t count) {
+        for (size_t i = 0; i < count; ++i) host[first + i] = (double)p[i] * scale + offset;
+    }));
+    h = *pinned;
+    if (f == MHD_FIELD_B_INDUCED && s->split()) {  // b = (hi + lo) b_scale
+        HIPCHK(launch_load_kind(s->stream, MHD_STORE_F16, s->bh(s->ch), stage, n));
+        STEPCHK(read_floats(s, stage, (size_t)n, [&](const float *p, size_t first, size_t count) {
+            for (size_t i = 0; i < count; ++i) host[first + i] += (double)p[i] * scale;
+        }));
+    }
     return state_status(h);
 }
 
@@ -2041,6 +2133,7 @@ mhd_status mhd_batch_create(const mhd_pipe_desc *pipes, int32_t n, void *dev_wor
             return fail(st, "pipe %d: %s", i, msg.c_str());
         }
         s->owner = b;
+        if (i > 0) s->io = b->pipes[0]->io;
         b->pipes.push_back(s);
     }
     *out = b;

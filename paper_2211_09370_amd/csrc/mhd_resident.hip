@@ -307,7 +307,7 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
                         for (int j = 0; j < 3; ++j) v[r][j] = c[r][j][k];
                 };
                 float S[1][3], B[1][3], P[1][2], cen[1][3], out[1][3];
-                plane_terms<1, Q27>(rows, W, S, B, P, cen);
+                plane_terms<1, Q27>(columns_rows<1>(rows), W, S, B, P, cen);
                 march.take(W, S, B, P, cen, out);
                 if (p >= 2)
 #pragma unroll

@@ -237,21 +237,38 @@ k_mag_sweep(SweepArgs a, const PipeStep *tab, const BlockMap *map,
         const float *s_bx = s_pl[cur][0], *s_by = s_pl[cur][1], *s_bz = s_pl[cur][2];
         const float *s_lxy = s_pl[cur][3], *s_lxz = s_pl[cur][4], *s_lyz = s_pl[cur][5];
         if constexpr (F32) {
-            if (own) {
-                float S[1][3], B[1][3], Pz[1][2], cen[1][3], out[1][3];
-                auto rows = [&](int k, float (&v)[3][3]) {
-#pragma unroll
-                    for (int r = 0; r < 3; ++r)
-#pragma unroll
-                        for (int j = 0; j < 3; ++j) v[r][j] = s_pl[cur][k][c0 + (r - 1) * HX + (j - 1)];
-                };
-                plane_terms<1, Q27>(rows, W, S, B, Pz, cen);
+            float S[1][3], B[1][3], Pz[1][2], cen[1][3], out[1][3];
+            auto take = [&](auto cols) {
+                plane_terms<1, Q27>(cols, W, S, B, Pz, cen);
                 march.take(W, S, B, Pz, cen, out);
-                if (p >= z0 + 1) {
+                if (own && p >= z0 + 1) {
                     st_off(o0, ko, out[0][0]);
                     st_off(o1, ko, out[0][1]);
                     st_off(o2, ko, out[0][2]);
                 }
+            };
+            if constexpr (TX == 64) {
+                // A wave is a row: 18 reads of the own column and 18 of the halo column instead of 54, and
+                // the columns beside it from the lanes beside it. Lanes beyond n_x hold staged (wrapped)
+                // cells, so the last cell's neighbour is there too.
+                if (gy < ny) {
+                    auto cells = [&](int k, float (&v)[3][1]) {
+#pragma unroll
+                        for (int r = 0; r < 3; ++r) v[r][0] = s_pl[cur][k][c0 + (r - 1) * HX];
+                    };
+                    auto end = [&](int k, float (&h)[3]) {
+#pragma unroll
+                        for (int r = 0; r < 3; ++r) h[r] = s_pl[cur][k][(ly + r) * HX + (lx < 32 ? 0 : HX - 1)];
+                    };
+                    take(columns_wave<1, true>(cells, end));
+                }
+            } else if (own) {
+                take(columns_rows<1>([&](int k, float (&v)[3][3]) {
+#pragma unroll
+                    for (int r = 0; r < 3; ++r)
+#pragma unroll
+                        for (int j = 0; j < 3; ++j) v[r][j] = s_pl[cur][k][c0 + (r - 1) * HX + (j - 1)];
+                }));
             }
         } else if (own) {
             // b components: centre value and in-plane sums of differences to it
@@ -413,15 +430,6 @@ struct Pair<__hip_bfloat16> {
     }
 };
 
-// Neighbouring lane's value across the whole wave (DPP wave rotation): lane l receives the value
-// of lane l - 1 (ror) or l + 1 (rol), lane 0 that of lane 63 and lane 63 that of lane 0.
-__device__ __forceinline__ float wave_ror1(float v) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x13C, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float wave_rol1(float v) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x134, 0xf, 0xf, true));
-}
-
 // The halo form (without the six-magnet table) is held to three waves per SIMD (at most 168
 // VGPRs, no spills), so that three 4-row workgroups share a CU on large boxes instead of two: the
 // 16-bit forms' steps on 512 x 256 x 256 then run 5-6% faster and the float32 64-pipe batch 5%.
@@ -437,7 +445,9 @@ k_mag_sweep_pair(SweepArgs a, const PipeStep *tab, const BlockMap *map,
     // per row, periodic in x): x0 .. x0+127 at 0 .. 127 and no halo columns; the x neighbours of a
     // lane's two cells come from the neighbouring lanes, across the wave ends for the wrap.
     constexpr int RS = 132;
-    constexpr int X0 = XWRAP ? 0 : 1;
+    // float32: x0 .. x0+127 at 0 .. 127, the halo columns at 128 and 129.
+    constexpr bool F32 = std::is_same<TB, float>::value;  // shared float32 arithmetic (mhd_sweep_math.h)
+    constexpr int X0 = XWRAP || F32 ? 0 : 1;
     __shared__ __align__(16) float s_pl[2][6][HY * RS];
 
     const int per = gridDim.x >> 3;
@@ -482,7 +492,6 @@ k_mag_sweep_pair(SweepArgs a, const PipeStep *tab, const BlockMap *map,
     const float b0f = LW::A0F * om, b0c = LW::A0C * om, b1f = LW::A1F * om, b1k = LW::A1K * om;
     const float l0f = LW::A0F * ko, l0c = LW::A0C * ko, l1c = LW::A1C * ko, l1f = LW::A1F * ko, l1k = LW::A1K * ko;
     const float w6 = (1.0f / 6.0f) * om;  // total weight of a neighbouring plane (both lattices)
-    constexpr bool F32 = std::is_same<TB, float>::value;  // shared float32 arithmetic (mhd_sweep_math.h)
     const SweepWeights W = sweep_weights<Q27>(a.kappa, a.omega);
     March<2> march;
 
@@ -505,7 +514,7 @@ k_mag_sweep_pair(SweepArgs a, const PipeStep *tab, const BlockMap *map,
     const int hx = hside ? wrapi(x0 + 128, nx) : wrapi(x0 - 1, nx);
     const int hyg = wrapi(y0 - 1 + min(hhy, HY - 1), ny);
     const unsigned hoff = (unsigned)(hx + nx * hyg);
-    const int hidx = min(hhy, HY - 1) * RS + (hside ? 129 : 0);
+    const int hidx = min(hhy, HY - 1) * RS + (hside ? 129 : F32 ? 128 : 0);
     // B_ext / b_scale of the staged columns
     const float bea[3] = {a.bext[xa] * ib, a.bext[nx + xa] * ib, a.bext[2 * nx + xa] * ib};
     const float beb[3] = {a.bext[xa + 1] * ib, a.bext[nx + xa + 1] * ib, a.bext[2 * nx + xa + 1] * ib};
@@ -772,7 +781,19 @@ k_mag_sweep_pair(SweepArgs a, const PipeStep *tab, const BlockMap *map,
             };
             float out[2][3];
             if constexpr (F32) {
-                plane_terms<2, Q27>(rows, W, S, B, Pz, cen);
+                auto cells = [&](int k, float (&v)[3][2]) {
+#pragma unroll
+                    for (int r = 0; r < 3; ++r) {
+                        const float2 c = *reinterpret_cast<const float2 *>(&s_pl[P][k][(w + r) * RS + 2 * l]);
+                        v[r][0] = c.x;
+                        v[r][1] = c.y;
+                    }
+                };
+                auto end = [&](int k, float (&h)[3]) {
+#pragma unroll
+                    for (int r = 0; r < 3; ++r) h[r] = s_pl[P][k][(w + r) * RS + 128 + (l >> 5)];
+                };
+                plane_terms<2, Q27>(columns_wave<2, !XWRAP>(cells, end), W, S, B, Pz, cen);
                 march.take(W, S, B, Pz, cen, out);
             } else {
             // b components: face and corner sums of differences to each centre, taken against

@@ -47,8 +47,7 @@ __device__ __forceinline__ void sweep_flux(float Bx, float By, float Bz, float u
 }
 
 // Contributions of one plane to the outputs at z + 1 (S + P), z (B) and z - 1 (S - P) of E cells
-// neighbouring in x (P is zero for the z component), and the cells' own b. rows(k, v) gives rows
-// y - 1, y, y + 1 of field k (b_x, b_y, b_z, flux xy, xz, yz) at columns x - 1 .. x + E.
+// neighbouring in x (P is zero for the z component), and the cells' own b.
 //
 // The b sums are differences to the centre, built from second differences along y of each
 // column and along x at the cell,
@@ -56,41 +55,44 @@ __device__ __forceinline__ void sweep_flux(float Bx, float By, float Bz, float u
 // so that neighbouring cells share their columns: every rounding stays relative to a neighbour
 // difference. The flux terms are of order b / R, so plain weighted sums keep their rounding
 // below that of b; their column sums s and differences q over rows y -+ 1 are shared as well.
-template <int E, bool Q27, typename ROWS>
-__device__ __forceinline__ void plane_terms(ROWS rows, const SweepWeights &W, float (&S)[E][3], float (&B)[E][3],
+//
+// Of the columns beside it a cell needs only their combinations and their centre row: cols.second(k,
+// c, d2y) and cols.first(k, c, q, s) give them for field k (b_x, b_y, b_z; flux xy, xz, yz) and columns
+// x - 1 .. x + E. A kernel that reads every column from LDS forms them all (ColumnsRows); one whose
+// neighbouring lanes hold the neighbouring columns forms its own E and takes the others' combinations
+// from there (ColumnsWave): the same operations on the same values, so the same bits.
+__device__ __forceinline__ float column_d2(float m, float c, float p) {
+#pragma clang fp contract(off)
+    return (p - c) - (c - m);
+}
+template <int E, bool Q27, typename COLS>
+__device__ __forceinline__ void plane_terms(COLS cols, const SweepWeights &W, float (&S)[E][3], float (&B)[E][3],
                                             float (&P)[E][2], float (&cen)[E][3]) {
 #pragma clang fp contract(off)
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        float v[3][E + 2], d2y[E + 2], g[E + 1];
-        rows(k, v);
+        float c[E + 2], d2y[E + 2], g[E + 1];
+        cols.second(k, c, d2y);
 #pragma unroll
-        for (int j = 0; j < E + 2; ++j) d2y[j] = (v[2][j] - v[1][j]) - (v[1][j] - v[0][j]);
-#pragma unroll
-        for (int j = 0; j <= E; ++j) g[j] = v[1][j + 1] - v[1][j];
+        for (int j = 0; j <= E; ++j) g[j] = c[j + 1] - c[j];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const float d2x = g[e + 1] - g[e];
             const float f = d2x + d2y[1 + e];
             const float q = fmaf(2.0f, d2x, d2y[e] + d2y[e + 2]);
-            cen[e][k] = v[1][1 + e];
+            cen[e][k] = c[1 + e];
             B[e][k] = fmaf(W.b0c, q, W.b0f * f);
             S[e][k] = W.b1f * f;
             if constexpr (Q27) S[e][k] = fmaf(W.b1k, q, S[e][k]);
         }
     }
     {  // flux xy: along y (component x) and along x (component y)
-        float v[3][E + 2], q[E + 2], s[E + 2];
-        rows(3, v);
-#pragma unroll
-        for (int j = 0; j < E + 2; ++j) {
-            q[j] = v[0][j] - v[2][j];
-            s[j] = v[0][j] + v[2][j];
-        }
+        float c[E + 2], q[E + 2], s[E + 2];
+        cols.template first<true, true>(3, c, q, s);
 #pragma unroll
         for (int e = 0; e < E; ++e) {
             const float dy = q[1 + e], cdy = q[e] + q[e + 2];
-            const float dx = v[1][e] - v[1][e + 2], cdx = s[e] - s[e + 2];
+            const float dx = c[e] - c[e + 2], cdx = s[e] - s[e + 2];
             B[e][0] = fmaf(W.l0c, cdy, fmaf(W.l0f, dy, B[e][0]));
             S[e][0] = fmaf(W.l1f, dy, S[e][0]);
             B[e][1] = fmaf(-W.l0c, cdx, fmaf(-W.l0f, dx, B[e][1]));
@@ -103,29 +105,22 @@ __device__ __forceinline__ void plane_terms(ROWS rows, const SweepWeights &W, fl
     }
     float t[E], ct[E];  // component z: flux xz along x and flux yz along y, faces and corners
     {                   // flux xz: through the planes (component x)
-        float v[3][E + 2], s[E + 2];
-        rows(4, v);
-#pragma unroll
-        for (int j = 0; j < E + 2; ++j) s[j] = v[0][j] + v[2][j];
+        float c[E + 2], q[E + 2], s[E + 2];
+        cols.template first<false, true>(4, c, q, s);
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            t[e] = v[1][e] - v[1][e + 2];
+            t[e] = c[e] - c[e + 2];
             ct[e] = s[e] - s[e + 2];
-            P[e][0] = fmaf(W.l1c, v[1][1 + e], W.l1f * ((v[1][e] + v[1][e + 2]) + s[1 + e]));
+            P[e][0] = fmaf(W.l1c, c[1 + e], W.l1f * ((c[e] + c[e + 2]) + s[1 + e]));
             if constexpr (Q27) P[e][0] = fmaf(W.l1k, s[e] + s[e + 2], P[e][0]);
         }
     }
-    {  // flux yz: through the planes (component y)
-        float v[3][E + 2], q[E + 2], s[E + 2];
-        rows(5, v);
-#pragma unroll
-        for (int j = 0; j < E + 2; ++j) {
-            q[j] = v[0][j] - v[2][j];
-            s[j] = v[0][j] + v[2][j];
-        }
+    {  // flux yz: through the planes (component y); beside the cell, s only on D3Q27
+        float c[E + 2], q[E + 2], s[E + 2];
+        cols.template first<true, Q27>(5, c, q, s);
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-            P[e][1] = fmaf(W.l1c, v[1][1 + e], W.l1f * ((v[1][e] + v[1][e + 2]) + s[1 + e]));
+            P[e][1] = fmaf(W.l1c, c[1 + e], W.l1f * ((c[e] + c[e + 2]) + s[1 + e]));
             if constexpr (Q27) P[e][1] = fmaf(W.l1k, s[e] + s[e + 2], P[e][1]);
             t[e] += q[1 + e];
             ct[e] += q[e] + q[e + 2];
@@ -137,6 +132,100 @@ __device__ __forceinline__ void plane_terms(ROWS rows, const SweepWeights &W, fl
         S[e][2] = fmaf(-W.l1f, t[e], S[e][2]);
         if constexpr (Q27) S[e][2] = fmaf(-W.l1k, ct[e], S[e][2]);
     }
+}
+
+// Columns from rows: rows(k, v) gives rows y - 1, y, y + 1 of field k at columns x - 1 .. x + E.
+template <int E, typename ROWS>
+struct ColumnsRows {
+    ROWS rows;
+    __device__ __forceinline__ void second(int k, float (&c)[E + 2], float (&d2y)[E + 2]) {
+        float v[3][E + 2];
+        rows(k, v);
+#pragma unroll
+        for (int j = 0; j < E + 2; ++j) {
+            c[j] = v[1][j];
+            d2y[j] = column_d2(v[0][j], v[1][j], v[2][j]);
+        }
+    }
+    // NQ, NS: whether q and s of the columns beside the cells are used
+    template <bool NQ, bool NS>
+    __device__ __forceinline__ void first(int k, float (&c)[E + 2], float (&q)[E + 2], float (&s)[E + 2]) {
+#pragma clang fp contract(off)
+        float v[3][E + 2];
+        rows(k, v);
+#pragma unroll
+        for (int j = 0; j < E + 2; ++j) {
+            c[j] = v[1][j];
+            q[j] = v[0][j] - v[2][j];
+            s[j] = v[0][j] + v[2][j];
+        }
+    }
+};
+template <int E, typename ROWS>
+__device__ __forceinline__ ColumnsRows<E, ROWS> columns_rows(ROWS rows) {
+    return {rows};
+}
+
+// Columns of a wave whose lanes hold consecutive groups of E columns: own(k, v) gives rows y - 1, y,
+// y + 1 at the lane's columns. Two instructions a combination replace six reads or moves of raw rows
+// and the arithmetic of two columns: 256 x 132^2 (4-row tiles, 36 aligned reads a plane -> 18 and 18 of
+// one word) 43.8 -> 36.8 us a sweep, 512 x 256^2 240.2 -> 234.9, 128^3 16.5 -> 16.3, 200 x 132^2 (one
+// cell a lane) 40.5 -> 37.1. HALO: end(k, h) gives the rows of the column beyond the wave,
+// left of lane 0 and right of lane 63 (the lanes below 32 hold the left one, the others the right);
+// without it the wave is a whole periodic row and the ends wrap.
+__device__ __forceinline__ float wave_ror1(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x13C, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float wave_rol1(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x134, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float wave_shr1(float end, float v) {  // lane 0 keeps end
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(end), __float_as_int(v), 0x138, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float wave_shl1(float end, float v) {  // lane 63 keeps end
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(end), __float_as_int(v), 0x130, 0xf, 0xf, false));
+}
+template <int E, bool HALO, typename OWN, typename END>
+struct ColumnsWave {
+    OWN own;
+    END end;
+    // the columns beside the lane's: x holds its own at 1 .. E, h is the value at the wave's end
+    static __device__ __forceinline__ void beside(float (&x)[E + 2], float h) {
+        x[0] = HALO ? wave_shr1(h, x[E]) : wave_ror1(x[E]);
+        x[E + 1] = HALO ? wave_shl1(h, x[1]) : wave_rol1(x[1]);
+    }
+    __device__ __forceinline__ void second(int k, float (&c)[E + 2], float (&d2y)[E + 2]) {
+        float v[3][E], h[3] = {0.0f, 0.0f, 0.0f};
+        own(k, v);
+        if constexpr (HALO) end(k, h);
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            c[1 + j] = v[1][j];
+            d2y[1 + j] = column_d2(v[0][j], v[1][j], v[2][j]);
+        }
+        beside(c, h[1]);
+        beside(d2y, column_d2(h[0], h[1], h[2]));
+    }
+    template <bool NQ, bool NS>
+    __device__ __forceinline__ void first(int k, float (&c)[E + 2], float (&q)[E + 2], float (&s)[E + 2]) {
+#pragma clang fp contract(off)
+        float v[3][E], h[3] = {0.0f, 0.0f, 0.0f};
+        own(k, v);
+        if constexpr (HALO) end(k, h);
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            c[1 + j] = v[1][j];
+            q[1 + j] = v[0][j] - v[2][j];
+            s[1 + j] = v[0][j] + v[2][j];
+        }
+        beside(c, h[1]);
+        if constexpr (NQ) beside(q, h[0] - h[2]);
+        if constexpr (NS) beside(s, h[0] + h[2]);
+    }
+};
+template <int E, bool HALO, typename OWN, typename END>
+__device__ __forceinline__ ColumnsWave<E, HALO, OWN, END> columns_wave(OWN own, END end) {
+    return {own, end};
 }
 
 // Rolling state of a march along z, per cell and component: acc = A(p-2) + B(p-1) (the output at

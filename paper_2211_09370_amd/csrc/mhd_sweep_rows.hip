@@ -2,18 +2,18 @@
 // neighbouring x cells, a wave a 128-cell row, a workgroup 8 rows, and it marches along z over a chunk
 // of planes (mhd_sweep.hip describes the update; the arithmetic is mhd_sweep_math.h).
 //
-// What bounds a march of this kind is the chain of each plane in a CU: the vector instructions (240 a
-// wave and plane, 200 where x neighbours come by rotation) and around them the LDS latencies and the
+// What bounds a march of this kind is the chain of each plane in a CU: the vector instructions (220 a
+// wave and plane, 165 where x neighbours come by rotation) and around them the LDS latencies and the
 // issue of the loads. The planes go straight to LDS (global_load_lds, 16 bytes a lane, two rows an
 // instruction, no registers held), a ring of four raw planes of u and b; the flux of a plane takes
 // the place of its u, which nothing else reads. So the loads are never waited for (100 to 150 cycles
-// of 3,400 to 4,200 a plane), and what is left is arranged by who has time: two waves share a SIMD, the
+// of 3,200 to 4,100 a plane), and what is left is arranged by who has time: two waves share a SIMD, the
 // older one is served first and ends its plane some 700 cycles before the other, so the requests,
 // the two extra rows and the halo columns are work of the first four waves, at the end of the plane,
 // and the raw values of the next plane are read ahead of the reduction and become flux after it.
 // Against the form that stages through registers (k_mag_sweep_pair, which the 16-bit kinds keep): 512 x
-// 256^2, 128-plane chunks 263.5 -> 240.2 us (4.58 -> 5.03 TB/s algorithmic); 128 x 256^2, 32 planes
-// 57.4 -> 55.2 us. With 4-row tiles it is the slower one (128^3, 8 planes 17.3 against 16.7 us; 256 x
+// 256^2, 128-plane chunks 263.5 -> 240.2 us, and 234.9 us (5.14 TB/s algorithmic) since the columns beside
+// a lane's come from its neighbours; 128 x 256^2, 32 planes 57.4 -> 55.2 -> 54.0 us. With 4-row tiles it is the slower one (128^3, 8 planes 17.3 against 16.7 us; 256 x
 // 132^2 46.0 against 44.0): two workgroups a CU already fill each other's gaps there, so the 4-row
 // tiles keep the register form.
 //
@@ -51,21 +51,6 @@ __device__ __forceinline__ void load_lds4(unsigned lds, const char *src) {
 template <int N>
 __device__ __forceinline__ void wait_vm() {
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
-}
-
-// Neighbouring lane's value across the whole wave (DPP): rotation (lane 0 from lane 63, lane 63 from
-// lane 0), and shift with the end lane keeping `end`.
-__device__ __forceinline__ float wave_ror1(float v) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x13C, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float wave_rol1(float v) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x134, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float wave_shr1(float end, float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(end), __float_as_int(v), 0x138, 0xf, 0xf, false));
-}
-__device__ __forceinline__ float wave_shl1(float end, float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(end), __float_as_int(v), 0x130, 0xf, 0xf, false));
 }
 
 }  // namespace
@@ -228,24 +213,20 @@ __global__ void __launch_bounds__(64 * kRows) k_sweep_rows(SweepArgs a, const Pi
         float2 raw[6];
         if (p < z1) read_raw(next, w, raw);
         if (own) {
-            auto rows = [&](int k, float (&v)[3][4]) {
+            auto cells = [&](int k, float (&v)[3][2]) {
 #pragma unroll
                 for (int r = 0; r < 3; ++r) {
                     const float2 c = *reinterpret_cast<const float2 *>(&s_pl[slot][k][w + r][2 * l]);
-                    v[r][1] = c.x;
-                    v[r][2] = c.y;
-                    if constexpr (XWRAP) {
-                        v[r][0] = wave_ror1(c.y);
-                        v[r][3] = wave_rol1(c.x);
-                    } else {  // one read: the left halo value for the lanes below 32, the right one above
-                        const float h = s_col[slot][k][w + r][l >> 5];
-                        v[r][0] = wave_shr1(h, c.y);
-                        v[r][3] = wave_shl1(h, c.x);
-                    }
+                    v[r][0] = c.x;
+                    v[r][1] = c.y;
                 }
             };
+            auto end = [&](int k, float (&h)[3]) {
+#pragma unroll
+                for (int r = 0; r < 3; ++r) h[r] = s_col[slot][k][w + r][l >> 5];
+            };
             float S[2][3], B[2][3], P[2][2], cen[2][3], out[2][3];
-            plane_terms<2, Q27>(rows, W, S, B, P, cen);
+            plane_terms<2, Q27>(columns_wave<2, !XWRAP>(cells, end), W, S, B, P, cen);
             march.take(W, S, B, P, cen, out);
             if (p >= z0 + 1) {
                 // written through the L2 (agent-scope relaxed atomic stores of the same values): the next

@@ -9,7 +9,7 @@
 namespace mhd {
 
 constexpr int kResMaxThreads = 1024;
-constexpr int kResMaxStaged = 5 * kResMaxThreads;  // staged cells (tile and halo) of a workgroup
+constexpr int kResMaxStaged = 6 * kResMaxThreads;  // staged cells (tile and halo) of a workgroup
 constexpr int kResNoRow = 1 << 20;               // first row of a work-item that takes none
 constexpr size_t kResMaxLds = 160 * 1024 - 256;  // LDS of a CU less the kernel's own words
 constexpr int kResMaxTiles = 256;                // flags reserved in the workspace
@@ -27,13 +27,14 @@ constexpr long long kResRollTicks = 2000000;     // roll call: 20 ms of the 100 
 constexpr long long kResStallTicks = 1000000000; // a wait after it: 10 s
 constexpr int kStatusStalled = 2;                // DevCtrl::status bit
 
-// header of a tile's table: counts and offsets (in words from the table's start). Places in LDS are
-// given in words, ready to use: 3 n_x times the local row or the marker's index.
+// The tables are per place in the cross-section: those of all x tiles there are the same.
+// Header: counts and offsets (in words from the table's start). Places in LDS are
+// given in words, ready to use: 3 lw times the local row or the marker's index.
 enum {
     kResNLoad, kResOLoad,  // rows read each iteration: (place, first cell n_x (y + n_y z))
     kResNMk, kResOMk,      // markers' lines: places of 9 taps, line, 9 weights, padding
     kResNCor, kResOCor,    // corrected rows: places of km4 corrections, km4 weights, place of the row, padding
-    kResNNb, kResONb,      // tiles exchanged with
+    kResNNb, kResONb,      // places in the cross-section (y tile + gy z tile) exchanged with, itself among them
     kResOExp,              // ty x tz words: 1 if another tile reads the row
     kResHeader = 12
 };
@@ -47,7 +48,8 @@ struct ResArgs {
     int64_t M;
     int km4;
     int nx, ny, nz;
-    int ty, tz, gy, nwg;   // tile of the cross-section, tiles in y, tiles
+    int tx, ty, tz, gx, gy, nwg;  // tile, tiles in x and y, tiles
+    int lw;                // local columns: n_x if gx = 1, else tx + 2
     int slots, mk_max;     // rows of b in LDS (tile, halo, extra), markers' lines of a tile at most
     int n_mag;
     float kappa, omega;
@@ -57,9 +59,12 @@ struct ResArgs {
     long long roll_ticks;
 };
 
+// Tiles are tx columns of ty x tz rows: whole rows (gx = 1, periodic in the tile) or, where the box is
+// longer than a workgroup can hold or more workgroups shorten the work, a part of them between two
+// halo columns. Tile index = x tile + gx (y tile + gy z tile).
 struct ResPlan {
     bool ok = false;
-    int ty = 0, tz = 0, gy = 0, gz = 0, nwg = 0;
+    int tx = 0, ty = 0, tz = 0, gx = 0, gy = 0, gz = 0, nwg = 0, lw = 0;
     int ns = 0, cz = 0, threads = 0;
     int slots = 0, mk_max = 0, km4 = 0;
     size_t lds_bytes = 0;

@@ -4,15 +4,19 @@
 //
 // What bounds small boxes is the chain of launches: a sweep, an interpolation and a spreading are
 // 16 us per iteration on 8 x 32 x 32 as on 32^3, whatever the cells. Here a workgroup owns the rows
-// (x lines) of a TY x TZ tile of the cross-section and keeps their b in LDS and u in registers for
+// (x lines, or TX cells of them with a halo column at each end) of a TY x TZ tile of the
+// cross-section and keeps their b in LDS and u in registers for
 // all n_mag sweeps. Per iteration it sweeps its rows, writes those that other tiles read as b*
 // (uncorrected) to the buffer of b that the iteration's parity names, raises its flag, waits for
 // the flags of the tiles it exchanges with, reads the halo rows and the rows its markers' taps
 // need, and corrects tile and halo rows from LDS. Only that exchange goes through memory: 1.9 us a
 // round for up to 4 KB a workgroup and any number of workgroups (against 3.8 us and more for a
 // barrier over the whole grid). Per iteration, launch sequence against this: 8 x 32 x 32 16.0 ->
-// 4.1 us, 32^3 15.6 -> 5.9, 5 x 83 x 83 19 -> 4.0, 100 x 75 x 75 (D3Q27) 24 -> 12. Of the 4.1 us
-// the sweep is 1.5 (one wave on a SIMD: its instructions' issue), the wait and the reads after it
+// 4.1 us, 32^3 15.6 -> 5.0, 5 x 83 x 83 19 -> 4.0, 100 x 75 x 75 (D3Q27) 24 -> 12, 160 x 39 x 39
+// 17.3 -> 9.3, 436 x 34 x 34 21.7 -> 12.9, 192 x 70 x 70 (941 k cells, all the LDS) 21.5 -> 16.5.
+// Cut along x, a box that is long and narrow fills the CUs: 32^3 in 64 workgroups of whole rows
+// took 6.0 us, in 256 5.0; boxes longer than a workgroup has work-items for had to stay with the
+// launch sequence. Of the 4.1 us the sweep is 1.5 (one wave on a SIMD: its instructions' issue), the wait and the reads after it
 // 1.4, the correction 0.8 (four LDS latencies); of the 12 us the sweep is 6.5 (issue of the vector
 // instructions) and the wait for the tiles with most wall 2 to 4.
 //
@@ -103,32 +107,42 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
 
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const int64_t N = (int64_t)nx * ny * nz;
-    const int RS = NT / nx, tr0 = t / nx < RS ? t / nx : kResNoRow, xt = t % nx;
+    // local columns: the tile's, between its two halo columns where the box is cut along x (xh = 1); a
+    // whole row wraps onto itself (xh = 0)
+    const int LW = a.lw, xh = a.gx > 1 ? 1 : 0;
+    const int RS = NT / LW, tr0 = t / LW < RS ? t / LW : kResNoRow, xt = t % LW;
     const int PY = a.ty + 2;                 // local row slot = hy + PY hz, then the extra rows
     const int GR = PY * (a.tz + 2);          // rows of tile and halo
     // LDS, three components of a cell side by side (few addresses, and lanes on consecutive words)
-    float *sb = lds;                         // [slots][nx][3] b
-    float *sl = sb + 3 * a.slots * nx;       // [GR][nx][3] flux; reused for the corrections [mk][nx][3]
-    float *syz = sl + 3 * max(GR, a.mk_max) * nx;  // [GR][3] (y, z) part of B_ext
+    float *sb = lds;                         // [slots][LW][3] b
+    float *sl = sb + 3 * a.slots * LW;       // [GR][LW][3] flux; reused for the corrections [mk][LW][3]
+    float *syz = sl + 3 * max(GR, a.mk_max) * LW;  // [GR][3] (y, z) part of B_ext
     // this tile's table, 16-byte aligned as its entries are
-    int *stab = (int *)lds + ((3 * (a.slots * nx + max(GR, a.mk_max) * nx + GR) + 3) & ~3);
+    int *stab = (int *)lds + ((3 * (a.slots * LW + max(GR, a.mk_max) * LW + GR) + 3) & ~3);
     const SweepWeights W = sweep_weights<Q27>(a.kappa, a.omega);
-    const float be0 = a.bext[xt], be1 = a.bext[nx + xt], be2 = a.bext[2 * nx + xt];
+    float be0, be1, be2;
 
-    int y0 = 0, z0 = 0, th = 0, tw = 0;
+    // the tile: first row and column, rows in y and z, columns, and this work-item's column of the box
+    int y0 = 0, z0 = 0, th = 0, tw = 0, wx = 0, cx = 0;
     float u[NS][3];
 
     // the tile's table to LDS, u of its staged cells to registers (0 where there is no cell)
     auto setup = [&](int tile) {
         const int x = opaque(xt), tr = opaque(tr0);
         __syncthreads();
-        const int *src = a.tab + a.tab_off[tile];
-        const int len = a.tab_off[tile + 1] - a.tab_off[tile];
+        const int tix = tile % a.gx, tyz = tile / a.gx;
+        const int *src = a.tab + a.tab_off[tyz];
+        const int len = a.tab_off[tyz + 1] - a.tab_off[tyz];
         for (int k = t; k < len; k += NT) stab[k] = src[k];
-        y0 = (tile % a.gy) * a.ty;
-        z0 = (tile / a.gy) * a.tz;
+        y0 = (tyz % a.gy) * a.ty;
+        z0 = (tyz / a.gy) * a.tz;
         th = min(a.ty, ny - y0);
         tw = min(a.tz, nz - z0);
+        wx = min(a.tx, nx - tix * a.tx);
+        cx = wrapi(tix * a.tx - xh + x, nx);
+        be0 = a.bext[cx];
+        be1 = a.bext[nx + cx];
+        be2 = a.bext[2 * nx + cx];
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const int slot = tr + s * RS, hz = slot / PY, hy = slot - hz * PY;
@@ -136,7 +150,7 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
             if (slot < GR && hy < th + 2 && hz < tw + 2) {
                 const int64_t row = wrapi(y0 - 1 + hy, ny) + (int64_t)ny * wrapi(z0 - 1 + hz, nz);
 #pragma unroll
-                for (int c = 0; c < 3; ++c) u[s][c] = a.u[c * N + x + nx * row];
+                for (int c = 0; c < 3; ++c) u[s][c] = a.u[c * N + cx + nx * row];
                 if (a.bext_yz && x == 0)
                     for (int c = 0; c < 3; ++c) syz[3 * slot + c] = a.bext_yz[c * (int64_t)ny * nz + row];
             }
@@ -150,7 +164,13 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
     constexpr int kBatch = 6;
     auto load_rows = [&](const float *src, bool own) {
         const int x = opaque(xt), tr = opaque(tr0);
-        const int nl = tab_hdr(kResNLoad), n = nl + (own ? th * tw : 0);
+        if (x >= wx + 2 * xh) {
+            __syncthreads();
+            return;
+        }
+        // the tile's own rows: all, or only the halo columns of them
+        const bool edge = xh && (x == 0 || x == wx + 1);
+        const int nl = tab_hdr(kResNLoad), n = nl + (own || edge ? th * tw : 0);
         const int *list = stab + tab_hdr(kResOLoad);
         for (int r0 = tr; r0 < n; r0 += kBatch * RS) {
             float v[kBatch][3];
@@ -167,10 +187,10 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
                         at = e.y;
                     } else {
                         const int lz = (r - nl) / th, ly = (r - nl) - lz * th;
-                        to[q] = 3 * nx * (ly + 1 + PY * (lz + 1));
+                        to[q] = 3 * LW * (ly + 1 + PY * (lz + 1));
                         at = nx * (y0 + ly + ny * (z0 + lz));
                     }
-                    const float *p = src + (x + at);
+                    const float *p = src + (cx + at);
                     v[q][0] = ld_agent(p);
                     v[q][1] = ld_agent(p + N);
                     v[q][2] = ld_agent(p + 2 * N);
@@ -192,7 +212,7 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
     // (s, wall values) of the work-item's first marker, requested ahead of the wait for the neighbours
     float pre[4];
     auto marker_data = [&](int line, float (&d)[4]) {
-        const int64_t j = (int64_t)line * nx + xt;
+        const int64_t j = (int64_t)line * nx + cx;
         d[0] = a.sj[j];
         d[1] = a.wall[j];
         d[2] = a.wall[a.M + j];
@@ -224,7 +244,7 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
                 I1 = fmaf(w, q[1], I1);
                 I2 = fmaf(w, q[2], I2);
             }
-            float *d = sl + 3 * (m * nx + x);
+            float *d = sl + 3 * (m * LW + x);
             d[0] = sw[0] * (sw[1] - I0);
             d[1] = sw[0] * (sw[2] - I1);
             d[2] = sw[0] * (sw[3] - I2);
@@ -260,12 +280,12 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
     // LDS and, where a row is read by another tile (or all = true), to buffer dst.
     auto sweep = [&](float *dst, bool all) {
         const int x = opaque(xt), tr = opaque(tr0);
-        const int xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
+        const int xm = x == 0 ? LW - 1 : x - 1, xp = x == LW - 1 ? 0 : x + 1;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
             const int slot = tr + s * RS;
             if (slot < GR) {
-                const int i = 3 * (slot * nx + x);
+                const int i = 3 * (slot * LW + x);
                 float e0 = be0, e1 = be1, e2 = be2;
                 if (a.bext_yz) {
                     e0 += syz[3 * slot];
@@ -277,23 +297,23 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
         }
         __syncthreads();
         const int chunk = tr / a.ty, ly = tr - chunk * a.ty, zb = chunk * CZ;
-        const bool own = ly < th && zb < tw;
+        const bool own = ly < th && zb < tw && x >= xh && x < xh + wx;
         float res[CZ][3];
         if (own) {
             March<1> march;
             // cells x - 1, x, x + 1 of row ly and plane zb; opaque, so that the addresses of every plane
             // are not kept in registers across the iterations (and, for tall
             // columns, one plane's reads at a time)
-            int cm = 3 * ((ly + PY * zb) * nx + xm), cx = 3 * ((ly + PY * zb) * nx + x), cp = 3 * ((ly + PY * zb) * nx + xp);
+            int cm = 3 * ((ly + PY * zb) * LW + xm), cc = 3 * ((ly + PY * zb) * LW + x), cp = 3 * ((ly + PY * zb) * LW + xp);
 #pragma unroll
             for (int p = 0; p < CZ + 2; ++p) {
-                if constexpr (CZ > 1) asm volatile("" : "+v"(cm), "+v"(cx), "+v"(cp) : : "memory");
+                if constexpr (CZ > 1) asm volatile("" : "+v"(cm), "+v"(cc), "+v"(cp) : : "memory");
                 float c[3][3][6];
 #pragma unroll
                 for (int r = 0; r < 3; ++r)
 #pragma unroll
                     for (int j = 0; j < 3; ++j) {
-                        const int o = (j == 0 ? cm : j == 1 ? cx : cp) + 3 * nx * r;
+                        const int o = (j == 0 ? cm : j == 1 ? cc : cp) + 3 * LW * r;
 #pragma unroll
                         for (int k = 0; k < 3; ++k) {
                             c[r][j][k] = sb[o + k];
@@ -312,9 +332,9 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
                 if (p >= 2)
 #pragma unroll
                     for (int c = 0; c < 3; ++c) res[p - 2][c] = out[0][c];
-                const int up = zb + p <= tw ? 3 * nx * PY : 0;  // past the tile's last plane: taken again, unused
+                const int up = zb + p <= tw ? 3 * LW * PY : 0;  // past the tile's last plane: taken again, unused
                 cm += up;
-                cx += up;
+                cc += up;
                 cp += up;
             }
         }
@@ -326,12 +346,12 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
             for (int p = 0; p < CZ; ++p) {
                 const int lz = zb + p;
                 if (lz >= tw) break;
-                float *o = sb + 3 * ((ly + 1 + PY * (lz + 1)) * nx + x);
+                float *o = sb + 3 * ((ly + 1 + PY * (lz + 1)) * LW + x);
                 o[0] = res[p][0];
                 o[1] = res[p][1];
                 o[2] = res[p][2];
-                if (all || exported[ly + a.ty * lz]) {
-                    float *g = dst + (x + (int64_t)nx * (y0 + ly + (int64_t)ny * (z0 + lz)));
+                if (all || exported[ly + a.ty * lz] || (xh && (x == 1 || x == wx))) {
+                    float *g = dst + (cx + (int64_t)nx * (y0 + ly + (int64_t)ny * (z0 + lz)));
                     st_agent(g, res[p][0]);
                     st_agent(g + N, res[p][1]);
                     st_agent(g + 2 * N, res[p][2]);
@@ -343,10 +363,11 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
     };
     auto store_tile = [&](float *dst) {
         const int x = opaque(xt), tr = opaque(tr0);
+        if (x < xh || x >= xh + wx) return;
         for (int r = tr; r < th * tw; r += RS) {
             const int lz = r / th, ly = r - lz * th;
-            float *p = dst + (x + (int64_t)nx * (y0 + ly + (int64_t)ny * (z0 + lz)));
-            const float *q = sb + 3 * ((ly + 1 + PY * (lz + 1)) * nx + x);
+            float *p = dst + (cx + (int64_t)nx * (y0 + ly + (int64_t)ny * (z0 + lz)));
+            const float *q = sb + 3 * ((ly + 1 + PY * (lz + 1)) * LW + x);
             st_agent(p, q[0]);
             st_agent(p + N, q[1]);
             st_agent(p + 2 * N, q[2]);
@@ -375,8 +396,11 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
     const int me = blockIdx.x;
     setup(me);
     load_rows(a.b[0], true);
-    const int nnb = tab_hdr(kResNNb);
-    const int nb = t < nnb ? stab[tab_hdr(kResONb) + t] : 0;
+    // the tiles exchanged with: those of the list, and where the box is cut along x also those before and
+    // after each in x (itself listed; a tile waits for itself at once)
+    const int wide = xh ? 3 : 1, nnb = wide * tab_hdr(kResNNb);
+    int nb = me;
+    if (t < nnb) nb = wrapi(me % a.gx + (xh ? t % 3 - 1 : 0), a.gx) + a.gx * stab[tab_hdr(kResONb) + t / wide];
     for (int i = 0; i < a.n_mag; ++i) {
         float *next = a.b[1 - (i & 1)];
         sweep(next, false);
@@ -429,9 +453,9 @@ hipError_t launch_mag_resident(hipStream_t s, const ResArgs &a, const ResPlan &p
     if (e != hipSuccess) return e;
     if (p.ns == 1) return resident_t<1, 1>(s, a, p, q27);
     if (p.ns == 2) return resident_t<2, 1>(s, a, p, q27);
-    if (p.cz == 2) return resident_t<5, 2>(s, a, p, q27);
-    if (p.cz == 4) return resident_t<5, 4>(s, a, p, q27);
-    return resident_t<5, 6>(s, a, p, q27);
+    if (p.cz == 2) return resident_t<6, 2>(s, a, p, q27);
+    if (p.cz == 4) return resident_t<6, 4>(s, a, p, q27);
+    return resident_t<6, 6>(s, a, p, q27);
 }
 
 }  // namespace mhd

@@ -12,50 +12,51 @@ namespace {
 
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
-// Launch shape for tiles of ty x tz rows: the shortest column per work-item (CZ; each column also
-// takes the two planes around it) whose columns fit the workgroup, unless taller ones cost fewer
-// vector instructions in all: a plane of a column is about 800 cycles of latency for a lone wave of
-// a SIMD and 140 vector instructions of 4 cycles (140 cycles of a CU's four SIMDs) per wave. The
-// workgroup is as large as the rows read and staged can use.
-bool launch_shape(int nx, int ty, int tz, ResPlan &p) {
+// Launch shape for tiles of ty x tz rows: the column height (CZ planes; each column also takes the two
+// planes around it) that costs least. A plane of a column measured about 660 ns of latency and 23 ns
+// for every wave of the workgroup's columns. The workgroup is as large as the rows read and staged
+// can use.
+bool launch_shape(int lw, int ty, int tz, ResPlan &p, long &cost) {
     const int gr = (ty + 2) * (tz + 2);
-    const int forms[5][2] = {{1, 1}, {2, 1}, {5, 2}, {5, 4}, {5, 6}};
+    const int forms[5][2] = {{1, 1}, {2, 1}, {6, 2}, {6, 4}, {6, 6}};
     long best = -1;
     for (const auto &f : forms) {
-        const int ns = f[0], cz = f[1], cols = nx * ty * ceil_div(tz, cz);
-        int nt = std::max({nx * ceil_div(gr, ns), cols, 64});
+        const int ns = f[0], cz = f[1], cols = lw * ty * ceil_div(tz, cz);
+        int nt = std::max({lw * ceil_div(gr, ns), cols, 64});
         nt = ceil_div(nt, 64) * 64;
         if (nt > kResMaxThreads) continue;
-        const long t = (long)(cz + 2) * std::max<long>(800, 140L * ceil_div(cols, 64));
+        const long t = (long)(cz + 2) * (660 + 23L * ceil_div(cols, 64));
         if (best < 0 || t < best) {
             best = t;
             p.ns = ns;
             p.cz = cz;
             // a round of rows read from memory costs more than the barriers of a larger workgroup
-            p.threads = std::max(nt, std::min(kResMaxThreads, ceil_div(nx * ceil_div(gr, 2), 64) * 64));
+            p.threads = std::max(nt, std::min(kResMaxThreads, ceil_div(lw * ceil_div(gr, 2), 64) * 64));
         }
     }
+    cost = best;
     return best >= 0;
 }
 
 bool build(int nx, int ny, int nz, const ResWall &w, ResPlan &p) {
-    const int ty = p.ty, tz = p.tz, PY = ty + 2, GR = PY * (tz + 2), nrows = ny * nz;
+    const int ty = p.ty, tz = p.tz, lw = p.lw, PY = ty + 2, GR = PY * (tz + 2), nrows = ny * nz;
+    const int nyz = p.gy * p.gz;
     auto owner = [&](int row) { return (row % ny) / ty + p.gy * ((row / ny) / tz); };
     std::vector<int> band((size_t)nrows, -1);
     for (size_t r = 0; r < w.band_row.size(); ++r) band[(size_t)w.band_row[r]] = (int)r;
     std::vector<char> exported((size_t)nrows, 0);
-    std::vector<std::set<int>> nb((size_t)p.nwg);
+    std::vector<std::set<int>> nb((size_t)nyz);
     struct Tile {
         std::vector<int> load, mk, cor;
         int n_mk = 0, n_cor = 0;
     };
-    std::vector<Tile> tiles((size_t)p.nwg);
+    std::vector<Tile> tiles((size_t)nyz);
     std::vector<int> slot_of((size_t)nrows), mk_of(w.tap_row.size() / (size_t)w.tm);
     p.slots = GR;
     p.mk_max = 0;
     p.km4 = (w.km + 3) & ~3;
     if (w.tm > kResTaps) return false;
-    for (int t = 0; t < p.nwg; ++t) {
+    for (int t = 0; t < nyz; ++t) {
         Tile &T = tiles[(size_t)t];
         const int y0 = (t % p.gy) * ty, z0 = (t / p.gy) * tz;
         const int th = std::min(ty, ny - y0), tw = std::min(tz, nz - z0);
@@ -91,29 +92,27 @@ bool build(int nx, int ny, int nz, const ResWall &w, ResPlan &p) {
                                 slot_of[(size_t)row] = extra;
                                 load.push_back({extra++, row});
                             }
-                            e[(size_t)i] = 3 * nx * slot_of[(size_t)row];
+                            e[(size_t)i] = 3 * lw * slot_of[(size_t)row];
                             if (i < w.tm) std::memcpy(&e[(size_t)(kResTaps + 1 + i)], &w.tap_w[(size_t)l * w.tm + i], 4);
                         }
                         e[kResTaps] = l;
                         T.mk.insert(T.mk.end(), e.begin(), e.end());
                     }
-                    line[(size_t)q] = 3 * nx * mk_of[(size_t)l];
+                    line[(size_t)q] = 3 * lw * mk_of[(size_t)l];
                     if (q < w.km) std::memcpy(&wt[(size_t)q], &w.band_w[(size_t)r * w.km + q], 4);
                 }
                 T.n_cor += 1;
                 T.cor.insert(T.cor.end(), line.begin(), line.end());
                 T.cor.insert(T.cor.end(), wt.begin(), wt.end());
-                T.cor.insert(T.cor.end(), {3 * nx * (hy + PY * hz), 0, 0, 0});
+                T.cor.insert(T.cor.end(), {3 * lw * (hy + PY * hz), 0, 0, 0});
             }
+        nb[(size_t)t].insert(t);
         for (const auto &l : load) {
-            T.load.push_back(3 * nx * l.first);
+            T.load.push_back(3 * lw * l.first);
             T.load.push_back(nx * l.second);
             exported[(size_t)l.second] = 1;
-            const int o = owner(l.second);
-            if (o != t) {  // a reader and its source wait for each other
-                nb[(size_t)t].insert(o);
-                nb[(size_t)o].insert(t);
-            }
+            nb[(size_t)t].insert(owner(l.second));  // a reader and its source wait for each other
+            nb[(size_t)owner(l.second)].insert(t);
         }
         p.slots = std::max(p.slots, extra);
         p.mk_max = std::max(p.mk_max, T.n_mk);
@@ -121,7 +120,7 @@ bool build(int nx, int ny, int nz, const ResWall &w, ResPlan &p) {
     p.tab.clear();
     p.tab_off.assign(1, 0);
     size_t longest = 0, most_nb = 0;
-    for (int t = 0; t < p.nwg; ++t) {
+    for (int t = 0; t < nyz; ++t) {
         const Tile &T = tiles[(size_t)t];
         const int y0 = (t % p.gy) * ty, z0 = (t / p.gy) * tz;
         std::vector<int> v(kResHeader, 0);
@@ -148,38 +147,50 @@ bool build(int nx, int ny, int nz, const ResWall &w, ResPlan &p) {
         longest = std::max(longest, v.size());
         most_nb = std::max(most_nb, nb[(size_t)t].size());
     }
-    p.lds_bytes = 4 * (3 * (size_t)(p.slots + std::max(GR, p.mk_max)) * nx + 3 * (size_t)GR + 3 + longest);
-    return p.lds_bytes <= kResMaxLds && p.tab.size() + p.tab_off.size() <= resident_tab_ints(ny, nz) && (int)most_nb <= p.threads;
+    p.lds_bytes = 4 * (3 * (size_t)(p.slots + std::max(GR, p.mk_max)) * lw + 3 * (size_t)GR + 3 + longest);
+    return p.lds_bytes <= kResMaxLds && p.tab.size() + p.tab_off.size() <= resident_tab_ints(ny, nz) && 3 * (int)most_nb <= p.threads;
 }
 
 }  // namespace
 
 ResPlan make_resident_plan(int nx, int ny, int nz, const ResWall &wall, int max_wg) {
     struct Cand {
-        long staged;
-        int nwg, ty, tz;
+        long cost;
+        ResPlan p;
     };
     std::vector<Cand> cand;
     max_wg = std::min(max_wg, kResMaxTiles);
-    // Tiles of at least 4 x 4 rows (or the whole cross-section): smaller ones read more rows than
-    // they own. The fewest staged cells first: the busiest workgroup sets the pace.
-    for (int ty = std::min(4, ny); ty <= std::min(ny, 24); ++ty)
-        for (int tz = std::min(4, nz); tz <= std::min(nz, 24); ++tz) {
-            const long nwg = (long)ceil_div(ny, ty) * ceil_div(nz, tz), gr = (long)(ty + 2) * (tz + 2);
-            if (nwg > max_wg || 24 * gr * nx > (long)kResMaxLds || gr * nx > kResMaxStaged) continue;
-            cand.push_back({gr * nx, (int)nwg, ty, tz});
-        }
+    // Tiles of at least 4 x 4 rows and 8 columns (or the whole box): smaller ones read more than they own.
+    // The cost is an iteration's time in ns beyond what all forms share (1.4 us): the columns' time
+    // (launch_shape), 1 ns for every staged cell and, cut along x, 700 ns (three times the neighbours)
+    // and 9 ns for every row's end cells, which are written and read by themselves. It reproduced 36
+    // measured forms of nine boxes (5 to 18.5 us an iteration, 1 to 28 tiles along x) within 4% rms.
+    for (int gx = 1; gx <= std::max(1, nx / 8); ++gx)
+        for (int ty = std::min(4, ny); ty <= std::min(ny, 24); ++ty)
+            for (int tz = std::min(4, nz); tz <= std::min(nz, 24); ++tz) {
+                Cand c;
+                ResPlan &p = c.p;
+                p.tx = ceil_div(nx, gx);
+                p.gx = ceil_div(nx, p.tx);
+                if (p.gx != gx) continue;
+                p.lw = gx == 1 ? nx : p.tx + 2;
+                p.ty = ty;
+                p.tz = tz;
+                p.gy = ceil_div(ny, ty);
+                p.gz = ceil_div(nz, tz);
+                const long nwg = (long)gx * p.gy * p.gz, staged = (long)(ty + 2) * (tz + 2) * p.lw;
+                if (nwg > max_wg || 24 * staged > (long)kResMaxLds || staged > kResMaxStaged) continue;
+                p.nwg = (int)nwg;
+                if (!launch_shape(p.lw, ty, tz, p, c.cost)) continue;
+                c.cost += staged + (gx > 1 ? 700 + 9L * (ty + 2) * (tz + 2) : 0);
+                cand.push_back(c);
+            }
     std::stable_sort(cand.begin(), cand.end(), [](const Cand &a, const Cand &b) {
-        return a.staged != b.staged ? a.staged < b.staged : a.nwg < b.nwg;
+        return a.cost != b.cost ? a.cost < b.cost : a.p.nwg < b.p.nwg;
     });
-    ResPlan p;
     for (size_t i = 0; i < cand.size() && i < 6; ++i) {
-        p.ty = cand[i].ty;
-        p.tz = cand[i].tz;
-        p.gy = ceil_div(ny, p.ty);
-        p.gz = ceil_div(nz, p.tz);
-        p.nwg = p.gy * p.gz;
-        if (!launch_shape(nx, p.ty, p.tz, p) || !build(nx, ny, nz, wall, p)) continue;
+        ResPlan &p = cand[i].p;
+        if (!build(nx, ny, nz, wall, p)) continue;
         p.ok = true;
         return p;
     }

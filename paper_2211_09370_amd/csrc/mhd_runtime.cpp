@@ -580,6 +580,9 @@ mhd_status resident_iteration(mhd_sim *s, const StepConst &c) {
     a.nx = c.nx;
     a.ny = c.ny;
     a.nz = c.nz;
+    a.tx = p.tx;
+    a.gx = p.gx;
+    a.lw = p.lw;
     a.ty = p.ty;
     a.tz = p.tz;
     a.gy = p.gy;
@@ -590,7 +593,7 @@ mhd_status resident_iteration(mhd_sim *s, const StepConst &c) {
     a.kappa = c.kappa;
     a.omega = c.omega;
     a.tab_off = s->at<int>(s->L.res_tab);
-    a.tab = a.tab_off + p.nwg + 1;
+    a.tab = a.tab_off + p.gy * p.gz + 1;
     a.sync = s->at<int>(s->L.res_sync);
     a.status = c.status;
     a.roll_ticks = s->res_mode == 2 ? -1 : kResRollTicks;

@@ -35,6 +35,15 @@ def box(case):
         return random_box(20, 26, 22, key=406, n_mag=4, R=8.0), dict(lattice=27, alpha=0.5), True
     if case == "long_rows":  # several staged rows and a tall column per work-item
         return random_box(100, 40, 44, key=407, n_mag=3, R=15.0), {}, True
+    if case == "x_tiles":  # rows cut into tiles with halo columns, the last one shorter
+        return random_box(203, 26, 30, key=410, n_mag=4, R=9.0), {}, True
+    if case == "x_tiles_magnets_q27":
+        return W.pipe_workload("six_x", 411, 150, 29, 29, 12.0, 50.0, 10.0, 1e-2, bext_kind=W.BEXT_SIX_MAGNETS, n_mag=3,
+                               b_amp=1e-3, noise=1e-2), dict(lattice=27), True
+    if case == "two_x_tiles_no_wall":  # the same tile on both sides in x
+        return random_box(21, 60, 80, key=412, n_mag=3), {}, False
+    if case == "largest":  # close to what a workgroup's LDS holds
+        return random_box(192, 70, 70, key=413, n_mag=2, R=33.0), {}, True
     if case == "pair_width":  # n_x = 128: the launch sequence is the paired sweep
         return random_box(128, 20, 22, key=408, n_mag=3, R=7.0), {}, True
     if case == "wall_through_the_faces":  # markers whose taps wrap around the box
@@ -44,7 +53,8 @@ def box(case):
 
 
 CASES = ("pipe_walls", "cube_even", "ragged_tiles", "one_sweep", "no_wall", "one_cell_wide", "six_magnets",
-         "q27_accelerated", "long_rows", "pair_width", "wall_through_the_faces")
+         "q27_accelerated", "long_rows", "pair_width", "wall_through_the_faces", "x_tiles", "x_tiles_magnets_q27",
+         "two_x_tiles_no_wall", "largest")
 
 
 def make(w, over, wall, mode, monkeypatch):

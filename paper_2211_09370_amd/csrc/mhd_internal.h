@@ -56,6 +56,7 @@ struct SweepLaunch {
     int pair;            // 1: two x cells per lane (n_x a multiple of 128); ty = rows per tile
     int byz = 0;         // 1: add the (y, z) table of B_ext (six magnets) while staging
     int q27 = 0;         // 1: D3Q27 weights
+    int mixed = 0;       // 1: float32 boxes of a batch with different forms of 256 work-items
 };
 
 // Arguments of one magnetic sweep launch over one box.
@@ -68,7 +69,7 @@ struct SweepArgs {
     const float *bext;  // 3 x nx
     const float *bext_yz;  // 3 x (ny nz) table added to bext (six magnets), else NULL
     int nx, ny, nz;
-    int tiles_x, tiles_y, nzc, zchunk, nblocks;
+    int tile_x, tiles_x, tiles_y, nzc, zchunk, nblocks;
     float kappa, u_scale, b_scale, inv_b_scale;
     float omega;        // b' = b + omega (S(b) - b); 1 for the plain sweep
     int q27;            // 1: D3Q27 lattice

@@ -1734,7 +1734,10 @@ mhd_status build_plan(mhd_batch *b) {
         if ((s->prm.lattice == 27) != (b->pipes[0]->prm.lattice == 27))
             return fail(MHD_ERR_UNSUPPORTED, "all pipes of a batch must use the same lattice");
     b->q27 = b->pipes[0]->prm.lattice == 27;
-    auto key = [](const SweepLaunch &L) { return (L.pair ? 100 + L.ty : L.tx) + 1000 * L.byz; };
+    // float32 forms of 256 work-items (all but the 8-row tiles) share one launch
+    const bool f32 = b->kinds == pack_kinds(MHD_STORE_F32, MHD_STORE_F32, MHD_STORE_F32);
+    auto form = [](const SweepLaunch &L) { return L.pair ? 100 + L.ty : L.tx; };
+    auto key = [&](const SweepLaunch &L) { return (f32 && form(L) != 108 ? 0 : form(L)) + 1000 * L.byz; };
     for (int p : b->order) {
         mhd_sim *s = b->pipes[p];
         SweepLaunch e = effective_tiles(s->sweep, s->g.nx);
@@ -1748,6 +1751,7 @@ mhd_status build_plan(mhd_batch *b) {
             g = &b->groups.back();
             g->L = e;
         }
+        if (form(g->L) != form(e)) g->L.mixed = 1;
         g->pipes.push_back(p);
         g->nmag.push_back(s->prm.n_mag);
     }

@@ -47,28 +47,33 @@ namespace mhd {
 // relative to lo, not to b. The first sweep of a step (a.bho set) re-splits v = hi + lo +
 // increment into a new hi = fp16(v) and lo = fp16(v - hi).
 // -------------------------------------------------------------------------------------------
-template <int TX, int TY, typename TU, typename TB, bool BATCH, bool SPLIT, bool BYZ, bool Q27>
-__global__ void __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(std::is_same<TB, float>::value && !BYZ ? 4 : 1)))
-k_mag_sweep(SweepArgs a, const PipeStep *tab, const BlockMap *map,
-                                                      int which, int nbatch) {
+
+// The tile of this workgroup (its index within its box; -1: none) and, in a batch, its box's arguments.
+// XCD-aware order: the hardware hands consecutive workgroups to the 8 XCDs in turn; give each XCD a
+// contiguous run of tiles so neighbouring tiles share halo rows in one L2.
+template <bool BATCH>
+__device__ __forceinline__ int sweep_tile(SweepArgs &a, const PipeStep *tab, const BlockMap *map, int which, int nbatch) {
+    const int per = gridDim.x >> 3;
+    const int lb = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if constexpr (BATCH) {
+        if (lb >= nbatch) return -1;
+        const BlockMap m = map[lb];
+        a = tab[m.pipe].sw[which];
+        return m.local;
+    }
+    return lb < a.nblocks ? lb : -1;
+}
+
+template <int TX, int TY>
+constexpr int kSweepLds = 2 * 6 * (TX + 2) * (TY + 2);  // two LDS planes (floats)
+
+template <int TX, int TY, typename TU, typename TB, bool SPLIT, bool BYZ, bool Q27>
+__device__ __forceinline__ void sweep_cells(const SweepArgs &a, const int lb, float *lds) {
     using LW = Lat<Q27>;
     constexpr int NT = TX * TY, HX = TX + 2, HY = TY + 2, HN = HX * HY;
     constexpr int NSLOT = (HN + NT - 1) / NT;
     // two LDS planes: the next plane is staged while the current one is reduced
-    __shared__ float s_pl[2][6][HN];
-
-    // XCD-aware order: the hardware hands consecutive workgroups to the 8 XCDs in turn; give
-    // each XCD a contiguous run of tiles so neighbouring tiles share halo rows in one L2.
-    const int per = gridDim.x >> 3;
-    int lb = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-    if constexpr (BATCH) {
-        if (lb >= nbatch) return;
-        const BlockMap m = map[lb];
-        a = tab[m.pipe].sw[which];
-        lb = m.local;
-    } else {
-        if (lb >= a.nblocks) return;
-    }
+    float (*s_pl)[6][HN] = reinterpret_cast<float (*)[6][HN]>(lds);
     const int tix = lb % a.tiles_x;
     const int rest = lb / a.tiles_x;
     const int tiy = rest % a.tiles_y;
@@ -385,6 +390,14 @@ k_mag_sweep(SweepArgs a, const PipeStep *tab, const BlockMap *map,
 #undef MHD_PLANE_DIFFS
 }
 
+template <int TX, int TY, typename TU, typename TB, bool BATCH, bool SPLIT, bool BYZ, bool Q27>
+__global__ void __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(std::is_same<TB, float>::value && !BYZ ? 4 : 1)))
+k_mag_sweep(SweepArgs a, const PipeStep *tab, const BlockMap *map, int which, int nbatch) {
+    __shared__ float lds[kSweepLds<TX, TY>];
+    const int lb = sweep_tile<BATCH>(a, tab, map, which, nbatch);
+    if (lb >= 0) sweep_cells<TX, TY, TU, TB, SPLIT, BYZ, Q27>(a, lb, lds);
+}
+
 // -------------------------------------------------------------------------------------------
 // Paired magnetic sweep for boxes with n_x a multiple of 128: the same plane march and the same
 // update as k_mag_sweep, but every lane owns two neighbouring x cells, so a wave covers a
@@ -430,15 +443,11 @@ struct Pair<__hip_bfloat16> {
     }
 };
 
-// The halo form (without the six-magnet table) is held to three waves per SIMD (at most 168
-// VGPRs, no spills), so that three 4-row workgroups share a CU on large boxes instead of two: the
-// 16-bit forms' steps on 512 x 256 x 256 then run 5-6% faster and the float32 64-pipe batch 5%.
-// The single-box float32 form is left unbounded (the bound made its step 0.4% slower).
-template <int TY, typename TU, typename TB, bool BATCH, bool SPLIT, bool BYZ, bool Q27, bool XWRAP>
-__global__ void __launch_bounds__(64 * TY)
-__attribute__((amdgpu_waves_per_eu(XWRAP || BYZ || (std::is_same<TB, float>::value && !BATCH) ? 1 : 3)))
-k_mag_sweep_pair(SweepArgs a, const PipeStep *tab, const BlockMap *map,
-                                                            int which, int nbatch) {
+template <int TY>
+constexpr int kPairLds = 2 * 6 * (TY + 2) * 132;
+
+template <int TY, typename TU, typename TB, bool SPLIT, bool BYZ, bool Q27, bool XWRAP>
+__device__ __forceinline__ void sweep_pairs(const SweepArgs &a, const int lb, float *lds) {
     using LW = Lat<Q27>;
     constexpr int HY = TY + 2;        // staged rows
     // LDS row stride: x0-1 at 0, x0 .. x0+127 at 1 .. 128, x0+128 at 129. XWRAP (n_x = 128, one tile
@@ -448,18 +457,7 @@ k_mag_sweep_pair(SweepArgs a, const PipeStep *tab, const BlockMap *map,
     // float32: x0 .. x0+127 at 0 .. 127, the halo columns at 128 and 129.
     constexpr bool F32 = std::is_same<TB, float>::value;  // shared float32 arithmetic (mhd_sweep_math.h)
     constexpr int X0 = XWRAP || F32 ? 0 : 1;
-    __shared__ __align__(16) float s_pl[2][6][HY * RS];
-
-    const int per = gridDim.x >> 3;
-    int lb = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-    if constexpr (BATCH) {
-        if (lb >= nbatch) return;
-        const BlockMap m = map[lb];
-        a = tab[m.pipe].sw[which];
-        lb = m.local;
-    } else {
-        if (lb >= a.nblocks) return;
-    }
+    float (*s_pl)[6][HY * RS] = reinterpret_cast<float (*)[6][HY * RS]>(lds);
     const int tix = lb % a.tiles_x;
     const int rest = lb / a.tiles_x;
     const int tiy = rest % a.tiles_y;
@@ -949,6 +947,43 @@ k_mag_sweep_pair(SweepArgs a, const PipeStep *tab, const BlockMap *map,
     }
 }
 
+// The halo form (without the six-magnet table) is held to three waves per SIMD (at most 168
+// VGPRs, no spills), so that three 4-row workgroups share a CU on large boxes instead of two: the
+// 16-bit forms' steps on 512 x 256 x 256 then run 5-6% faster and the float32 64-pipe batch 5%.
+// The single-box float32 form is left unbounded (the bound made its step 0.4% slower).
+template <int TY, typename TU, typename TB, bool BATCH, bool SPLIT, bool BYZ, bool Q27, bool XWRAP>
+__global__ void __launch_bounds__(64 * TY)
+__attribute__((amdgpu_waves_per_eu(XWRAP || BYZ || (std::is_same<TB, float>::value && !BATCH) ? 1 : 3)))
+k_mag_sweep_pair(SweepArgs a, const PipeStep *tab, const BlockMap *map, int which, int nbatch) {
+    __shared__ __align__(16) float lds[kPairLds<TY>];
+    const int lb = sweep_tile<BATCH>(a, tab, map, which, nbatch);
+    if (lb >= 0) sweep_pairs<TY, TU, TB, SPLIT, BYZ, Q27, XWRAP>(a, lb, lds);
+}
+
+// float32 boxes of a batch with different tile forms in one launch (256 work-items in each form):
+// launched form by form, every launch has its own first loads and its own last wave, and the groups
+// of few boxes leave CUs idle. The form is the box's, so a workgroup takes one branch. 16 pipes of
+// 32 to 256 planes, radii 16 to 64, three forms: a step and its read back 355 -> 346 ms (six steps).
+template <bool BYZ, bool Q27>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BYZ ? 1 : 3)))
+k_mag_sweep_mixed(const PipeStep *tab, const BlockMap *map, int which, int nbatch) {
+    __shared__ __align__(16) float lds[kPairLds<4>];
+    static_assert(kPairLds<4> >= kSweepLds<64, 4> && kPairLds<4> >= kSweepLds<32, 8> &&
+                      kPairLds<4> >= kSweepLds<16, 16> && kPairLds<4> >= kSweepLds<8, 32>,
+                  "one buffer for every form");
+    SweepArgs a;
+    const int lb = sweep_tile<true>(a, tab, map, which, nbatch);
+    if (lb < 0) return;
+    switch (a.tile_x) {
+        case 128: sweep_pairs<4, float, float, false, BYZ, Q27, false>(a, lb, lds); break;
+        case 64: sweep_cells<64, 4, float, float, false, BYZ, Q27>(a, lb, lds); break;
+        case 32: sweep_cells<32, 8, float, float, false, BYZ, Q27>(a, lb, lds); break;
+        case 16: sweep_cells<16, 16, float, float, false, BYZ, Q27>(a, lb, lds); break;
+        default: sweep_cells<8, 32, float, float, false, BYZ, Q27>(a, lb, lds); break;
+    }
+}
+
+
 // ===========================================================================================
 // Host-side launchers of the sweep
 // ===========================================================================================
@@ -968,6 +1003,7 @@ SweepArgs make_sweep_args(const void *u, const void *b, void *bo, const float *b
     const bool pair = L.pair && c.nx % 128 == 0;
     const int tx = pair ? 128 : L.tx;
     const int ty = pair ? (L.ty >= 8 ? 8 : 4) : 256 / L.tx;
+    a.tile_x = tx;
     a.tiles_x = (c.nx + tx - 1) / tx;
     a.tiles_y = (c.ny + ty - 1) / ty;
     a.zchunk = L.zchunk;
@@ -1042,8 +1078,18 @@ static hipError_t sweep_kinds_yz(hipStream_t s, int kinds, const SweepArgs &a, S
     const int ku = (kinds >> 4) & 15, kb = (kinds >> 8) & 15;
     // float32 tiles of 8 rows have a kernel of their own; those of 4 rows are faster here (both measured
     // there)
-    if (L.pair && L.ty >= 8 && ku == MHD_KIND_F32 && kb == MHD_KIND_F32)
+    if (!L.mixed && L.pair && L.ty >= 8 && ku == MHD_KIND_F32 && kb == MHD_KIND_F32)
         return launch_sweep_rows(s, BATCH, a, L, tab, map, which, nblocks, e0, e1);
+    if constexpr (BATCH) {
+        if (L.mixed) {
+            const dim3 grid(sweep_grid(nblocks));
+            if (L.q27)
+                hipExtLaunchKernelGGL(k_mag_sweep_mixed<BYZ, true>, grid, dim3(256), 0, s, e0, e1, 0, tab, map, which, nblocks);
+            else
+                hipExtLaunchKernelGGL(k_mag_sweep_mixed<BYZ, false>, grid, dim3(256), 0, s, e0, e1, 0, tab, map, which, nblocks);
+            return hipGetLastError();
+        }
+    }
     if (L.q27) {  // D3Q27: float32 and the split form
         if (ku == MHD_KIND_F32 && kb == MHD_KIND_F32)
             return sweep_typed<float, float, BATCH, false, BYZ, true>(s, a, L, tab, map, which, nblocks, e0, e1);

@@ -220,3 +220,28 @@ def test_blow_up_in_one_pipe_is_reported_for_that_pipe_only():
     B.pipes[1].get_field("u")
     assert B.pipes[1].last_status == _abi.MHD_ERR_UNSTABLE
     B.close()
+
+
+@pytest.mark.parametrize("lattice", [19, 27])
+@pytest.mark.parametrize("magnets", [False, True])
+def test_every_tile_form_of_a_batch(lattice, magnets):
+    """float32 boxes of all tile forms, ragged in x and y, in one batch (the forms of 256 work-items
+    share a launch, the 8-row tiles have their own): the same bits as each box alone."""
+    spec = []
+    for i, (nx, ny, nz) in enumerate(((7, 33, 9), (19, 17, 5), (45, 9, 11), (70, 6, 9), (128, 7, 10), (256, 9, 19))):
+        if magnets:
+            w = W.pipe_workload("forms", 420 + i, nx, 25, 25, 9.0, 50.0, 10.0, 1e-2,
+                                bext_kind=W.BEXT_SIX_MAGNETS, n_mag=5 - i % 3, b_amp=1e-3)
+        else:
+            w = random_box(nx, ny, nz, key=420 + i, n_mag=5 - i % 3)
+        w.params.lattice = lattice
+        spec.append((w, magnets))
+    B = make_batch(spec)
+    for p, t in zip(B.pipes, ((8, 4, 0, 4), (16, 8, 0, 4), (32, 3, 0, 4), (64, 8, 0, 4), (64, 8, 1, 4), (64, 16, 1, 8))):
+        p.tiles = t
+    S = make_singles(spec, [p.tiles for p in B.pipes])
+    B.step(2)
+    for s in S:
+        s.step(2)
+    for i, (p, s) in enumerate(zip(B.pipes, S)):
+        assert_same(p, s, f"tile form {i}")

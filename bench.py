@@ -50,7 +50,8 @@ sys.path.insert(0, ROOT)
 PEAK_HBM_GBS = 8000.0
 SWEEP_BYTES_PER_CELL = 36  # read u (12 B) + b (12 B), write b* (12 B), float32
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "mag_sweep_pipe512_traffic.txt")
-KERNEL_SRC = os.path.join(ROOT, "paper_2211_09370_amd", "csrc", "mhd_sweep.hip")
+KERNEL_SRC = [os.path.join(ROOT, "paper_2211_09370_amd", "csrc", f)
+              for f in ("mhd_sweep.hip", "mhd_sweep_rows.hip", "mhd_sweep_math.h")]
 
 
 def log(*a):
@@ -58,7 +59,7 @@ def log(*a):
 
 
 def kernel_hash():
-    return hashlib.sha256(open(KERNEL_SRC, "rb").read()).hexdigest()[:16]
+    return hashlib.sha256(b"".join(open(f, "rb").read() for f in KERNEL_SRC)).hexdigest()[:16]
 
 
 def read_traffic(tiles):
@@ -108,7 +109,7 @@ def traffic_summary(fetch_dir, write_dir, copy_mib):
     out = {}
     for tag, d, counter in (("fetch", fetch_dir, "FETCH_SIZE"), ("write", write_dir, "WRITE_SIZE")):
         rows = _counter_rows(d, counter)
-        sweep = [v for k, v in rows if "k_mag_sweep" in k]
+        sweep = [v for k, v in rows if "k_mag_sweep" in k or "k_sweep_rows" in k]
         copy = [v for k, v in rows if ("copy" in k.lower() or "elementwise" in k.lower())]
         if not sweep or not copy:
             raise SystemExit(f"no sweep or copy dispatches with {counter} under {d}")

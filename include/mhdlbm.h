@@ -180,7 +180,12 @@ mhd_status mhd_set_markers(mhd_sim *s, const double *xyz, int64_t M, const doubl
 /* Parameters (copied). INVALID_ARG if nu <= 0, eta <= 0, n_mag < 1, a fringe width <= 0,
  * 0 < alpha below its lattice bound, or (with markers set) 1 + d_j (lambda - 1) <= 0 for some
  * marker (the scaling of Sec. 5.5 / 5.6 would be singular or negative). UNSUPPORTED if
- * tau = 3 nu / gamma + 1/2 >= 1 with gamma != 1 (the macroscopic branch has no rescaling). */
+ * tau = 3 nu / gamma + 1/2 >= 1 with gamma != 1 (the macroscopic branch has no rescaling).
+ * float32 boxes whose fields fit the chip's LDS (up to about 0.9 M cells; with a wall, one made of
+ * lines) run the n_mag sweeps of a step and their wall corrections as one launch, with the same
+ * results; not while profiling, in calls made under the caller's own stream capture, or in a
+ * batch. The environment variable MHD_RESIDENT, read here, selects: 0 = never, 1 (default) =
+ * where it fits, 2 = always its one-workgroup form (slow; for tests). */
 mhd_status mhd_set_params(mhd_sim *s, const mhd_params *p);
 
 /* Copy a field in / out (host float64, layout above; rho has 1 component, u and b 3).

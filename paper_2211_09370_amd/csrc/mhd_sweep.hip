@@ -401,17 +401,19 @@ k_mag_sweep(SweepArgs a, const PipeStep *tab, const BlockMap *map, int which, in
 // -------------------------------------------------------------------------------------------
 // Paired magnetic sweep for boxes with n_x a multiple of 128: the same plane march and the same
 // update as k_mag_sweep, but every lane owns two neighbouring x cells, so a wave covers a
-// 128-cell row. Rows are loaded and stored as 8-byte (float32) or 4-byte (16-bit) pairs — half
-// the memory instructions per cell — and a lane reads the four values x-1 .. x+2 of a staged
-// row from LDS with two aligned 8-byte reads serving both of its cells. The arithmetic shares
-// work between the two cells (differences against one reference, shared column sums, weights
-// with kappa and the relaxation folded in), so it rounds differently from k_mag_sweep at the
-// float32 level. Single boxes with n_x = 128 (XWRAP: one tile spans the periodic row) stage no
-// halo columns: a lane reads its own two cells with one 8-byte LDS read and takes x-1 and x+2
-// from the neighbouring lanes by wave rotation, the ends wrapping as the row does. The values
-// are the same, so the results are bit for bit those of the halo form (which the batch keeps,
-// since one of its launches can mix pipes of different n_x). In float32 this form also stages
-// by 16-byte loads, four cells per lane and two rows per wave, which halves the load
+// 128-cell row. Rows are loaded and stored as 8-byte (float32) or 4-byte (16-bit) pairs: half
+// the memory instructions per cell. The 16-bit kinds read the four values x-1 .. x+2 of a staged
+// row from LDS with two aligned 8-byte reads and share work between the two cells (differences
+// against one reference, shared column sums, weights with kappa and the relaxation folded in).
+// float32 (4-row tiles; mhd_sweep_rows.hip has those of 8 rows) reads only the lane's own pair of
+// each row: of the columns beside it just d2y, the row difference sums and the centre enter, and the
+// neighbouring lanes have formed those (DPP), the wave's ends taking them from the halo columns. It
+// is bound by the plane's chain in a CU, vector instructions and LDS reads, so the fewer reads show:
+// 256 x 132^2 43.8 -> 36.8 us, 128^3 16.5 -> 16.3 us. Its arithmetic is mhd_sweep_math.h, in every
+// form the same bits. Single boxes with n_x = 128 (XWRAP: one tile spans the periodic row) stage no
+// halo columns, x neighbours come by wave rotation, the ends wrapping as the row does; the batch
+// keeps the halo form, since one of its launches can mix pipes of different n_x. In float32 XWRAP
+// also stages by 16-byte loads, four cells per lane and two rows per wave, which halves the load
 // instructions of a plane.
 // -------------------------------------------------------------------------------------------
 template <typename T>
@@ -756,7 +758,7 @@ __device__ __forceinline__ void sweep_pairs(const SweepArgs &a, const int lb, fl
             // (C = S - P) of both cells: S and B collect the in-plane sums, P the flux through
             // the planes (components x, y; zero for z, so A = C there).
             float S[2][3], B[2][3], Pz[2][2], cen[2][3];
-            // rows y-1, y, y+1 of a field at columns xa-1 .. xa+2 (two aligned 8-byte reads per row)
+            // 16-bit kinds: rows y-1, y, y+1 of a field at columns xa-1 .. xa+2 (two aligned 8-byte reads per row)
             auto rows = [&](int k, float (&v)[3][4]) {
 #pragma unroll
                 for (int r = 0; r < 3; ++r) {

@@ -13,9 +13,9 @@
 // and the raw values of the next plane are read ahead of the reduction and become flux after it.
 // Against the form that stages through registers (k_mag_sweep_pair, which the 16-bit kinds keep): 512 x
 // 256^2, 128-plane chunks 263.5 -> 240.2 us, and 234.9 us (5.14 TB/s algorithmic) since the columns beside
-// a lane's come from its neighbours; 128 x 256^2, 32 planes 57.4 -> 55.2 -> 54.0 us. With 4-row tiles it is the slower one (128^3, 8 planes 17.3 against 16.7 us; 256 x
-// 132^2 46.0 against 44.0): two workgroups a CU already fill each other's gaps there, so the 4-row
-// tiles keep the register form.
+// a lane's come from its neighbours; 128 x 256^2, 32 planes 57.4 -> 55.2 -> 54.0 us. With 4-row tiles
+// it is the slower one (128^3, 8 planes 17.3 against 16.7 us; 256 x 132^2 46.0 against 44.0): two
+// workgroups a CU already fill each other's gaps there, so the 4-row tiles keep the register form.
 //
 // Step p of the march: wait for this wave's part of plane p + 1, workgroup barrier, reduce plane p
 // (b and flux from its ring slot), write the outputs of plane p - 1, form the flux of plane p + 1,

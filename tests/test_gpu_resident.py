@@ -41,7 +41,9 @@ def box(case):
         return W.pipe_workload("six_x", 411, 150, 29, 29, 12.0, 50.0, 10.0, 1e-2, bext_kind=W.BEXT_SIX_MAGNETS, n_mag=3,
                                b_amp=1e-3, noise=1e-2), dict(lattice=27), True
     if case == "two_x_tiles_no_wall":  # the same tile on both sides in x
-        return random_box(21, 60, 80, key=412, n_mag=3), {}, False
+        return random_box(64, 53, 53, key=412, n_mag=3), {}, False
+    if case == "tall_columns":  # six planes a work-item
+        return random_box(40, 157, 157, key=414, n_mag=2), {}, False
     if case == "largest":  # close to what a workgroup's LDS holds
         return random_box(192, 70, 70, key=413, n_mag=2, R=33.0), {}, True
     if case == "pair_width":  # n_x = 128: the launch sequence is the paired sweep
@@ -54,7 +56,7 @@ def box(case):
 
 CASES = ("pipe_walls", "cube_even", "ragged_tiles", "one_sweep", "no_wall", "one_cell_wide", "six_magnets",
          "q27_accelerated", "long_rows", "pair_width", "wall_through_the_faces", "x_tiles", "x_tiles_magnets_q27",
-         "two_x_tiles_no_wall", "largest")
+         "two_x_tiles_no_wall", "tall_columns", "largest")
 
 
 def make(w, over, wall, mode, monkeypatch):

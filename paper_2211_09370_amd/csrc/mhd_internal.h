@@ -77,7 +77,8 @@ struct SweepArgs {
 // Sweep arguments of a box for tile choice L (tile counts and workgroup count filled in).
 SweepArgs make_sweep_args(const void *u, const void *b, void *bo, const float *bext, StepConst c, SweepLaunch L);
 
-hipError_t launch_ctrl_begin(hipStream_t s, DevCtrl *ctrl, StepConst c);
+// sync (optional): roll call and flags of nwg workgroups to clear for the step's resident iteration
+hipError_t launch_ctrl_begin(hipStream_t s, DevCtrl *ctrl, StepConst c, int *sync, int nwg);
 hipError_t launch_step_end(hipStream_t s, DevCtrl *ctrl, const double *flow_part, StepConst c,
                            double inv_count);
 // One sweep with arguments a (from make_sweep_args, split-form fields filled in by the caller).

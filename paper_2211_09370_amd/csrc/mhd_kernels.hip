@@ -22,6 +22,7 @@
 #include <algorithm>
 
 #include "mhd_device.h"
+#include "mhd_resident.h"
 
 namespace mhd {
 
@@ -66,8 +67,14 @@ __device__ __forceinline__ void ctrl_begin_body(DevCtrl *ctrl, const StepConst &
         G = c.G0;
     ctrl->G_step = G;
 }
-__global__ void k_ctrl_begin(DevCtrl *ctrl, StepConst c) {
+// One workgroup. sync: the roll call and the flags of the step's resident iteration are cleared here,
+// which saves a launch of a step (5 x 83 x 83, 12 sweeps: 93.0 -> 91.3 us a step).
+__global__ void __launch_bounds__(kResMaxTiles) k_ctrl_begin(DevCtrl *ctrl, StepConst c, int *sync, int nwg) {
     if (threadIdx.x == 0) ctrl_begin_body(ctrl, c);
+    if (sync) {
+        if (threadIdx.x < kResFlags) sync[threadIdx.x] = 0;
+        if ((int)threadIdx.x < nwg) sync[kResFlags + kResFlagStride * threadIdx.x] = 0;
+    }
 }
 // one workgroup per box
 __global__ void k_ctrl_begin_batch(const PipeStep *tab) {
@@ -1006,8 +1013,8 @@ __global__ void k_load(const T *src, float *dst, int64_t n) {
 // ===========================================================================================
 static inline unsigned blocks_for(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 
-hipError_t launch_ctrl_begin(hipStream_t s, DevCtrl *ctrl, StepConst c) {
-    hipLaunchKernelGGL(k_ctrl_begin, dim3(1), dim3(64), 0, s, ctrl, c);
+hipError_t launch_ctrl_begin(hipStream_t s, DevCtrl *ctrl, StepConst c, int *sync, int nwg) {
+    hipLaunchKernelGGL(k_ctrl_begin, dim3(1), dim3(sync ? kResMaxTiles : 64), 0, s, ctrl, c, sync, nwg);
     return hipGetLastError();
 }
 

@@ -428,12 +428,6 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
     }
 }
 
-// Clears the roll call and the flags before the launches of a step.
-__global__ void __launch_bounds__(256) k_resident_reset(int *sync, int nwg) {
-    if (threadIdx.x < kResFlags) sync[threadIdx.x] = 0;
-    for (int w = threadIdx.x; w < nwg; w += blockDim.x) sync[kResFlags + kResFlagStride * w] = 0;
-}
-
 template <int NS, int CZ>
 static hipError_t resident_t(hipStream_t s, ResArgs a, const ResPlan &p, bool q27) {
     const void *form[2] = {q27 ? (const void *)k_mag_resident<NS, CZ, true, false> : (const void *)k_mag_resident<NS, CZ, false, false>,
@@ -448,9 +442,6 @@ static hipError_t resident_t(hipStream_t s, ResArgs a, const ResPlan &p, bool q2
 }
 
 hipError_t launch_mag_resident(hipStream_t s, const ResArgs &a, const ResPlan &p, bool q27) {
-    hipLaunchKernelGGL(k_resident_reset, dim3(1), dim3(256), 0, s, a.sync, p.nwg);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     if (p.ns == 1) return resident_t<1, 1>(s, a, p, q27);
     if (p.ns == 2) return resident_t<2, 1>(s, a, p, q27);
     if (p.cz == 2) return resident_t<6, 2>(s, a, p, q27);

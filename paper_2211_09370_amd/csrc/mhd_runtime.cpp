@@ -606,7 +606,9 @@ mhd_status resident_iteration(mhd_sim *s, const StepConst &c) {
 mhd_status one_step(mhd_sim *s) {
     const StepConst c = step_const(s);
     hipStream_t st = s->stream;
-    STEPCHK(timed(s, MHD_K_CONTROL, "ctrl_begin", [&] { return launch_ctrl_begin(st, s->ctrl(), c); }));
+    STEPCHK(timed(s, MHD_K_CONTROL, "ctrl_begin", [&] {
+        return launch_ctrl_begin(st, s->ctrl(), c, s->res_now ? s->at<int>(s->L.res_sync) : nullptr, s->res_plan.nwg);
+    }));
     // 1. magnetic iteration, wall correction after every sweep
     if (s->res_now) {
         STEPCHK(resident_iteration(s, c));

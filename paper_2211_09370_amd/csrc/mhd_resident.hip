@@ -164,13 +164,10 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
     constexpr int kBatch = 6;
     auto load_rows = [&](const float *src, bool own) {
         const int x = opaque(xt), tr = opaque(tr0);
-        if (x >= wx + 2 * xh) {
-            __syncthreads();
-            return;
-        }
-        // the tile's own rows: all, or only the halo columns of them
+        // the tile's own rows: all, or only the halo columns of them; nothing beyond the columns of a
+        // shorter last tile, whose work-items still come to the barrier below as all do
         const bool edge = xh && (x == 0 || x == wx + 1);
-        const int nl = tab_hdr(kResNLoad), n = nl + (own || edge ? th * tw : 0);
+        const int nl = tab_hdr(kResNLoad), n = x < wx + 2 * xh ? nl + (own || edge ? th * tw : 0) : 0;
         const int *list = stab + tab_hdr(kResOLoad);
         for (int r0 = tr; r0 < n; r0 += kBatch * RS) {
             float v[kBatch][3];

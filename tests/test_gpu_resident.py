@@ -148,3 +148,29 @@ def test_new_markers_and_parameters_between_steps(monkeypatch):
         out.append([sim.get_field(f) for f in ("rho", "u", "b")])
         sim.close()
     assert all(np.array_equal(x, y) for x, y in zip(*out))
+
+
+@pytest.mark.parametrize("case", ["131x57x57", "400x42x42", "163x53x53", "497x31x31", "131x43x43 six magnets q27"])
+def test_wide_x_tiles_with_a_shorter_last_one(case, monkeypatch):
+    """Tiles of more columns than a wave, the last one shorter, so that waves with and without idle
+    columns share a workgroup (the CPU tests check that these boxes are cut so): the same fields in
+    every form."""
+    print("case resident wide", case, flush=True)
+    shape, *rest = case.split(" ")
+    nx, ny, nz = (int(v) for v in shape.split("x"))
+    R = {57: 25.0, 42: 18.0, 53: 24.0, 31: 13.0, 43: 18.0}[ny]
+    if rest:
+        w = W.pipe_workload("six_wide", 416, nx, ny, nz, R, 50.0, 10.0, 1e-2, bext_kind=W.BEXT_SIX_MAGNETS, n_mag=3, b_amp=1e-3,
+                            noise=1e-2)
+        over = dict(lattice=27)
+    else:
+        w, over = random_box(nx, ny, nz, key=415, n_mag=3, R=R), {}
+    out = {}
+    for mode in ("0", "1", "2"):
+        sim = make(w, over, True, mode, monkeypatch)
+        sim.step(2)
+        out[mode] = [sim.get_field(f) for f in ("rho", "u", "b")]
+        sim.close()
+    for mode in ("1", "2"):
+        for f, x, y in zip(("rho", "u", "b"), out["0"], out[mode]):
+            assert np.array_equal(x, y), (case, mode, f, float(np.abs(x - y).max()))

@@ -1,0 +1,81 @@
+"""The resident magnetic iteration without a GPU: the kernel source is compiled for the CPU (tests/emu),
+its workgroups run as fibers, and the fields are compared bit for bit with plain loops over the box. The
+emulation also checks that all work-items of a workgroup come to the same barrier. The plans (plain host
+code) are checked for what the kernel relies on: symmetric neighbour lists, every row and tap in LDS,
+work-items for every staged row, LDS and table space."""
+import os
+import random
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+EMU = os.path.join(HERE, "emu")
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2211_09370_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def emu(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("emu") / "resident_emu")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-ffp-contract=off", "-fno-extern-tls-init", "-pthread", "-Wno-unknown-pragmas",
+                    "-I" + EMU, os.path.join(EMU, "resident_emu.cpp"), os.path.join(CSRC, "mhd_resident_plan.cpp"), "-o", exe],
+                   check=True)
+    return exe
+
+
+def run(exe, *args):
+    r = subprocess.run([exe, *[str(a) for a in args]], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, (r.returncode, r.stderr)
+    return r.stdout.strip()
+
+
+# nx, ny, nz, radius (0: no wall), n_mag, lattice, alpha, six magnets, compute units, workgroups at once
+CASES = {
+    "whole_rows": (8, 32, 32, 14, 3, 19, 1, 0, 8, 8),
+    "ragged_tiles": (5, 29, 31, 12, 2, 19, 1, 0, 16, 16),
+    "one_sweep_no_wall": (9, 14, 30, 0, 1, 19, 1, 0, 12, 12),
+    "one_cell_wide": (1, 24, 1, 0, 3, 19, 1, 0, 8, 8),
+    "q27_accelerated_magnets": (20, 22, 20, 7, 2, 27, 0.5, 1, 16, 16),
+    "x_tiles": (60, 12, 14, 4, 3, 19, 1, 0, 16, 16),
+    # tiles wider than a wave, the last one shorter: waves with and without idle columns
+    "wide_short": (131, 14, 14, 3.5, 3, 19, 1, 0, 8, 8),
+    "wide_short_even": (262, 10, 10, 0, 2, 19, 1, 0, 8, 8),
+    "wide_short_q27_magnets": (129, 20, 20, 6.5, 2, 27, 1, 1, 16, 16),
+    "very_wide_short": (251, 8, 8, 0, 2, 19, 1, 0, 8, 8),
+}
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_kernel_equals_plain_loops_bitwise(emu, case, mode):
+    """mode 1: every workgroup resident; 2: the roll call is given up and the stand-in does the work."""
+    nx, ny, nz, R, n_mag, lattice, alpha, magnets, cus, at_once = CASES[case]
+    out = run(emu, nx, ny, nz, R, n_mag, lattice, alpha, magnets, cus, mode, at_once)
+    assert out.endswith(" ok") and out.startswith("planned 1"), out
+    if "wide_short" in case:
+        f = out.split()
+        assert int(f[f.index("lw") + 1]) > 64 and f[f.index("short") + 1] == "1", out
+
+
+# boxes of the GPU tests (tests/test_gpu_resident.py) whose last x tile is shorter than its tiles of more
+# than a wave's columns
+WIDE_SHORT = ((131, 57, 57, 25), (400, 42, 42, 18), (163, 53, 53, 24), (497, 31, 31, 13), (131, 43, 43, 18), (194, 45, 45, 20))
+
+
+def test_plans_hold_what_the_kernel_relies_on(emu, tmp_path):
+    rng = random.Random(11)
+    boxes = [(*b, 256) for b in WIDE_SHORT]
+    while len(boxes) < 400:
+        nx, ny, nz = (int(round(2 ** rng.uniform(0, e))) for e in (9.2, 7, 7))
+        R = rng.choice([0, rng.uniform(0.15, 0.49) * min(ny, nz)])
+        boxes.append((nx, ny, nz, R, rng.choice([256, 256, 64, 16])))
+    path = tmp_path / "boxes"
+    path.write_text("".join("%d %d %d %.9g %d\n" % b for b in boxes))
+    lines = run(emu, path).splitlines()
+    assert len(lines) == len(boxes)
+    assert all(l.endswith(" ok") for l in lines), [l for l in lines if not l.endswith(" ok")][:5]
+    planned = [l.split() for l in lines if " planned 1 " in l]
+    assert len(planned) > 200
+    for l in lines[:len(WIDE_SHORT)]:
+        f = l.split()
+        assert f[5] == "1" and int(f[7]) > 64 and f[9] == "1", l

@@ -184,8 +184,10 @@ mhd_status mhd_set_markers(mhd_sim *s, const double *xyz, int64_t M, const doubl
  * float32 boxes whose fields fit the chip's LDS (up to about 0.9 M cells; with a wall, one made of
  * lines) run the n_mag sweeps of a step and their wall corrections as one launch, with the same
  * results; not while profiling, in calls made under the caller's own stream capture, or in a
- * batch. The environment variable MHD_RESIDENT, read here, selects: 0 = never, 1 (default) =
- * where it fits, 2 = always its one-workgroup form (slow; for tests). */
+ * batch. This call and mhd_set_markers prepare that launch (about 1 ms of host time when the wall
+ * is new), so that step calls only launch. The environment variable MHD_RESIDENT, read here,
+ * selects: 0 = never, 1 (default) = where it fits, 2 = always its one-workgroup form (slow; for
+ * tests). */
 mhd_status mhd_set_params(mhd_sim *s, const mhd_params *p);
 
 /* Copy a field in / out (host float64, layout above; rho has 1 component, u and b 3).
@@ -216,9 +218,11 @@ mhd_status mhd_step(mhd_sim *s, int64_t n_steps, int32_t budget_every);
  * force, wall corrections, flow-rate and budget partials) in a static device array of the library
  * (32 MiB per GPU, held until the process ends) instead of the solver's workspace. Same kernels
  * and launch order as mhd_step, issued directly (no graph), so the results are the same bit for
- * bit; the caller still provides the fields (the solver's workspace) and the stream. No call
- * allocates, frees or clears memory; every scratch value is written before it is read within a
- * step. INVALID_ARG if the box needs more than the array holds (about 2.7 M cells); the other
+ * bit (under the caller's own stream capture the sweeps are launches of their own, see
+ * mhd_set_params, with the same results); the caller still provides the fields (the solver's
+ * workspace) and the stream. No call allocates or frees memory, waits, or clears more than the
+ * flags of the step's resident launch (in the workspace, by the step's first kernel); every scratch
+ * value is written before it is read within a step. INVALID_ARG if the box needs more than the array holds (about 2.7 M cells); the other
  * errors as mhd_step. All calls on one GPU share that GPU's array: calls whose work overlaps on
  * the GPU (two solvers on different streams, or another thread) race on it, so serialise them. */
 mhd_status mhd_step_noalloc(mhd_sim *s, int64_t n_steps, int32_t budget_every);

@@ -217,8 +217,8 @@ struct mhd_sim {
     std::vector<StepGraph> graphs;
     bool graph_on = true;
     // Resident magnetic iteration (mhd_resident.hip): the wall as lines along x (empty tap_row: no
-    // wall; wall_lines false: markers of another form), and the plan for it, made before the first step
-    // that uses it. MHD_RESIDENT at mhd_set_params: 0 = never, 1 (default) = where the box fits,
+    // wall; wall_lines false: markers of another form), and the plan for it (plan_resident; not ok until
+    // made). MHD_RESIDENT at mhd_set_params: 0 = never, 1 (default) = where the box fits,
     // 2 = its one-workgroup form always.
     ResWall res_wall;
     bool wall_lines = true;
@@ -748,7 +748,7 @@ struct ResidentUse {
     int device, nwg;
 };
 std::mutex g_res_mu;
-std::vector<ResidentUse> g_res_use;  // boxes whose last call had resident launches
+std::vector<ResidentUse> g_res_use;  // boxes with a plan, and the workgroups of their last resident launches
 
 class ResidentCall {
   public:
@@ -758,16 +758,13 @@ class ResidentCall {
     }
     mhd_status begin() {
         s->res_now = false;
-        if (s->res_mode == 0 || s->prof || !s->L.res_sync || !s->wall_lines) return MHD_OK;
+        if (s->res_mode == 0 || s->prof || !s->res_plan.ok) return MHD_OK;
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(s->stream, &cap) != hipSuccess) {
             (void)hipGetLastError();
             return MHD_OK;
         }
         if (cap != hipStreamCaptureStatusNone) return MHD_OK;  // a caller's graph: replayed at times unknown here
-        if (!s->res_planned) STEPCHK(plan());
-        if (!s->res_plan.ok) return MHD_OK;
-        if (!s->res_event) HIPCHK(hipEventCreateWithFlags(&s->res_event, hipEventDisableTiming));
         lock = std::unique_lock<std::mutex>(g_res_mu);
         int others = 0;
         for (const ResidentUse &x : g_res_use)
@@ -784,13 +781,15 @@ class ResidentCall {
         s->res_now = false;
         const hipError_t e = hipEventRecord(s->res_event, s->stream);
         auto at = std::find_if(g_res_use.begin(), g_res_use.end(), [&](const ResidentUse &x) { return x.sim == s; });
-        if (at == g_res_use.end())
-            g_res_use.push_back({s, s->device, s->res_plan.nwg});
-        else
-            at->nwg = s->res_plan.nwg;
+        at->nwg = s->res_plan.nwg;
         lock.unlock();
         if (e != hipSuccess) return fail(MHD_ERR_HIP, "hipEventRecord failed: %s", hipGetErrorString(e));
         return MHD_OK;
+    }
+    static void enter(mhd_sim *s) {
+        std::lock_guard<std::mutex> g(g_res_mu);
+        if (std::none_of(g_res_use.begin(), g_res_use.end(), [&](const ResidentUse &x) { return x.sim == s; }))
+            g_res_use.push_back({s, s->device, 0});
     }
     static void forget(mhd_sim *s) {
         std::lock_guard<std::mutex> g(g_res_mu);
@@ -801,25 +800,41 @@ class ResidentCall {
   private:
     mhd_sim *s;
     std::unique_lock<std::mutex> lock;
+};
 
-    mhd_status plan() {
-        HIPCHK(hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, s->device));
-        drop_step_graphs(s);
-        s->res_plan = make_resident_plan(s->g.nx, s->g.ny, s->g.nz, s->res_wall, s->cus);
-        ResPlan &p = s->res_plan;
-        if (p.ok) {
-            HIPCHK(hipMemcpyAsync(s->ws + s->L.res_tab, p.tab_off.data(), p.tab_off.size() * sizeof(int), hipMemcpyHostToDevice,
-                                  s->stream));
-            HIPCHK(hipMemcpyAsync(s->ws + s->L.res_tab + p.tab_off.size() * sizeof(int), p.tab.data(),
-                                  p.tab.size() * sizeof(int), hipMemcpyHostToDevice, s->stream));
-            HIPCHK(hipStreamSynchronize(s->stream));
-            p.tab = std::vector<int>();
-            p.tab_off = std::vector<int>();
-        }
+// Plan of the resident iteration for the box's wall, its tables in the workspace, and its event: all
+// that its steps need, so that a step call only launches. Called by mhd_set_markers and mhd_set_params
+// (which wait for the stream in any case), up to 1 ms of host time where something has changed. A box
+// of a batch has no steps of its own.
+mhd_status plan_resident(mhd_sim *s) {
+    if (s->res_planned || !s->have_params || s->res_mode == 0 || s->owner) return MHD_OK;
+    s->res_plan = ResPlan{};
+    if (!s->L.res_sync || !s->wall_lines) {
         s->res_planned = true;
         return MHD_OK;
     }
-};
+    HIPCHK(hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, s->device));
+    drop_step_graphs(s);
+    if (!s->res_event) HIPCHK(hipEventCreateWithFlags(&s->res_event, hipEventDisableTiming));
+    ResPlan p;
+    try {
+        p = make_resident_plan(s->g.nx, s->g.ny, s->g.nz, s->res_wall, s->cus);
+        if (p.ok) ResidentCall::enter(s);
+    } catch (const std::bad_alloc &) {
+        return fail(MHD_ERR_OOM, "host allocation failed");
+    }
+    if (p.ok) {
+        HIPCHK(hipMemcpyAsync(s->ws + s->L.res_tab, p.tab_off.data(), p.tab_off.size() * sizeof(int), hipMemcpyHostToDevice, s->stream));
+        HIPCHK(hipMemcpyAsync(s->ws + s->L.res_tab + p.tab_off.size() * sizeof(int), p.tab.data(), p.tab.size() * sizeof(int),
+                              hipMemcpyHostToDevice, s->stream));
+        HIPCHK(hipStreamSynchronize(s->stream));
+        p.tab = std::vector<int>();
+        p.tab_off = std::vector<int>();
+        s->res_plan = std::move(p);
+    }
+    s->res_planned = true;
+    return MHD_OK;
+}
 
 // The tile choice a launch really uses (the paired form needs nx % 128 == 0).
 SweepLaunch effective_tiles(const SweepLaunch &L, int nx) {
@@ -1126,6 +1141,7 @@ mhd_status mhd_set_markers(mhd_sim *s, const double *xyz, int64_t M, const doubl
     s->res_wall = std::move(rw);
     s->wall_lines = wall_lines && ring_mode != 0;
     s->res_planned = false;
+    s->res_plan = ResPlan{};
     s->M = M;
     s->nband = nband;
     s->tm = tm;
@@ -1140,7 +1156,7 @@ mhd_status mhd_set_markers(mhd_sim *s, const double *xyz, int64_t M, const doubl
         s->wall_lines = true;
         return st;
     }
-    return MHD_OK;
+    return plan_resident(s);
 }
 
 mhd_status mhd_set_params(mhd_sim *s, const mhd_params *p) {
@@ -1202,7 +1218,7 @@ mhd_status mhd_set_params(mhd_sim *s, const mhd_params *p) {
         HIPCHK(hipMemcpyAsync(s->ctrl(), &h, sizeof h, hipMemcpyHostToDevice, s->stream));
         HIPCHK(hipStreamSynchronize(s->stream));
     }
-    return MHD_OK;
+    return plan_resident(s);
 }
 
 mhd_status mhd_set_field(mhd_sim *s, mhd_field f, const double *host) {

@@ -1,6 +1,7 @@
-// Stand-in for the HIP headers that compiles a kernel source for the CPU (tests/emu/resident_emu.cpp): a
-// workgroup is one thread of the host whose work-items are fibers that run from barrier to barrier.
-// Only what the resident iteration and the headers it includes use is here.
+// Stand-in for the HIP headers, to compile sources of the library for the CPU. resident_emu.cpp takes a
+// kernel: a workgroup is one thread of the host whose work-items are fibers that run from barrier to
+// barrier. runtime_emu.cpp takes the host runtime: it implements the calls below on host memory. Only
+// what those sources use is here.
 #pragma once
 
 #include <math.h>
@@ -21,10 +22,45 @@ struct alignas(8) float2 { float x, y; };
 struct alignas(16) float4 { float x, y, z, w; };
 struct alignas(8) int2 { int x, y; };
 struct alignas(16) int4 { int x, y, z, w; };
-typedef void *hipStream_t;
-typedef void *hipEvent_t;
-enum hipError_t { hipSuccess = 0, hipErrorUnknown = 999 };
+typedef struct emuStream *hipStream_t;
+typedef struct emuEvent *hipEvent_t;
+typedef struct emuGraph *hipGraph_t;
+typedef struct emuGraph *hipGraphExec_t;
+typedef struct emuNode *hipGraphNode_t;
+enum hipError_t { hipSuccess = 0, hipErrorOutOfMemory = 2, hipErrorInvalidHandle = 400, hipErrorNotReady = 600, hipErrorUnknown = 999 };
 enum hipFuncAttribute { hipFuncAttributeMaxDynamicSharedMemorySize = 8 };
+enum hipMemcpyKind { hipMemcpyHostToDevice = 1, hipMemcpyDeviceToHost = 2, hipMemcpyDeviceToDevice = 3 };
+enum hipStreamCaptureMode { hipStreamCaptureModeRelaxed = 2 };
+enum hipStreamCaptureStatus { hipStreamCaptureStatusNone = 0, hipStreamCaptureStatusActive = 1 };
+enum hipDeviceAttribute_t { hipDeviceAttributeMultiprocessorCount = 63 };
+constexpr unsigned hipEventDisableTiming = 2, hipHostMallocDefault = 0, hipHostMallocMapped = 2;
+
+hipError_t hipGetLastError();
+const char *hipGetErrorString(hipError_t e);
+hipError_t hipGetDevice(int *d);
+hipError_t hipSetDevice(int d);
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t a, int d);
+hipError_t hipHostMalloc(void **p, size_t n, unsigned flags);
+hipError_t hipHostFree(void *p);
+hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned flags);
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t st);
+hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t st);
+hipError_t hipStreamSynchronize(hipStream_t s);
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned flags);
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *c);
+hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode m);
+hipError_t hipStreamEndCapture(hipStream_t s, hipGraph_t *g);
+hipError_t hipGraphInstantiate(hipGraphExec_t *e, hipGraph_t g, hipGraphNode_t *n, char *log, size_t len);
+hipError_t hipGraphDestroy(hipGraph_t g);
+hipError_t hipGraphExecDestroy(hipGraphExec_t e);
+hipError_t hipGraphLaunch(hipGraphExec_t e, hipStream_t s);
+hipError_t hipEventCreate(hipEvent_t *e);
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned flags);
+hipError_t hipEventDestroy(hipEvent_t e);
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s);
+hipError_t hipEventQuery(hipEvent_t e);
+hipError_t hipEventSynchronize(hipEvent_t e);
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t a, hipEvent_t b);
 
 namespace emu {
 struct Lane {
@@ -101,7 +137,3 @@ inline int __float_as_int(float v) {
     memcpy(&i, &v, 4);
     return i;
 }
-
-// empty asm statements that hide a value from the optimiser
-#define asm
-#define volatile(...)

@@ -24,9 +24,6 @@
 
 #include <hip/hip_runtime.h>
 
-#undef asm
-#undef volatile
-
 namespace emu {
 
 thread_local Lane lane;
@@ -110,6 +107,7 @@ namespace mhd {
 thread_local __attribute__((aligned(16))) float lds[160 * 1024 / 4];
 }
 
+// the kernel's asm statements are empty ones that hide a value from the optimiser
 #define asm
 #define volatile(...)
 #include "../../paper_2211_09370_amd/csrc/mhd_resident.hip"

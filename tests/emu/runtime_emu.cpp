@@ -1,0 +1,289 @@
+// The host runtime (mhd_runtime.cpp) on the CPU: the HIP calls work on host memory, with copies that
+// happen only when something waits for them, and the kernel launches do nothing. For what the runtime
+// promises about its calls: which of them wait, allocate or take a lock, and what is left under way
+// after an error.
+//
+//   runtime_emu SCENARIO     prints "ok" or what went wrong
+#include <stdio.h>
+#include <stdlib.h>
+
+#include <atomic>
+#include <chrono>
+#include <functional>
+#include <map>
+#include <mutex>
+#include <set>
+#include <string>
+#include <thread>
+#include <vector>
+
+#include <hip/hip_runtime.h>
+
+struct emuStream {
+    int device = 0;
+    bool capturing = false;
+    std::vector<std::function<void()>> todo;            // what a wait still has to do
+    std::vector<std::pair<const char *, size_t>> host;  // host ranges that those copies use
+};
+struct emuEvent {
+    int device = 0;
+    emuStream *on = nullptr;  // recorded on, and not waited for since
+    size_t at = 0;
+};
+struct emuGraph {};
+
+namespace emu {
+
+std::recursive_mutex mu;
+thread_local int device = 0;
+std::vector<std::string> calls;         // every call since the last clear()
+std::string fail_call;                  // this call fails after fail_after more of them
+int fail_after = 0;
+std::map<char *, size_t> pinned;
+std::string complaint;
+std::atomic<int> resident_launches{0}, sweep_launches{0};
+std::function<void(hipStream_t)> on_graph_launch;
+
+void complain(const std::string &s) {
+    if (complaint.empty()) complaint = s;
+}
+// Notes the call; true if it is to fail.
+bool note(const char *name) {
+    calls.push_back(name);
+    return fail_call == name && fail_after-- == 0;
+}
+int count(const std::set<std::string> &names) {
+    int n = 0;
+    for (const auto &c : calls) n += names.count(c) ? 1 : 0;
+    return n;
+}
+void clear() { calls.clear(); }
+void drain(emuStream *s, size_t n) {
+    for (size_t i = 0; i < n; ++i) s->todo[i]();
+    s->todo.erase(s->todo.begin(), s->todo.begin() + (long)n);
+    if (s->todo.empty()) s->host.clear();
+}
+emuStream null_stream;
+emuStream *of(hipStream_t s) { return s ? s : &null_stream; }
+
+}  // namespace emu
+using namespace emu;
+
+#define CALL(name)                                    \
+    std::lock_guard<std::recursive_mutex> lock_(mu);  \
+    if (note(name)) return hipErrorUnknown
+
+hipError_t hipGetLastError() { return hipSuccess; }
+const char *hipGetErrorString(hipError_t) { return "emulated error"; }
+hipError_t hipGetDevice(int *d) { return *d = device, hipSuccess; }
+hipError_t hipSetDevice(int d) { return device = d, hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { return *v = 256, hipSuccess; }
+hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int) { CALL("hipFuncSetAttribute"); return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
+    CALL("hipHostMalloc");
+    *p = aligned_alloc(4096, (n + 4095) / 4096 * 4096);
+    pinned[(char *)*p] = n;
+    return hipSuccess;
+}
+std::vector<emuStream *> streams{&null_stream};
+hipError_t hipHostFree(void *p) {
+    CALL("hipHostFree");
+    const size_t n = pinned[(char *)p];
+    for (emuStream *s : streams)
+        for (auto &r : s->host)
+            if (r.first < (char *)p + n && (char *)p < r.first + r.second) complain("pinned memory freed under a copy");
+    pinned.erase((char *)p);
+    free(p);
+    return hipSuccess;
+}
+hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned) { return *d = h, hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t st) {
+    CALL("hipMemcpyAsync");
+    if (k == hipMemcpyDeviceToHost && n == 64 && (uintptr_t)d % 8) complain("control block read to a misaligned address");
+    const char *host = k == hipMemcpyDeviceToHost ? (const char *)d : k == hipMemcpyHostToDevice ? (const char *)s : nullptr;
+    bool deferred = false;  // a copy from or to pageable memory waits for itself
+    for (auto &r : pinned) deferred = deferred || (host >= r.first && host < r.first + r.second);
+    if (!deferred && k != hipMemcpyDeviceToDevice) {
+        drain(of(st), of(st)->todo.size());
+        memcpy(d, s, n);
+        return hipSuccess;
+    }
+    if (host) of(st)->host.push_back({host, n});
+    of(st)->todo.push_back([=] { memcpy(d, s, n); });
+    return hipSuccess;
+}
+hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t st) {
+    CALL("hipMemsetAsync");
+    of(st)->todo.push_back([=] { memset(d, v, n); });
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t s) {
+    CALL("hipStreamSynchronize");
+    drain(of(s), of(s)->todo.size());
+    return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { CALL("hipStreamWaitEvent"); return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *c) {
+    CALL("hipStreamIsCapturing");
+    *c = of(s)->capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipStreamBeginCapture(hipStream_t s, hipStreamCaptureMode) { CALL("hipStreamBeginCapture"); s->capturing = true; return hipSuccess; }
+hipError_t hipStreamEndCapture(hipStream_t s, hipGraph_t *g) {
+    CALL("hipStreamEndCapture");
+    s->capturing = false;
+    *g = new emuGraph;
+    return hipSuccess;
+}
+hipError_t hipGraphInstantiate(hipGraphExec_t *e, hipGraph_t, hipGraphNode_t *, char *, size_t) {
+    CALL("hipGraphInstantiate");
+    *e = new emuGraph;
+    return hipSuccess;
+}
+hipError_t hipGraphDestroy(hipGraph_t g) { delete g; return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t e) { delete e; return hipSuccess; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t s) {
+    {
+        CALL("hipGraphLaunch");
+    }
+    if (on_graph_launch) on_graph_launch(s);
+    return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t *e) { CALL("hipEventCreate"); *e = new emuEvent; (*e)->device = device; return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) { CALL("hipEventDestroy"); delete e; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+    CALL("hipEventRecord");
+    if (e->device != of(s)->device) return hipErrorInvalidHandle;  // as HIP has it
+    e->on = of(s);
+    e->at = of(s)->todo.size();
+    return hipSuccess;
+}
+hipError_t hipEventQuery(hipEvent_t e) { CALL("hipEventQuery"); return e->on && !e->on->todo.empty() ? hipErrorNotReady : hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t e) {
+    CALL("hipEventSynchronize");
+    if (e->on) drain(e->on, e->on->todo.size());  // later copies as well: they may have happened
+    return hipSuccess;
+}
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { return *ms = 1.0f, hipSuccess; }
+
+#include "../../paper_2211_09370_amd/csrc/mhd_runtime.cpp"
+
+namespace mhd {  // launches: counted, nothing else
+SweepArgs make_sweep_args(const void *, const void *, void *, const float *, StepConst, SweepLaunch) { return {}; }
+hipError_t launch_ctrl_begin(hipStream_t, DevCtrl *, StepConst, int *, int) { return hipSuccess; }
+hipError_t launch_step_end(hipStream_t, DevCtrl *, const double *, StepConst, double) { return hipSuccess; }
+hipError_t launch_mag_sweep(hipStream_t, int, const SweepArgs &, SweepLaunch, hipEvent_t, hipEvent_t) { return ++sweep_launches, hipSuccess; }
+hipError_t launch_mag_resident(hipStream_t, const ResArgs &, const ResPlan &, bool) { return ++resident_launches, hipSuccess; }
+hipError_t launch_ib(hipStream_t, int, void *, float, float, const IbArgs &) { return hipSuccess; }
+hipError_t launch_lorentz(hipStream_t, int, const void *, const void *, const float *, const float *, const DevCtrl *, float *, StepConst) { return hipSuccess; }
+hipError_t launch_fluid(hipStream_t, int, const void *, const void *, const float *, void *, void *, void *, StepConst) { return hipSuccess; }
+hipError_t launch_flow_partial(hipStream_t, int, const void *, double *, StepConst) { return hipSuccess; }
+hipError_t launch_lorentz_fluid(hipStream_t, const LfArgs &) { return hipSuccess; }
+hipError_t launch_budget(hipStream_t, int, const void *, const void *, const void *, const void *, const float *, const float *, DevCtrl *, double *, mhd_budget *, StepConst) { return hipSuccess; }
+hipError_t launch_ctrl_begin_batch(hipStream_t, const PipeStep *, int) { return hipSuccess; }
+hipError_t launch_step_end_batch(hipStream_t, const PipeStep *, int) { return hipSuccess; }
+hipError_t launch_mag_sweep_batch(hipStream_t, int, SweepLaunch, const PipeStep *, const BlockMap *, int, int, hipEvent_t, hipEvent_t) { return ++sweep_launches, hipSuccess; }
+hipError_t launch_ib_interp_batch(hipStream_t, int, const PipeStep *, const BlockMap *, int, int) { return hipSuccess; }
+hipError_t launch_ib_spread_batch(hipStream_t, int, const PipeStep *, const BlockMap *, int, int) { return hipSuccess; }
+hipError_t launch_lorentz_batch(hipStream_t, int, const PipeStep *, const BlockMap *, int, bool) { return hipSuccess; }
+hipError_t launch_fluid_batch(hipStream_t, int, const PipeStep *, const BlockMap *, int, bool) { return hipSuccess; }
+hipError_t launch_flow_partial_batch(hipStream_t, int, const PipeStep *, int) { return hipSuccess; }
+hipError_t launch_store_kind(hipStream_t, int, const float *, void *, int64_t) { return hipSuccess; }
+hipError_t launch_load_kind(hipStream_t, int, const void *, float *, int64_t) { return hipSuccess; }
+hipError_t launch_store_split(hipStream_t, const float *, void *, void *, int64_t) { return hipSuccess; }
+hipError_t launch_reset_records(hipStream_t, DevCtrl *) { return hipSuccess; }
+hipError_t launch_residual_final(hipStream_t, const double *, double *) { return hipSuccess; }
+}  // namespace mhd
+
+// A box of 8 x 32 x 32 with a ring wall (it has a resident plan) on a stream of a device.
+struct Box {
+    emuStream stream;
+    std::vector<char> ws;
+    mhd_sim *sim = nullptr;
+    mhd_grid_desc g{};
+    explicit Box(int dev = 0, int nx = 8, int ny = 32, int nz = 32) {
+        stream.device = dev;
+        {
+            std::lock_guard<std::recursive_mutex> l(mu);
+            streams.push_back(&stream);
+        }
+        g.nx = nx;
+        g.ny = ny;
+        g.nz = nz;
+        const int lines = 60;
+        size_t bytes = 0;
+        check(mhd_workspace_size(&g, (int64_t)lines * nx, &bytes));
+        ws.resize(bytes + 256);
+        const int before = device;
+        device = dev;
+        check(mhd_create(&g, (int64_t)lines * nx, (void *)(((uintptr_t)ws.data() + 255) & ~(uintptr_t)255), bytes, &stream, &sim));
+        device = before;
+    }
+    static void check(mhd_status st) {
+        if (st != MHD_OK) {
+            printf("status %d: %s\n", st, mhd_last_error());
+            fflush(stdout);
+            _Exit(0);
+        }
+    }
+    void wall(double R = 9.0) {
+        const int lines = 60, M = lines * g.nx;
+        std::vector<double> x(3 * (size_t)M);
+        for (int l = 0; l < lines; ++l)
+            for (int i = 0; i < g.nx; ++i) {
+                x[(size_t)(l * g.nx + i)] = i;
+                x[(size_t)(M + l * g.nx + i)] = g.ny / 2 + R * std::cos(2 * M_PI * l / lines);
+                x[(size_t)(2 * M + l * g.nx + i)] = g.nz / 2 + R * std::sin(2 * M_PI * l / lines);
+            }
+        check(mhd_set_markers(sim, x.data(), M, nullptr, nullptr));
+    }
+    void params(int n_mag = 12) {
+        mhd_params p{};
+        p.nu = 0.05;
+        p.eta = 3.0;
+        p.n_mag = n_mag;
+        check(mhd_set_params(sim, &p));
+    }
+    ~Box() { check(mhd_destroy(sim)); }
+};
+const std::set<std::string> kWaits{"hipStreamSynchronize", "hipEventSynchronize", "hipMemcpyAsync", "hipMemsetAsync"};
+const std::set<std::string> kAllocs{"hipHostMalloc", "hipHostFree", "hipEventCreate", "hipEventDestroy"};
+
+const char *first_call(const std::set<std::string> &names) {
+    for (const auto &c : calls)
+        if (names.count(c)) return c.c_str();
+    return "";
+}
+
+// The first step after new markers or parameters only launches.
+std::string step_only_launches(bool noalloc) {
+    std::vector<char> scratch(64 << 20);
+    for (int order = 0; order < 2; ++order) {
+        Box b;
+        if (order) b.params();
+        b.wall();
+        if (!order) b.params();
+        for (int k = 0; k < 3; ++k) {
+            clear();
+            const int before = resident_launches;
+            Box::check(noalloc ? step_in_scratch(b.sim, 2, 0, scratch.data()) : mhd_step(b.sim, 2, 0));
+            if (count(kWaits)) return std::string("a step called ") + first_call(kWaits);
+            if (count(kAllocs)) return std::string("a step called ") + first_call(kAllocs);
+            if (resident_launches == before && (noalloc || k == 0)) return "the step was not a resident one";
+            if (k == 0) b.wall(8.0);
+            if (k == 1) b.params(13);
+        }
+    }
+    return "ok";
+}
+
+int main(int argc, char **argv) {
+    const std::string what = argc > 1 ? argv[1] : "";
+    std::string r = "unknown scenario";
+    if (what == "step") r = step_only_launches(false);
+    if (what == "step_noalloc") r = step_only_launches(true);
+    puts((complaint.empty() ? r : complaint).c_str());
+    fflush(stdout);
+    return 0;
+}

@@ -1,0 +1,27 @@
+"""What the host runtime promises about its calls, without a GPU: mhd_runtime.cpp compiled against an
+emulation of the HIP calls on host memory (tests/emu/runtime_emu.cpp), which records them."""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+EMU = os.path.join(HERE, "emu")
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2211_09370_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def emu(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("emu") / "runtime_emu")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-w", "-I" + EMU, os.path.join(EMU, "runtime_emu.cpp"),
+                    os.path.join(CSRC, "mhd_resident_plan.cpp"), "-o", exe], check=True)
+    return exe
+
+
+@pytest.mark.parametrize("scenario", [
+    "step",          # the first steps after new markers or parameters wait for nothing and allocate nothing
+    "step_noalloc",  # nor do the allocation-free ones
+])
+def test_scenario(emu, scenario):
+    r = subprocess.run([emu, scenario], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", (r.returncode, r.stdout, r.stderr)

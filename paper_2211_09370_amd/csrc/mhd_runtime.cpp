@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <condition_variable>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -738,17 +739,43 @@ SweepLaunch default_tiles(const mhd_grid_desc &g) {
     return L;
 }
 
-// One call that steps a box: decides whether its steps run the resident iteration, and orders such
-// calls of one process on one GPU. Workgroups of a resident launch wait for each other, so those
-// in flight at once must fit the chip together: a call whose workgroups would not fit beside the
-// unfinished ones of other boxes waits for them on the GPU (the roll call in the kernel covers what
-// this process cannot see). Held from the decision to the last launch.
+// Some steps of a box: decides whether they run the resident iteration, and orders such steps
+// of one process on one GPU. Workgroups of a resident launch wait for each other, so those
+// in flight at once must fit the chip together: steps whose workgroups would not fit beside the
+// unfinished ones of other boxes wait for them on the GPU (the roll call in the kernel covers what
+// this process cannot see). The GPU's lock is held from the decision to the last launch, of
+// kResSteps steps at most, so that a long call lets other boxes' in.
+constexpr int64_t kResSteps = 32;
 struct ResidentUse {
     mhd_sim *sim;
-    int device, nwg;
+    int nwg;  // workgroups of its last resident launches
 };
-std::mutex g_res_mu;
-std::vector<ResidentUse> g_res_use;  // boxes with a plan, and the workgroups of their last resident launches
+class TurnLock {  // first come, first served: a long call that takes it again and again waits its turn
+  public:
+    void lock() {
+        std::unique_lock<std::mutex> l(mu);
+        const uint64_t mine = taken++;
+        cv.wait(l, [&] { return mine == served; });
+    }
+    void unlock() {
+        {
+            std::lock_guard<std::mutex> l(mu);
+            ++served;
+        }
+        cv.notify_all();
+    }
+
+  private:
+    std::mutex mu;
+    std::condition_variable cv;
+    uint64_t taken = 0, served = 0;
+};
+struct ResidentGpu {
+    TurnLock mu;
+    std::vector<ResidentUse> use;  // boxes with a plan
+};
+constexpr int kMaxGpus = 64;
+ResidentGpu g_res[kMaxGpus];
 
 class ResidentCall {
   public:
@@ -756,8 +783,8 @@ class ResidentCall {
     ~ResidentCall() {
         if (s->res_now) (void)end();  // an error left the call early: what it launched is in flight
     }
-    mhd_status begin() {
-        s->res_now = false;
+    mhd_status next() {  // before the first steps, and before each further kResSteps
+        STEPCHK(end());
         if (s->res_mode == 0 || s->prof || !s->res_plan.ok) return MHD_OK;
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(s->stream, &cap) != hipSuccess) {
@@ -765,14 +792,15 @@ class ResidentCall {
             return MHD_OK;
         }
         if (cap != hipStreamCaptureStatusNone) return MHD_OK;  // a caller's graph: replayed at times unknown here
-        lock = std::unique_lock<std::mutex>(g_res_mu);
+        ResidentGpu &gpu = g_res[s->device];
+        lock = std::unique_lock<TurnLock>(gpu.mu);
         int others = 0;
-        for (const ResidentUse &x : g_res_use)
-            if (x.sim != s && x.device == s->device && hipEventQuery(x.sim->res_event) == hipErrorNotReady) others += x.nwg;
+        for (const ResidentUse &x : gpu.use)
+            if (x.sim != s && hipEventQuery(x.sim->res_event) == hipErrorNotReady) others += x.nwg;
         (void)hipGetLastError();
         if (others > 0 && others + s->res_plan.nwg > s->cus)
-            for (const ResidentUse &x : g_res_use)
-                if (x.sim != s && x.device == s->device) HIPCHK(hipStreamWaitEvent(s->stream, x.sim->res_event, 0));
+            for (const ResidentUse &x : gpu.use)
+                if (x.sim != s) HIPCHK(hipStreamWaitEvent(s->stream, x.sim->res_event, 0));
         s->res_now = true;
         return MHD_OK;
     }
@@ -780,26 +808,27 @@ class ResidentCall {
         if (!s->res_now) return MHD_OK;
         s->res_now = false;
         const hipError_t e = hipEventRecord(s->res_event, s->stream);
-        auto at = std::find_if(g_res_use.begin(), g_res_use.end(), [&](const ResidentUse &x) { return x.sim == s; });
-        at->nwg = s->res_plan.nwg;
+        for (ResidentUse &x : g_res[s->device].use)
+            if (x.sim == s) x.nwg = s->res_plan.nwg;
         lock.unlock();
         if (e != hipSuccess) return fail(MHD_ERR_HIP, "hipEventRecord failed: %s", hipGetErrorString(e));
         return MHD_OK;
     }
     static void enter(mhd_sim *s) {
-        std::lock_guard<std::mutex> g(g_res_mu);
-        if (std::none_of(g_res_use.begin(), g_res_use.end(), [&](const ResidentUse &x) { return x.sim == s; }))
-            g_res_use.push_back({s, s->device, 0});
+        ResidentGpu &gpu = g_res[s->device];
+        std::lock_guard<TurnLock> g(gpu.mu);
+        if (std::none_of(gpu.use.begin(), gpu.use.end(), [&](const ResidentUse &x) { return x.sim == s; })) gpu.use.push_back({s, 0});
     }
     static void forget(mhd_sim *s) {
-        std::lock_guard<std::mutex> g(g_res_mu);
-        g_res_use.erase(std::remove_if(g_res_use.begin(), g_res_use.end(), [&](const ResidentUse &x) { return x.sim == s; }),
-                        g_res_use.end());
+        if (s->device >= kMaxGpus) return;
+        ResidentGpu &gpu = g_res[s->device];
+        std::lock_guard<TurnLock> g(gpu.mu);
+        gpu.use.erase(std::remove_if(gpu.use.begin(), gpu.use.end(), [&](const ResidentUse &x) { return x.sim == s; }), gpu.use.end());
     }
 
   private:
     mhd_sim *s;
-    std::unique_lock<std::mutex> lock;
+    std::unique_lock<TurnLock> lock;
 };
 
 // Plan of the resident iteration for the box's wall, its tables in the workspace, and its event: all
@@ -809,7 +838,7 @@ class ResidentCall {
 mhd_status plan_resident(mhd_sim *s) {
     if (s->res_planned || !s->have_params || s->res_mode == 0 || s->owner) return MHD_OK;
     s->res_plan = ResPlan{};
-    if (!s->L.res_sync || !s->wall_lines) {
+    if (!s->L.res_sync || !s->wall_lines || s->device >= kMaxGpus) {
         s->res_planned = true;
         return MHD_OK;
     }
@@ -1308,11 +1337,11 @@ mhd_status mhd_step(mhd_sim *s, int64_t n_steps, int32_t budget_every) {
     g_err.clear();
     STEPCHK(step_checks(s, n_steps));
     ResidentCall resident(s);
-    STEPCHK(resident.begin());
     // On a caller stream the step is captured once per buffer state and replayed as a HIP graph
     // (one launch call per step instead of about 3 n_mag + 6); profiling steps launch directly.
     const bool graph = s->graph_on && s->stream != nullptr && !s->prof;
     for (int64_t i = 0; i < n_steps; ++i) {
+        if (i % kResSteps == 0) STEPCHK(resident.next());
         if (graph) {
             const int key = s->cb | (s->cr << 1) | (s->cu << 2) | (s->ch << 3) | (s->res_now ? 16 : 0);
             auto it = std::find_if(s->graphs.begin(), s->graphs.end(), [&](const mhd_sim::StepGraph &g) { return g.key == key; });
@@ -1387,9 +1416,10 @@ mhd_status step_in_scratch(mhd_sim *s, int64_t n_steps, int32_t budget_every, vo
     s->scr.flow = reinterpret_cast<double *>(base + off[2]);
     s->scr.red = reinterpret_cast<double *>(base + off[3]);
     ResidentCall resident(s);
-    mhd_status st = resident.begin();
+    mhd_status st = MHD_OK;
     for (int64_t i = 0; i < n_steps && st == MHD_OK; ++i) {  // direct launches: no graph holds these pointers
-        st = one_step(s);
+        if (i % kResSteps == 0) st = resident.next();
+        if (st == MHD_OK) st = one_step(s);
         if (st == MHD_OK && budget_every > 0 && s->t_host % budget_every == 0) st = record_budget(s);
     }
     s->scr = mhd_sim::Scratch{};

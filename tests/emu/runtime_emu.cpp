@@ -278,11 +278,59 @@ std::string step_only_launches(bool noalloc) {
     return "ok";
 }
 
+// While a box is held up in the middle of a long call (its launches block, as they do when the stream is
+// full), a box on another GPU steps all the same.
+std::string other_gpu_steps() {
+    Box a(0), b(1);
+    for (Box *x : {&a, &b}) device = x->stream.device, x->wall(), x->params();
+    std::atomic<bool> held{false}, go{false}, done{false};
+    on_graph_launch = [&](hipStream_t s) {
+        if (s != &a.stream) return;
+        held = true;
+        while (!go) std::this_thread::yield();
+    };
+    std::thread ta([&] { Box::check(mhd_step(a.sim, 4, 0)); });
+    while (!held) std::this_thread::yield();
+    std::thread tb([&] {
+        device = 1;
+        Box::check(mhd_step(b.sim, 2, 0));
+        done = true;
+    });
+    for (int i = 0; i < 2000 && !done; ++i) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+    const bool free_to_go = done;
+    go = true;
+    ta.join();
+    tb.join();
+    device = 0;
+    on_graph_launch = nullptr;
+    return free_to_go ? "ok" : "a step on another GPU waited for this call";
+}
+
+// On one GPU, a short call waits for a bounded part of a long one at most.
+std::string long_call_lets_others_in() {
+    Box a, b;
+    for (Box *x : {&a, &b}) x->wall(), x->params(), Box::check(mhd_step(x->sim, 2, 0));
+    std::atomic<int> launched{0};
+    on_graph_launch = [&](hipStream_t s) {
+        if (s == &a.stream) ++launched, std::this_thread::sleep_for(std::chrono::milliseconds(1));
+    };
+    const int steps = 2000;
+    std::thread ta([&] { Box::check(mhd_step(a.sim, steps, 0)); });
+    while (launched < 10) std::this_thread::yield();
+    Box::check(mhd_step(b.sim, 1, 0));
+    const int at = launched;
+    ta.join();
+    on_graph_launch = nullptr;
+    return at < steps / 2 ? "ok" : "a step waited for " + std::to_string(at) + " steps of another box";
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     std::string r = "unknown scenario";
     if (what == "step") r = step_only_launches(false);
     if (what == "step_noalloc") r = step_only_launches(true);
+    if (what == "other_gpu") r = other_gpu_steps();
+    if (what == "long_call") r = long_call_lets_others_in();
     puts((complaint.empty() ? r : complaint).c_str());
     fflush(stdout);
     return 0;

@@ -82,6 +82,8 @@ struct ResWall {
 // Tiles, tables and launch shape of a box for at most max_wg workgroups; ok = false if it does not fit.
 ResPlan make_resident_plan(int nx, int ny, int nz, const ResWall &wall, int max_wg);
 
+// Readies the kernels of plan p on the current GPU (once, before launches).
+hipError_t prepare_mag_resident(const ResPlan &p);
 // The launches of one step's iteration; a.sync cleared before (launch_ctrl_begin).
 hipError_t launch_mag_resident(hipStream_t s, const ResArgs &a, const ResPlan &p, bool q27);
 

@@ -425,25 +425,41 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
     }
 }
 
+// The kernels of a launch shape: [D3Q27][stand-in]
+struct ResForms {
+    const void *k[2][2];
+};
 template <int NS, int CZ>
-static hipError_t resident_t(hipStream_t s, ResArgs a, const ResPlan &p, bool q27) {
-    const void *form[2] = {q27 ? (const void *)k_mag_resident<NS, CZ, true, false> : (const void *)k_mag_resident<NS, CZ, false, false>,
-                           q27 ? (const void *)k_mag_resident<NS, CZ, true, true> : (const void *)k_mag_resident<NS, CZ, false, true>};
-    void *args[] = {&a};
-    for (int solo = 0; solo < 2; ++solo) {
-        hipError_t e = hipFuncSetAttribute(form[solo], hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds_bytes);
-        if (e == hipSuccess) e = hipLaunchKernel(form[solo], dim3(solo ? 1 : p.nwg), dim3(p.threads), args, p.lds_bytes, s);
-        if (e != hipSuccess) return e;
-    }
+static ResForms forms_t() {
+    return {{{(const void *)k_mag_resident<NS, CZ, false, false>, (const void *)k_mag_resident<NS, CZ, false, true>},
+             {(const void *)k_mag_resident<NS, CZ, true, false>, (const void *)k_mag_resident<NS, CZ, true, true>}}};
+}
+static ResForms resident_forms(const ResPlan &p) {
+    if (p.ns == 1) return forms_t<1, 1>();
+    if (p.ns == 2) return forms_t<2, 1>();
+    if (p.cz == 2) return forms_t<6, 2>();
+    if (p.cz == 4) return forms_t<6, 4>();
+    return forms_t<6, 6>();
+}
+
+hipError_t prepare_mag_resident(const ResPlan &p) {
+    const ResForms f = resident_forms(p);
+    for (const auto &lattice : f.k)
+        for (const void *k : lattice) {  // the same limit for every plan: boxes share the kernels
+            const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kResMaxLds);
+            if (e != hipSuccess) return e;
+        }
     return hipSuccess;
 }
 
 hipError_t launch_mag_resident(hipStream_t s, const ResArgs &a, const ResPlan &p, bool q27) {
-    if (p.ns == 1) return resident_t<1, 1>(s, a, p, q27);
-    if (p.ns == 2) return resident_t<2, 1>(s, a, p, q27);
-    if (p.cz == 2) return resident_t<6, 2>(s, a, p, q27);
-    if (p.cz == 4) return resident_t<6, 4>(s, a, p, q27);
-    return resident_t<6, 6>(s, a, p, q27);
+    const ResForms f = resident_forms(p);
+    void *args[] = {const_cast<ResArgs *>(&a)};
+    for (int solo = 0; solo < 2; ++solo) {
+        const hipError_t e = hipLaunchKernel(f.k[q27][solo], dim3(solo ? 1 : p.nwg), dim3(p.threads), args, p.lds_bytes, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace mhd

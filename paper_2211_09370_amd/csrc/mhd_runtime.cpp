@@ -398,10 +398,27 @@ mhd_status upload_bext(mhd_sim *s) {
     return MHD_OK;
 }
 
+// The machine's GPU as the thread's current one while this lives: events and kernel attributes belong to the
+// GPU that is current when they are made, and a caller's may be another.
+class OnDevice {
+  public:
+    explicit OnDevice(int dev) {
+        if (hipGetDevice(&before) == hipSuccess && before != dev) changed = hipSetDevice(dev) == hipSuccess;
+    }
+    ~OnDevice() {
+        if (changed) (void)hipSetDevice(before);
+    }
+
+  private:
+    int before = 0;
+    bool changed = false;
+};
+
 // Pinned chunks for copies of up to n floats, and 64 floats behind them for the control block.
-mhd_status io_buffers(HostIo &io, size_t n) {
+mhd_status io_buffers(HostIo &io, size_t n, int device) {
     const size_t chunk = std::min(n, kIoChunk), slots = n > kIoChunk ? kIoSlots : 1;
     if (io.chunk >= chunk && io.slots >= slots) return MHD_OK;
+    const OnDevice on(device);
     if (io.buf) (void)hipHostFree(io.buf);
     io.buf = nullptr;
     io.chunk = io.slots = 0;
@@ -475,7 +492,7 @@ mhd_status fill_field(mhd_sim *s, mhd_field f, const double *host) {
         dst = s->b(s->cb);
     }
     std::lock_guard<std::mutex> held(s->io->mu);
-    STEPCHK(io_buffers(*s->io, (size_t)(3 * N)));
+    STEPCHK(io_buffers(*s->io, (size_t)(3 * N), s->device));
     auto scaled = [&](float *p, size_t first, size_t count) {
         for (size_t i = 0; i < count; ++i) p[i] = (float)((host[first + i] - offset) / scale);
     };
@@ -842,6 +859,7 @@ mhd_status plan_resident(mhd_sim *s) {
         s->res_planned = true;
         return MHD_OK;
     }
+    const OnDevice on(s->device);
     HIPCHK(hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, s->device));
     drop_step_graphs(s);
     if (!s->res_event) HIPCHK(hipEventCreateWithFlags(&s->res_event, hipEventDisableTiming));
@@ -857,6 +875,7 @@ mhd_status plan_resident(mhd_sim *s) {
         HIPCHK(hipMemcpyAsync(s->ws + s->L.res_tab + p.tab_off.size() * sizeof(int), p.tab.data(), p.tab.size() * sizeof(int),
                               hipMemcpyHostToDevice, s->stream));
         HIPCHK(hipStreamSynchronize(s->stream));
+        HIPCHK(prepare_mag_resident(p));
         p.tab = std::vector<int>();
         p.tab_off = std::vector<int>();
         s->res_plan = std::move(p);
@@ -1291,7 +1310,7 @@ mhd_status mhd_get_field(mhd_sim *s, mhd_field f, double *host) {
     }
     DevCtrl h;
     std::lock_guard<std::mutex> held(s->io->mu);
-    STEPCHK(io_buffers(*s->io, (size_t)(3 * s->N)));
+    STEPCHK(io_buffers(*s->io, (size_t)(3 * s->N), s->device));
     // read with the field: one wait for both
     DevCtrl *pinned = reinterpret_cast<DevCtrl *>(s->io->buf + s->io->slots * s->io->chunk);
     HIPCHK(hipMemcpyAsync(pinned, s->ctrl(), sizeof h, hipMemcpyDeviceToHost, s->stream));

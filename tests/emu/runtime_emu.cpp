@@ -43,6 +43,7 @@ std::map<char *, size_t> pinned;
 std::string complaint;
 std::atomic<int> resident_launches{0}, sweep_launches{0};
 std::function<void(hipStream_t)> on_graph_launch;
+int prepared_on = -1;  // GPU that was current when the resident kernels were prepared
 
 void complain(const std::string &s) {
     if (complaint.empty()) complaint = s;
@@ -175,6 +176,7 @@ hipError_t launch_ctrl_begin(hipStream_t, DevCtrl *, StepConst, int *, int) { re
 hipError_t launch_step_end(hipStream_t, DevCtrl *, const double *, StepConst, double) { return hipSuccess; }
 hipError_t launch_mag_sweep(hipStream_t, int, const SweepArgs &, SweepLaunch, hipEvent_t, hipEvent_t) { return ++sweep_launches, hipSuccess; }
 hipError_t launch_mag_resident(hipStream_t, const ResArgs &, const ResPlan &, bool) { return ++resident_launches, hipSuccess; }
+hipError_t prepare_mag_resident(const ResPlan &) { return prepared_on = device, hipSuccess; }
 hipError_t launch_ib(hipStream_t, int, void *, float, float, const IbArgs &) { return hipSuccess; }
 hipError_t launch_lorentz(hipStream_t, int, const void *, const void *, const float *, const float *, const DevCtrl *, float *, StepConst) { return hipSuccess; }
 hipError_t launch_fluid(hipStream_t, int, const void *, const void *, const float *, void *, void *, void *, StepConst) { return hipSuccess; }
@@ -324,12 +326,28 @@ std::string long_call_lets_others_in() {
     return at < steps / 2 ? "ok" : "a step waited for " + std::to_string(at) + " steps of another box";
 }
 
+// Calls made while another GPU is the thread's current one: what they create belongs to the machine's GPU.
+std::string other_device_current() {
+    Box b(1);
+    device = 0;
+    const size_t n = 3 * (size_t)b.g.nx * b.g.ny * b.g.nz;
+    std::vector<double> f(n, 0.25), g(n);
+    b.wall();
+    b.params();
+    Box::check(mhd_set_field(b.sim, MHD_FIELD_U, f.data()));
+    Box::check(mhd_step(b.sim, 2, 0));
+    Box::check(mhd_get_field(b.sim, MHD_FIELD_RHO, g.data()));
+    if (prepared_on != 1) return "the kernels were prepared on another GPU";
+    return device == 0 ? "ok" : "the current GPU was changed";
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     std::string r = "unknown scenario";
     if (what == "step") r = step_only_launches(false);
     if (what == "step_noalloc") r = step_only_launches(true);
     if (what == "other_gpu") r = other_gpu_steps();
+    if (what == "device") r = other_device_current();
     if (what == "long_call") r = long_call_lets_others_in();
     puts((complaint.empty() ? r : complaint).c_str());
     fflush(stdout);

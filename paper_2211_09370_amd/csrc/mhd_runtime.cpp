@@ -169,13 +169,14 @@ constexpr int kIoSlots = 4;
 // time.
 struct HostIo {
     std::mutex mu;
+    DevCtrl *ctrl = nullptr;  // the allocation: the control block, then the chunks
     float *buf = nullptr;
     size_t chunk = 0, slots = 0;
     hipEvent_t ev[kIoSlots] = {};
     ~HostIo() {
         for (hipEvent_t e : ev)
             if (e) (void)hipEventDestroy(e);
-        if (buf) (void)hipHostFree(buf);
+        if (ctrl) (void)hipHostFree(ctrl);
     }
 };
 
@@ -414,17 +415,19 @@ class OnDevice {
     bool changed = false;
 };
 
-// Pinned chunks for copies of up to n floats, and 64 floats behind them for the control block.
+// Pinned chunks for copies of up to n floats, and the control block ahead of them.
 mhd_status io_buffers(HostIo &io, size_t n, int device) {
     const size_t chunk = std::min(n, kIoChunk), slots = n > kIoChunk ? kIoSlots : 1;
     if (io.chunk >= chunk && io.slots >= slots) return MHD_OK;
     const OnDevice on(device);
-    if (io.buf) (void)hipHostFree(io.buf);
+    if (io.ctrl) (void)hipHostFree(io.ctrl);
+    io.ctrl = nullptr;
     io.buf = nullptr;
     io.chunk = io.slots = 0;
     void *p = nullptr;
-    HIPCHK(hipHostMalloc(&p, (slots * chunk + 64) * sizeof(float), hipHostMallocDefault));
-    io.buf = static_cast<float *>(p);
+    HIPCHK(hipHostMalloc(&p, align256(sizeof(DevCtrl)) + slots * chunk * sizeof(float), hipHostMallocDefault));
+    io.ctrl = static_cast<DevCtrl *>(p);
+    io.buf = reinterpret_cast<float *>(static_cast<char *>(p) + align256(sizeof(DevCtrl)));
     io.chunk = chunk;
     io.slots = slots;
     for (size_t k = 0; k < slots; ++k)
@@ -1312,12 +1315,11 @@ mhd_status mhd_get_field(mhd_sim *s, mhd_field f, double *host) {
     std::lock_guard<std::mutex> held(s->io->mu);
     STEPCHK(io_buffers(*s->io, (size_t)(3 * s->N), s->device));
     // read with the field: one wait for both
-    DevCtrl *pinned = reinterpret_cast<DevCtrl *>(s->io->buf + s->io->slots * s->io->chunk);
-    HIPCHK(hipMemcpyAsync(pinned, s->ctrl(), sizeof h, hipMemcpyDeviceToHost, s->stream));
+    HIPCHK(hipMemcpyAsync(s->io->ctrl, s->ctrl(), sizeof h, hipMemcpyDeviceToHost, s->stream));
     STEPCHK(read_floats(s, from, (size_t)n, [&](const float *p, size_t first, size_t count) {
         for (size_t i = 0; i < count; ++i) host[first + i] = (double)p[i] * scale + offset;
     }));
-    h = *pinned;
+    h = *s->io->ctrl;
     if (f == MHD_FIELD_B_INDUCED && s->split()) {  // b = (hi + lo) b_scale
         HIPCHK(launch_load_kind(s->stream, MHD_STORE_F16, s->bh(s->ch), stage, n));
         STEPCHK(read_floats(s, stage, (size_t)n, [&](const float *p, size_t first, size_t count) {

@@ -428,12 +428,28 @@ mhd_status io_buffers(HostIo &io, size_t n, int device) {
     HIPCHK(hipHostMalloc(&p, align256(sizeof(DevCtrl)) + slots * chunk * sizeof(float), hipHostMallocDefault));
     io.ctrl = static_cast<DevCtrl *>(p);
     io.buf = reinterpret_cast<float *>(static_cast<char *>(p) + align256(sizeof(DevCtrl)));
-    io.chunk = chunk;
-    io.slots = slots;
     for (size_t k = 0; k < slots; ++k)
         if (!io.ev[k]) HIPCHK(hipEventCreateWithFlags(&io.ev[k], hipEventDisableTiming));
+    io.chunk = chunk;
+    io.slots = slots;
     return MHD_OK;
 }
+
+// The staging of a field copy, held; an error that ends the copy early waits for what it has started, so
+// that the chunks are free for the next one.
+class IoUse {
+  public:
+    explicit IoUse(mhd_sim *sim) : s(sim), held(sim->io->mu) {}
+    ~IoUse() {
+        if (!complete) (void)hipStreamSynchronize(s->stream);
+    }
+    void done() { complete = true; }
+
+  private:
+    mhd_sim *s;
+    std::lock_guard<std::mutex> held;
+    bool complete = false;
+};
 
 // n floats at dev (device) to the host through pinned chunks (io_buffers has been called and the
 // staging is held): convert(pinned, first, count) of each, while the copies of the next ones run.
@@ -494,7 +510,7 @@ mhd_status fill_field(mhd_sim *s, mhd_field f, const double *host) {
         if (kind != MHD_STORE_F32) scale = s->g.b_scale;
         dst = s->b(s->cb);
     }
-    std::lock_guard<std::mutex> held(s->io->mu);
+    IoUse use(s);
     STEPCHK(io_buffers(*s->io, (size_t)(3 * N), s->device));
     auto scaled = [&](float *p, size_t first, size_t count) {
         for (size_t i = 0; i < count; ++i) p[i] = (float)((host[first + i] - offset) / scale);
@@ -518,6 +534,7 @@ mhd_status fill_field(mhd_sim *s, mhd_field f, const double *host) {
         HIPCHK(launch_store_kind(s->stream, MHD_STORE_F16, stage, s->u16(), n));
     }
     HIPCHK(hipStreamSynchronize(s->stream));
+    use.done();
     return MHD_OK;
 }
 
@@ -1312,7 +1329,7 @@ mhd_status mhd_get_field(mhd_sim *s, mhd_field f, double *host) {
         from = stage;
     }
     DevCtrl h;
-    std::lock_guard<std::mutex> held(s->io->mu);
+    IoUse use(s);
     STEPCHK(io_buffers(*s->io, (size_t)(3 * s->N), s->device));
     // read with the field: one wait for both
     HIPCHK(hipMemcpyAsync(s->io->ctrl, s->ctrl(), sizeof h, hipMemcpyDeviceToHost, s->stream));
@@ -1326,6 +1343,7 @@ mhd_status mhd_get_field(mhd_sim *s, mhd_field f, double *host) {
             for (size_t i = 0; i < count; ++i) host[first + i] += (double)p[i] * scale;
         }));
     }
+    use.done();
     return state_status(h);
 }
 

@@ -359,6 +359,31 @@ std::string odd_counts() {
     return "ok";
 }
 
+// A HIP call that fails in the middle of a field copy: the call returns with no copy of the pinned chunks
+// under way, and the next calls work.
+std::string error_in_a_copy() {
+    for (const char *call : {"hipMemcpyAsync", "hipEventRecord", "hipEventSynchronize", "hipHostMalloc", "hipEventCreate"})
+        for (int after = 0; after < 6; ++after)
+            for (int write = 0; write < 2; ++write) {
+                Box b(0, 96, 80, 80);  // several chunks
+                b.params();
+                const size_t n = 3 * (size_t)b.g.nx * b.g.ny * b.g.nz;
+                std::vector<double> f(n, 0.25), g(n);
+                auto copy = [&] { return write ? mhd_set_field(b.sim, MHD_FIELD_U, f.data()) : mhd_get_field(b.sim, MHD_FIELD_U, g.data()); };
+                fail_call = call;
+                fail_after = after;
+                const mhd_status st = copy();
+                const bool failed = fail_after < 0;
+                fail_call = "";
+                if (failed != (st != MHD_OK)) return std::string("an error of ") + call + " was not reported";
+                if (failed && !b.stream.host.empty()) return std::string("copies under way after an error of ") + call;
+                Box::check(mhd_set_field(b.sim, MHD_FIELD_U, f.data()));
+                Box::check(mhd_get_field(b.sim, MHD_FIELD_U, g.data()));
+                if (f != g) return std::string("read back differs after an error of ") + call;
+            }
+    return "ok";
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     std::string r = "unknown scenario";
@@ -367,6 +392,7 @@ int main(int argc, char **argv) {
     if (what == "other_gpu") r = other_gpu_steps();
     if (what == "device") r = other_device_current();
     if (what == "odd_counts") r = odd_counts();
+    if (what == "copy_error") r = error_in_a_copy();
     if (what == "long_call") r = long_call_lets_others_in();
     puts((complaint.empty() ? r : complaint).c_str());
     fflush(stdout);

@@ -24,6 +24,7 @@ def emu(tmp_path_factory):
     "other_gpu",     # a call held up on one GPU does not hold up steps on another
     "long_call",     # nor, for more than a bounded number of steps, on the same one
     "odd_counts",    # the control block is read to an address it can stand at
+    "copy_error",    # a failing call in the middle of a field copy leaves no copy under way
     "device",        # calls made while another GPU is the current one
 ])
 def test_scenario(emu, scenario):

@@ -40,14 +40,19 @@ constexpr int kRows = 8;  // rows of a tile
 __device__ __forceinline__ unsigned lds_offset(const void *p) {
     return (unsigned)(size_t)(__attribute__((address_space(3))) const void *)p;
 }
+// m0 is named as written, so that no value of the compiler's own is kept there across a load; it warns
+// that the register is one it reserves for such uses.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 // 16 bytes a lane from base + voff (bytes, per lane) to LDS at lds + 16 lane
 __device__ __forceinline__ void load_lds16(unsigned lds, unsigned voff, const void *base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(voff), "s"(base) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds), "v"(voff), "s"(base) : "m0", "memory");
 }
 // 4 bytes a lane from an address of its own, lanes of the execution mask only
 __device__ __forceinline__ void load_lds4(unsigned lds, const char *src) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(lds), "v"(src) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" : : "s"(lds), "v"(src) : "m0", "memory");
 }
+#pragma clang diagnostic pop
 template <int N>
 __device__ __forceinline__ void wait_vm() {
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");

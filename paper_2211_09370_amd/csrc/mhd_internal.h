@@ -18,7 +18,9 @@ struct DevCtrl {
     int32_t status;    // bit 0: unstable
     int32_t n_records; // budget records written since the host last drained the ring
     int32_t overflow;  // records dropped because the ring was full
-    int32_t pad[9];
+    int32_t stalled;   // 1: a wait of a step's resident iteration was given up (a word of its own, since
+                       // status is stored to by others)
+    int32_t pad[8];
 };
 
 // Scalar parameters the step kernels read (copied by value into every launch).

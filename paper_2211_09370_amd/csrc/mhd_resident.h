@@ -25,7 +25,6 @@ enum { kResCounting = 0, kResGo = 1, kResGivenUp = 2 };
 constexpr size_t kResSyncInts = kResFlags + (size_t)kResFlagStride * kResMaxTiles;
 constexpr long long kResRollTicks = 2000000;     // roll call: 20 ms of the 100 MHz clock
 constexpr long long kResStallTicks = 1000000000; // a wait after it: 10 s
-constexpr int kStatusStalled = 2;                // DevCtrl::status bit
 
 // The tables are per place in the cross-section: those of all x tiles there are the same.
 // Header: counts and offsets (in words from the table's start). Places in LDS are
@@ -55,7 +54,7 @@ struct ResArgs {
     float kappa, omega;
     const int *tab, *tab_off;
     int *sync;
-    int32_t *status;
+    int32_t *stalled;  // DevCtrl::stalled
     long long roll_ticks;
 };
 

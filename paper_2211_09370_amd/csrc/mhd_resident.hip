@@ -412,7 +412,7 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
                 if ((++polls & 1023) == 0 &&
                     (wall_clock64() - t0 > kResStallTicks || ld_agent(a.sync + kResStalled))) {
                     __hip_atomic_store(a.sync + kResStalled, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    *a.status |= kStatusStalled;
+                    *a.stalled = 1;
                     break;
                 }
             }

@@ -633,7 +633,7 @@ mhd_status resident_iteration(mhd_sim *s, const StepConst &c) {
     a.tab_off = s->at<int>(s->L.res_tab);
     a.tab = a.tab_off + p.gy * p.gz + 1;
     a.sync = s->at<int>(s->L.res_sync);
-    a.status = c.status;
+    a.stalled = &s->ctrl()->stalled;
     a.roll_ticks = s->res_mode == 2 ? -1 : kResRollTicks;
     const hipError_t e = launch_mag_resident(s->stream, a, p, c.lattice == 27);
     if (e != hipSuccess) return fail(MHD_ERR_HIP, "launch of the magnetic iteration failed: %s", hipGetErrorString(e));
@@ -709,7 +709,7 @@ mhd_status read_ctrl(mhd_sim *s, DevCtrl *h) {
 }
 
 mhd_status state_status(const DevCtrl &h) {
-    if (h.status & kStatusStalled) return fail(MHD_ERR_HIP, "the magnetic iteration of a step stalled on the GPU: the state is lost");
+    if (h.stalled) return fail(MHD_ERR_HIP, "the magnetic iteration of a step stalled on the GPU: the state is lost");
     if (h.status & 1) return fail(MHD_ERR_UNSTABLE, "a fluid step or a budget pass found non-finite values or |u| >= c_s");
     return MHD_OK;
 }

@@ -7,7 +7,7 @@
 //   resident_emu nx ny nz radius n_mag lattice alpha magnets max_wg mode workers
 //
 // radius 0: no wall; max_wg: compute units the plan is made for; mode: 1 resident, 2 roll call given
-// up (the stand-in does the work); workers: workgroups on the chip at once (the others start when one
+// up (the stand-in does the work), 4 a neighbour never comes; workers: workgroups on the chip at once (the others start when one
 // ends). Prints one line: the plan, then "ok" or what went wrong.
 #include <sched.h>
 #include <stdio.h>
@@ -52,7 +52,10 @@ void leave(int at) {
 }
 void barrier(int line) { leave(line); }
 void pause() { leave(0); }
+bool fast_clock = false;
 long long clock() {  // a slow clock: the emulation is slow as well
+    static std::atomic<long long> fast{0};
+    if (fast_clock) return fast += 10000000;
     timespec t;
     clock_gettime(CLOCK_MONOTONIC, &t);
     return t.tv_sec * 1000000ll + t.tv_nsec / 1000;
@@ -346,7 +349,7 @@ int main(int argc, char **argv) {
     for (auto *v : {&u, &b0, &b1, &bext, &byz, &sj, &wall})
         for (float &x : *v) x = 0.1f * rnd();
     std::vector<int> sync(kResSyncInts, 0);
-    int32_t status = 0;
+    int32_t stalled = 0;
     ResArgs a{};
     a.u = u.data();
     a.b[0] = b0.data();
@@ -375,8 +378,13 @@ int main(int argc, char **argv) {
     a.tab = p.tab.data();
     a.tab_off = p.tab_off.data();
     a.sync = sync.data();
-    a.status = &status;
+    a.stalled = &stalled;
     a.roll_ticks = mode == 2 ? -1 : 1000000000ll;
+    if (mode == 4) {  // as after a roll call that all but one workgroup left: its waits end all the same
+        sync[kResState] = kResGo;
+        emu::workers = 1;
+        emu::fast_clock = true;
+    }
     std::vector<float> want = b0;
     if (q27)
         reference<true>(a, w, want);
@@ -386,7 +394,7 @@ int main(int argc, char **argv) {
     const std::vector<float> &got = n_mag & 1 ? b0 : b1;
     size_t differ = 0;
     for (size_t i = 0; i < 3 * N; ++i) differ += memcmp(&want[i], &got[i], 4) != 0;
-    if (status) return printf("status %d\n", status), 0;
+    if (stalled) return puts("stalled"), 0;
     if (differ) return printf("%zu values differ\n", differ), 0;
     return puts("ok"), 0;
 }

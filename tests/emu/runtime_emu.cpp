@@ -201,6 +201,8 @@ hipError_t launch_reset_records(hipStream_t, DevCtrl *) { return hipSuccess; }
 hipError_t launch_residual_final(hipStream_t, const double *, double *) { return hipSuccess; }
 }  // namespace mhd
 
+void mark_stalled(DevCtrl *c) { c->stalled = 1; }
+
 // A box of 8 x 32 x 32 with a ring wall (it has a resident plan) on a stream of a device.
 struct Box {
     emuStream stream;
@@ -384,6 +386,21 @@ std::string error_in_a_copy() {
     return "ok";
 }
 
+// A step that stalled is reported as such, also where the state it left is an unstable one.
+std::string stall_report() {
+    Box b;
+    b.params();
+    std::vector<double> g(3 * (size_t)b.g.nx * b.g.ny * b.g.nz);
+    DevCtrl *c = b.sim->ctrl();
+    mark_stalled(c);
+    c->status = 1;  // as the fluid update and the budget pass store it
+    const mhd_status st = mhd_get_field(b.sim, MHD_FIELD_U, g.data());
+    if (st != MHD_ERR_HIP) return "the stall of a step was reported as " + std::to_string(st);
+    int64_t n = 0;
+    if (mhd_get_budgets(b.sim, nullptr, 0, &n) != MHD_ERR_HIP) return "the stall was not reported with the budgets";
+    return "ok";
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     std::string r = "unknown scenario";
@@ -393,6 +410,7 @@ int main(int argc, char **argv) {
     if (what == "device") r = other_device_current();
     if (what == "odd_counts") r = odd_counts();
     if (what == "copy_error") r = error_in_a_copy();
+    if (what == "stall") r = stall_report();
     if (what == "long_call") r = long_call_lets_others_in();
     puts((complaint.empty() ? r : complaint).c_str());
     fflush(stdout);

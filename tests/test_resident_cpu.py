@@ -57,6 +57,10 @@ def test_kernel_equals_plain_loops_bitwise(emu, case, mode):
         assert int(f[f.index("lw") + 1]) > 64 and f[f.index("short") + 1] == "1", out
 
 
+def test_a_wait_for_a_neighbour_that_never_comes_ends_and_is_reported(emu):
+    assert run(emu, 8, 32, 32, 14, 2, 19, 1, 0, 8, 4, 1).endswith(" stalled")
+
+
 # boxes of the GPU tests (tests/test_gpu_resident.py) whose last x tile is shorter than its tiles of more
 # than a wave's columns
 WIDE_SHORT = ((131, 57, 57, 25), (400, 42, 42, 18), (163, 53, 53, 24), (497, 31, 31, 13), (131, 43, 43, 18), (194, 45, 45, 20))

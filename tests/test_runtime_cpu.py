@@ -25,6 +25,7 @@ def emu(tmp_path_factory):
     "long_call",     # nor, for more than a bounded number of steps, on the same one
     "odd_counts",    # the control block is read to an address it can stand at
     "copy_error",    # a failing call in the middle of a field copy leaves no copy under way
+    "stall",         # a stalled step is not reported as an unstable state
     "device",        # calls made while another GPU is the current one
 ])
 def test_scenario(emu, scenario):

@@ -186,8 +186,9 @@ mhd_status mhd_set_markers(mhd_sim *s, const double *xyz, int64_t M, const doubl
  * results; not while profiling, in calls made under the caller's own stream capture, or in a
  * batch. This call and mhd_set_markers prepare that launch (about 1 ms of host time when the wall
  * is new), so that step calls only launch. The environment variable MHD_RESIDENT, read here,
- * selects: 0 = never, 1 (default) = where it fits, 2 = always its one-workgroup form (slow; for
- * tests). */
+ * selects: 0 = never, 1 (default) = where it fits; for tests, 2 = always the form that takes over
+ * when the launch's workgroups cannot all be on the GPU at once, 3 = as 1, each time with that
+ * happening (the next 64 steps or more then launch their sweeps one by one). */
 mhd_status mhd_set_params(mhd_sim *s, const mhd_params *p);
 
 /* Copy a field in / out (host float64, layout above; rho has 1 component, u and b 3).

@@ -67,12 +67,15 @@ __device__ __forceinline__ void ctrl_begin_body(DevCtrl *ctrl, const StepConst &
         G = c.G0;
     ctrl->G_step = G;
 }
-// One workgroup. sync: the roll call and the flags of the step's resident iteration are cleared here,
-// which saves a launch of a step (5 x 83 x 83, 12 sweeps: 93.0 -> 91.3 us a step).
+// One workgroup. sync: the roll call and the flags of the step's resident iteration are set here
+// (kResCounting is 0), which saves a launch of a step (5 x 83 x 83, 12 sweeps: 93.0 -> 91.3 us a step).
 __global__ void __launch_bounds__(kResMaxTiles) k_ctrl_begin(DevCtrl *ctrl, StepConst c, int *sync, int nwg) {
     if (threadIdx.x == 0) ctrl_begin_body(ctrl, c);
     if (sync) {
-        if (threadIdx.x < kResFlags) sync[threadIdx.x] = 0;
+        const int hold = sync[kResHold];
+        __syncthreads();
+        if (threadIdx.x < kResKept) sync[threadIdx.x] = threadIdx.x == kResState && hold > 0 ? kResHeld : 0;
+        if (threadIdx.x == 0 && hold > 0) sync[kResHold] = hold - 1;
         if ((int)threadIdx.x < nwg) sync[kResFlags + kResFlagStride * threadIdx.x] = 0;
     }
 }

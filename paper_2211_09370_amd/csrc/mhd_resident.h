@@ -19,9 +19,13 @@ constexpr size_t resident_tab_ints(int ny, int nz) {
     return (rows < 9000 ? 40 * rows : 360000) + 4096;
 }
 
-// words of the synchronisation area; flags stand 64 bytes apart
-enum { kResCount = 0, kResState = 1, kResStalled = 2, kResFlags = 16, kResFlagStride = 16 };
-enum { kResCounting = 0, kResGo = 1, kResGivenUp = 2 };
+// Words of the synchronisation area. Those below kResKept and the flags (64 bytes apart) are set anew by
+// every step's first launch; the others last: steps left that take the stand-in without a roll call,
+// roll calls given up, steps done by the stand-in.
+enum { kResCount = 0, kResState = 1, kResStalled = 2, kResTicket = 3, kResKept = 8, kResHold = 8, kResGiveUps = 9, kResStandIns = 10 };
+enum { kResFlags = 16, kResFlagStride = 16 };
+enum { kResCounting = 0, kResGo = 1, kResGivenUp = 2, kResHeld = 3 };
+constexpr int kResHoldSteps = 64;                // steps without a roll call after one was given up
 constexpr size_t kResSyncInts = kResFlags + (size_t)kResFlagStride * kResMaxTiles;
 constexpr long long kResRollTicks = 2000000;     // roll call: 20 ms of the 100 MHz clock
 constexpr long long kResStallTicks = 1000000000; // a wait after it: 10 s
@@ -54,8 +58,10 @@ struct ResArgs {
     float kappa, omega;
     const int *tab, *tab_off;
     int *sync;
-    int32_t *stalled;  // DevCtrl::stalled
-    long long roll_ticks;
+    int32_t *stalled;      // DevCtrl::stalled
+    long long roll_ticks;  // limit of the roll call; < 0: given up at once
+    int record;            // 1: a roll call given up is remembered (kResHold, and host for the next calls)
+    int *host;             // pinned: roll calls given up, steps done by the stand-in
 };
 
 // Tiles are tx columns of ty x tz rows: whole rows (gx = 1, periodic in the tile) or, where the box is
@@ -83,7 +89,7 @@ ResPlan make_resident_plan(int nx, int ny, int nz, const ResWall &wall, int max_
 
 // Readies the kernels of plan p on the current GPU (once, before launches).
 hipError_t prepare_mag_resident(const ResPlan &p);
-// The launches of one step's iteration; a.sync cleared before (launch_ctrl_begin).
+// The launches of one step's iteration; a.sync set by the step's first launch (launch_ctrl_begin).
 hipError_t launch_mag_resident(hipStream_t s, const ResArgs &a, const ResPlan &p, bool q27);
 
 }  // namespace mhd

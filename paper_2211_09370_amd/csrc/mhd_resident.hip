@@ -30,8 +30,18 @@
 // the last one to arrive turns the state from "counting" to "go", and one that has waited
 // roll_ticks turns it to "given up" instead, by compare-and-swap, so all agree. After "go" every
 // workgroup is resident and each wait ends; after "given up" all leave with b untouched, and the
-// launch that follows on the stream (solo = 1, one workgroup, nothing to wait for) does the same
-// iteration tile by tile through memory; it leaves at once after "go".
+// launch that follows on the stream, the stand-in, does the iteration; it leaves at once after "go".
+//
+// The stand-in needs no more of its workgroups on the chip than one. They take the tiles' turns (an
+// iteration of a tile) from a counter, iteration by iteration, wait for the tile's neighbours to have
+// had their turns of the iteration before, and take the tile from memory to memory. A turn waits for
+// turns of lower numbers only, which running workgroups have taken, so every wait ends however few
+// there are. A roll call given up is remembered for kResHoldSteps steps, which go to the stand-in at
+// once, and counted in host memory, where the next step calls see it and launch their sweeps one by
+// one for a while (ResidentCall, mhd_runtime.cpp): so a GPU that other work keeps busy costs one
+// roll call, not one a step. A step of 12 sweeps in the stand-in (in it as one workgroup that took
+// every tile before; resident): 8 x 32 x 32 100 us (2.7 ms; 81 us), 32^3 122 us (11.8 ms; 91 us),
+// 192 x 70 x 70 335 us (43 ms; 273 us).
 //
 // The arithmetic per cell is that of the other float32 kernels (mhd_sweep_math.h, and the wall
 // correction's sums in the same order), so the fields are the same bit for bit.
@@ -65,7 +75,7 @@ __device__ __forceinline__ int opaque(int v) {
 // Roll call; true if every workgroup of the grid is resident. Thread 0's answer, for all.
 __device__ __forceinline__ bool roll_call(int *sync, int nwg, long long ticks, int *answer) {
     if (threadIdx.x == 0) {
-        int *state = sync + kResState;
+        int *state = sync + kResState;  // kResHeld from the start: no roll call
         const int before = __hip_atomic_fetch_add(sync + kResCount, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         int expect = kResCounting;
         if (ticks < 0)  // never resident (tests of the fallback)
@@ -94,13 +104,13 @@ __device__ __forceinline__ bool roll_call(int *sync, int nwg, long long ticks, i
 
 // NS: staged rows (tile and halo) per work-item, CZ: cells of a z column per work-item. A work-item
 // keeps one x for the whole iteration and takes rows tr, tr + RS, ... of every list.
-template <int NS, int CZ, bool Q27, bool SOLO>
+template <int NS, int CZ, bool Q27, bool STAND_IN>
 __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
     extern __shared__ __align__(16) float lds[];
     __shared__ int s_state;
     const int t = threadIdx.x, NT = blockDim.x;
-    if constexpr (SOLO) {  // the launch before this one has done the iteration
-        if (ld_agent(a.sync + kResState) == kResGo) return;
+    if constexpr (STAND_IN) {
+        if (ld_agent(a.sync + kResState) == kResGo) return;  // the launch before this one has done the iteration
     } else {
         if (!roll_call(a.sync, a.nwg, a.roll_ticks, &s_state)) return;
     }
@@ -371,44 +381,21 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
         }
     };
 
-    if constexpr (SOLO) {
-        for (int i = 0; i < a.n_mag; ++i)
-            for (int tile = 0; tile < a.nwg; ++tile) {
-                setup(tile);
-                load_rows(a.b[i & 1], true);
-                request();
-                if (i) correct();
-                sweep(a.b[1 - (i & 1)], true);
-            }
-        for (int tile = 0; tile < a.nwg; ++tile) {
-            setup(tile);
-            load_rows(a.b[a.n_mag & 1], true);
-            request();
-            correct();
-            store_tile(a.b[1 - (a.n_mag & 1)]);
-        }
-        return;
-    } else {
+    // Flags count a tile's iterations. A wait guards against a stall of the machine with the clock, and
+    // reports it as an error of the step.
     int *flag = a.sync + kResFlags;
-    const int me = blockIdx.x;
-    setup(me);
-    load_rows(a.b[0], true);
     // the tiles exchanged with: those of the list, and where the box is cut along x also those before and
     // after each in x (itself listed; a tile waits for itself at once)
-    const int wide = xh ? 3 : 1, nnb = wide * tab_hdr(kResNNb);
-    int nb = me;
-    if (t < nnb) nb = wrapi(me % a.gx + (xh ? t % 3 - 1 : 0), a.gx) + a.gx * stab[tab_hdr(kResONb) + t / wide];
-    for (int i = 0; i < a.n_mag; ++i) {
-        float *next = a.b[1 - (i & 1)];
-        sweep(next, false);
-        if (t == 0) __hip_atomic_store(flag + kResFlagStride * me, i + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        request();
-        if (t < nnb) {
-            // every workgroup is resident, so this wait ends; the clock only guards against a stall
-            // of the machine, which is reported as an error of the step
+    const int wide = xh ? 3 : 1;
+    auto neighbour = [&](int tile) {
+        return t < wide * tab_hdr(kResNNb) ? wrapi(tile % a.gx + (xh ? t % 3 - 1 : 0), a.gx) + a.gx * stab[tab_hdr(kResONb) + t / wide]
+                                           : -1;
+    };
+    auto wait_for = [&](int nb, int done) {
+        if (nb >= 0) {
             const long long t0 = wall_clock64();
             int polls = 0;
-            while (ld_agent(flag + kResFlagStride * nb) < i + 1) {
+            while (ld_agent(flag + kResFlagStride * nb) < done) {
                 if ((++polls & 1023) == 0 &&
                     (wall_clock64() - t0 > kResStallTicks || ld_agent(a.sync + kResStalled))) {
                     __hip_atomic_store(a.sync + kResStalled, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -418,10 +405,55 @@ __global__ void __launch_bounds__(kResMaxThreads) k_mag_resident(ResArgs a) {
             }
         }
         __syncthreads();
-        load_rows(next, false);
-        correct();
-    }
-    store_tile(a.b[1 - (a.n_mag & 1)]);
+    };
+    auto raise = [&](int tile, int done) {
+        if (t == 0) __hip_atomic_store(flag + kResFlagStride * tile, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+
+    if constexpr (STAND_IN) {
+        // turn k: iteration k / nwg of tile k % nwg; after the last iteration a turn a tile corrects it
+        for (;;) {
+            __syncthreads();
+            if (t == 0) s_state = __hip_atomic_fetch_add(a.sync + kResTicket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            const int turn = s_state, i = turn / a.nwg, tile = turn - i * a.nwg;
+            if (i > a.n_mag) return;
+            if (turn == 0 && t == 0) {  // for the next steps and calls (one workgroup of a step comes here)
+                if (a.record && ld_agent(a.sync + kResState) == kResGivenUp) {
+                    a.sync[kResHold] = kResHoldSteps;
+                    const int n = ++a.sync[kResGiveUps];
+                    __hip_atomic_store(a.host, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                }
+                const int n = ++a.sync[kResStandIns];
+                __hip_atomic_store(a.host + 1, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+            setup(tile);
+            wait_for(neighbour(tile), i);
+            load_rows(a.b[i & 1], true);
+            request();
+            if (i) correct();
+            if (i < a.n_mag) {
+                sweep(a.b[1 - (i & 1)], true);
+                raise(tile, i + 1);
+            } else {
+                store_tile(a.b[1 - (i & 1)]);
+            }
+        }
+    } else {
+        const int me = blockIdx.x;
+        setup(me);
+        load_rows(a.b[0], true);
+        const int nb = neighbour(me);
+        for (int i = 0; i < a.n_mag; ++i) {
+            float *next = a.b[1 - (i & 1)];
+            sweep(next, false);
+            raise(me, i + 1);
+            request();
+            wait_for(nb, i + 1);
+            load_rows(next, false);
+            correct();
+        }
+        store_tile(a.b[1 - (a.n_mag & 1)]);
     }
 }
 
@@ -455,8 +487,8 @@ hipError_t prepare_mag_resident(const ResPlan &p) {
 hipError_t launch_mag_resident(hipStream_t s, const ResArgs &a, const ResPlan &p, bool q27) {
     const ResForms f = resident_forms(p);
     void *args[] = {const_cast<ResArgs *>(&a)};
-    for (int solo = 0; solo < 2; ++solo) {
-        const hipError_t e = hipLaunchKernel(f.k[q27][solo], dim3(solo ? 1 : p.nwg), dim3(p.threads), args, p.lds_bytes, s);
+    for (const void *k : f.k[q27]) {  // the iteration, its stand-in
+        const hipError_t e = hipLaunchKernel(k, dim3(p.nwg), dim3(p.threads), args, p.lds_bytes, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -220,13 +220,19 @@ struct mhd_sim {
     bool graph_on = true;
     // Resident magnetic iteration (mhd_resident.hip): the wall as lines along x (empty tap_row: no
     // wall; wall_lines false: markers of another form), and the plan for it (plan_resident; not ok until
-    // made). MHD_RESIDENT at mhd_set_params: 0 = never, 1 (default) = where the box fits,
-    // 2 = its one-workgroup form always.
+    // made). MHD_RESIDENT at mhd_set_params: 0 = never, 1 (default) = where the box fits, 2 = always the
+    // stand-in of a roll call given up, 3 = as 1 with every roll call given up.
     ResWall res_wall;
     bool wall_lines = true;
     ResPlan res_plan;
     bool res_planned = false, res_now = false;
     int res_mode = 1, cus = 0;
+    // Roll calls given up and steps done by the stand-in, as the GPU has written them to host memory;
+    // the first of them seen so far, steps left that launch their sweeps one by one because of it, how
+    // many those were, and resident steps since.
+    int *res_host = nullptr, *res_host_dev = nullptr;
+    int res_seen = 0;
+    int64_t res_skip = 0, res_backoff = 0, res_since = 0;
     hipEvent_t res_event = nullptr;  // end of this box's last steps with resident launches
     std::shared_ptr<HostIo> io = std::make_shared<HostIo>();  // one for all boxes of a batch
     bool fused_lf = true;  // Lorentz + fluid in one launch where the storage allows (MHD_FUSED_LF=0: two)
@@ -602,7 +608,7 @@ mhd_status mag_iteration(mhd_sim *s, const StepConst &c, int m) {
     return MHD_OK;
 }
 
-// All sweeps of a step and their wall corrections in one launch (and its one-workgroup stand-in).
+// All sweeps of a step and their wall corrections in one launch (and its stand-in).
 mhd_status resident_iteration(mhd_sim *s, const StepConst &c) {
     const ResPlan &p = s->res_plan;
     ResArgs a{};
@@ -634,7 +640,9 @@ mhd_status resident_iteration(mhd_sim *s, const StepConst &c) {
     a.tab = a.tab_off + p.gy * p.gz + 1;
     a.sync = s->at<int>(s->L.res_sync);
     a.stalled = &s->ctrl()->stalled;
-    a.roll_ticks = s->res_mode == 2 ? -1 : kResRollTicks;
+    a.roll_ticks = s->res_mode >= 2 ? -1 : kResRollTicks;
+    a.record = s->res_mode != 2;
+    a.host = s->res_host_dev;
     const hipError_t e = launch_mag_resident(s->stream, a, p, c.lattice == 27);
     if (e != hipSuccess) return fail(MHD_ERR_HIP, "launch of the magnetic iteration failed: %s", hipGetErrorString(e));
     if ((s->prm.n_mag & 1) == 0) s->cb = 1 - s->cb;  // the result is in b[1 - (n_mag & 1)]
@@ -645,7 +653,7 @@ mhd_status one_step(mhd_sim *s) {
     const StepConst c = step_const(s);
     hipStream_t st = s->stream;
     STEPCHK(timed(s, MHD_K_CONTROL, "ctrl_begin", [&] {
-        return launch_ctrl_begin(st, s->ctrl(), c, s->res_now ? s->at<int>(s->L.res_sync) : nullptr, s->res_plan.nwg);
+        return launch_ctrl_begin(st, s->ctrl(), c, s->res_plan.ok ? s->at<int>(s->L.res_sync) : nullptr, s->res_plan.nwg);
     }));
     // 1. magnetic iteration, wall correction after every sweep
     if (s->res_now) {
@@ -780,7 +788,8 @@ SweepLaunch default_tiles(const mhd_grid_desc &g) {
 // of one process on one GPU. Workgroups of a resident launch wait for each other, so those
 // in flight at once must fit the chip together: steps whose workgroups would not fit beside the
 // unfinished ones of other boxes wait for them on the GPU (the roll call in the kernel covers what
-// this process cannot see). The GPU's lock is held from the decision to the last launch, of
+// this process cannot see; when one was given up, the next steps launch their sweeps one by one, 64
+// of them and twice as many each further time in a row). The GPU's lock is held from the decision to the last launch, of
 // kResSteps steps at most, so that a long call lets other boxes' in.
 constexpr int64_t kResSteps = 32;
 struct ResidentUse {
@@ -820,9 +829,23 @@ class ResidentCall {
     ~ResidentCall() {
         if (s->res_now) (void)end();  // an error left the call early: what it launched is in flight
     }
-    mhd_status next() {  // before the first steps, and before each further kResSteps
+    // before the first steps of a call and before each further kResSteps; left: steps still to do
+    mhd_status next(int64_t left) {
         STEPCHK(end());
         if (s->res_mode == 0 || s->prof || !s->res_plan.ok) return MHD_OK;
+        if (s->prm.n_mag >= INT32_MAX / (2 * kResMaxTiles)) return MHD_OK;  // the stand-in's turns are counted in 32 bits
+        const int64_t n = std::min(left, kResSteps);
+        const int given_up = __atomic_load_n(s->res_host, __ATOMIC_RELAXED);
+        if (given_up != s->res_seen) {
+            s->res_backoff = std::min<int64_t>(std::max<int64_t>(2 * s->res_backoff, kResHoldSteps), 64 * kResHoldSteps);
+            s->res_skip = s->res_backoff;
+            s->res_seen = given_up;
+            s->res_since = 0;
+        }
+        if (s->res_skip > 0) {
+            s->res_skip -= n;
+            return MHD_OK;
+        }
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(s->stream, &cap) != hipSuccess) {
             (void)hipGetLastError();
@@ -838,6 +861,8 @@ class ResidentCall {
         if (others > 0 && others + s->res_plan.nwg > s->cus)
             for (const ResidentUse &x : gpu.use)
                 if (x.sim != s) HIPCHK(hipStreamWaitEvent(s->stream, x.sim->res_event, 0));
+        s->res_since += n;
+        if (s->res_since > 16 * s->res_backoff) s->res_backoff = 0;  // the GPU has long been free
         s->res_now = true;
         return MHD_OK;
     }
@@ -883,6 +908,18 @@ mhd_status plan_resident(mhd_sim *s) {
     HIPCHK(hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, s->device));
     drop_step_graphs(s);
     if (!s->res_event) HIPCHK(hipEventCreateWithFlags(&s->res_event, hipEventDisableTiming));
+    if (!s->res_host) {
+        void *h = nullptr, *d = nullptr;
+        HIPCHK(hipHostMalloc(&h, 2 * sizeof(int), hipHostMallocMapped));
+        const hipError_t e = hipHostGetDevicePointer(&d, h, 0);
+        if (e != hipSuccess) {
+            (void)hipHostFree(h);
+            return fail(MHD_ERR_HIP, "hipHostGetDevicePointer failed: %s", hipGetErrorString(e));
+        }
+        s->res_host = static_cast<int *>(h);
+        s->res_host[0] = s->res_host[1] = 0;
+        s->res_host_dev = static_cast<int *>(d);
+    }
     ResPlan p;
     try {
         p = make_resident_plan(s->g.nx, s->g.ny, s->g.nz, s->res_wall, s->cus);
@@ -1380,7 +1417,7 @@ mhd_status mhd_step(mhd_sim *s, int64_t n_steps, int32_t budget_every) {
     // (one launch call per step instead of about 3 n_mag + 6); profiling steps launch directly.
     const bool graph = s->graph_on && s->stream != nullptr && !s->prof;
     for (int64_t i = 0; i < n_steps; ++i) {
-        if (i % kResSteps == 0) STEPCHK(resident.next());
+        if (i % kResSteps == 0) STEPCHK(resident.next(n_steps - i));
         if (graph) {
             const int key = s->cb | (s->cr << 1) | (s->cu << 2) | (s->ch << 3) | (s->res_now ? 16 : 0);
             auto it = std::find_if(s->graphs.begin(), s->graphs.end(), [&](const mhd_sim::StepGraph &g) { return g.key == key; });
@@ -1457,7 +1494,7 @@ mhd_status step_in_scratch(mhd_sim *s, int64_t n_steps, int32_t budget_every, vo
     ResidentCall resident(s);
     mhd_status st = MHD_OK;
     for (int64_t i = 0; i < n_steps && st == MHD_OK; ++i) {  // direct launches: no graph holds these pointers
-        if (i % kResSteps == 0) st = resident.next();
+        if (i % kResSteps == 0) st = resident.next(n_steps - i);
         if (st == MHD_OK) st = one_step(s);
         if (st == MHD_OK && budget_every > 0 && s->t_host % budget_every == 0) st = record_budget(s);
     }
@@ -1667,6 +1704,7 @@ mhd_status mhd_destroy(mhd_sim *s) {
     (void)hipStreamSynchronize(s->stream);
     ResidentCall::forget(s);
     if (s->res_event) (void)hipEventDestroy(s->res_event);
+    if (s->res_host) (void)hipHostFree(s->res_host);
     for (int k = 0; k < MHD_K_COUNT; ++k)
         for (auto &e : s->ev_pool[k]) {
             (void)hipEventDestroy(e.a);

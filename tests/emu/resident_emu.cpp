@@ -6,9 +6,10 @@
 //
 //   resident_emu nx ny nz radius n_mag lattice alpha magnets max_wg mode workers
 //
-// radius 0: no wall; max_wg: compute units the plan is made for; mode: 1 resident, 2 roll call given
-// up (the stand-in does the work), 4 a neighbour never comes; workers: workgroups on the chip at once (the others start when one
-// ends). Prints one line: the plan, then "ok" or what went wrong.
+// radius 0: no wall; max_wg: compute units the plan is made for; mode: 1 resident, 2 the stand-in, 3 the
+// stand-in after a roll call given up, 4 resident and a neighbour never comes, 5 the stand-in of a later
+// step; workers: workgroups on the chip at once (the others start when one ends). Prints one line: the
+// plan, then "ok" or what went wrong.
 #include <sched.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -379,7 +380,11 @@ int main(int argc, char **argv) {
     a.tab_off = p.tab_off.data();
     a.sync = sync.data();
     a.stalled = &stalled;
-    a.roll_ticks = mode == 2 ? -1 : 1000000000ll;
+    a.roll_ticks = mode == 2 || mode == 3 ? -1 : 1000000000ll;
+    int host[2] = {0, 0};
+    a.record = mode != 2;
+    a.host = host;
+    if (mode == 5) sync[kResState] = kResHeld, sync[kResHold] = 7;
     if (mode == 4) {  // as after a roll call that all but one workgroup left: its waits end all the same
         sync[kResState] = kResGo;
         emu::workers = 1;
@@ -396,5 +401,9 @@ int main(int argc, char **argv) {
     for (size_t i = 0; i < 3 * N; ++i) differ += memcmp(&want[i], &got[i], 4) != 0;
     if (stalled) return puts("stalled"), 0;
     if (differ) return printf("%zu values differ\n", differ), 0;
+    const int given_up = mode == 3, stood_in = mode == 2 || mode == 3 || mode == 5, hold = mode == 3 ? kResHoldSteps : mode == 5 ? 7 : 0;
+    if (sync[kResGiveUps] != given_up || host[0] != given_up || sync[kResStandIns] != stood_in || host[1] != stood_in ||
+        sync[kResHold] != hold)
+        return printf("given up %d %d stood in %d %d hold %d\n", sync[kResGiveUps], host[0], sync[kResStandIns], host[1], sync[kResHold]), 0;
     return puts("ok"), 0;
 }

@@ -44,6 +44,7 @@ std::string complaint;
 extern const size_t sizeof_ctrl;
 std::atomic<int> resident_launches{0}, sweep_launches{0};
 std::function<void(hipStream_t)> on_graph_launch;
+bool gpu_busy = false;  // roll calls are given up
 int prepared_on = -1;  // GPU that was current when the resident kernels were prepared
 
 void complain(const std::string &s) {
@@ -178,7 +179,10 @@ SweepArgs make_sweep_args(const void *, const void *, void *, const float *, Ste
 hipError_t launch_ctrl_begin(hipStream_t, DevCtrl *, StepConst, int *, int) { return hipSuccess; }
 hipError_t launch_step_end(hipStream_t, DevCtrl *, const double *, StepConst, double) { return hipSuccess; }
 hipError_t launch_mag_sweep(hipStream_t, int, const SweepArgs &, SweepLaunch, hipEvent_t, hipEvent_t) { return ++sweep_launches, hipSuccess; }
-hipError_t launch_mag_resident(hipStream_t, const ResArgs &, const ResPlan &, bool) { return ++resident_launches, hipSuccess; }
+hipError_t launch_mag_resident(hipStream_t, const ResArgs &a, const ResPlan &, bool) {
+    if (gpu_busy) ++a.host[0];  // as the stand-in of a roll call given up counts it
+    return ++resident_launches, hipSuccess;
+}
 hipError_t prepare_mag_resident(const ResPlan &) { return prepared_on = device, hipSuccess; }
 hipError_t launch_ib(hipStream_t, int, void *, float, float, const IbArgs &) { return hipSuccess; }
 hipError_t launch_lorentz(hipStream_t, int, const void *, const void *, const float *, const float *, const DevCtrl *, float *, StepConst) { return hipSuccess; }
@@ -401,6 +405,40 @@ std::string stall_report() {
     return "ok";
 }
 
+// After a roll call was given up, steps launch their sweeps one by one for a while: 64, then twice as
+// many each time it happens again, and 64 again once the GPU has long been free.
+std::string given_up() {
+    Box b;
+    b.wall();
+    b.params(1);
+    Box::check(mhd_set_graph(b.sim, 0));
+    auto resident_steps = [&](int n) {
+        const int before = resident_launches;
+        for (int i = 0; i < n; ++i) Box::check(mhd_step(b.sim, 1, 0));
+        return resident_launches - before;
+    };
+    if (resident_steps(5) != 5) return "not resident on a free GPU";
+    for (int wait = 64; wait <= 256; wait *= 2) {
+        gpu_busy = true;
+        if (resident_steps(1) != 1) return "the step before the roll call is given up";
+        gpu_busy = false;
+        if (resident_steps(wait) != 0) return "resident right after a roll call was given up (" + std::to_string(wait) + ")";
+        if (resident_steps(3) != 3) return "not resident again after " + std::to_string(wait) + " steps";
+    }
+    if (resident_steps(16 * 256) != 16 * 256) return "not resident on a GPU that is free again";
+    gpu_busy = true;
+    resident_steps(1);
+    gpu_busy = false;
+    if (resident_steps(66) != 2) return "the number of steps was not set back";
+    // a long call looks between its steps
+    gpu_busy = true;
+    const int before = resident_launches;
+    Box::check(mhd_step(b.sim, 1000, 0));
+    const int tried = resident_launches - before;
+    gpu_busy = false;
+    return tried > 0 && tried < 1000 / 4 ? "ok" : "a long call made " + std::to_string(tried) + " resident steps of 1000 on a busy GPU";
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     std::string r = "unknown scenario";
@@ -411,6 +449,7 @@ int main(int argc, char **argv) {
     if (what == "odd_counts") r = odd_counts();
     if (what == "copy_error") r = error_in_a_copy();
     if (what == "stall") r = stall_report();
+    if (what == "given_up") r = given_up();
     if (what == "long_call") r = long_call_lets_others_in();
     puts((complaint.empty() ? r : complaint).c_str());
     fflush(stdout);

@@ -1,7 +1,7 @@
 """The resident magnetic iteration (all sweeps of a step and their wall corrections in one launch)
 against the launch sequence of a sweep, an interpolation and a spreading per iteration: the same
 fields bit for bit. MHD_RESIDENT at mhd_set_params selects the form: 0 = launch sequence, 1 = resident
-where the box fits, 2 = its one-workgroup stand-in, which a launch whose workgroups do not all
+where the box fits, 2 = its stand-in, which a launch whose workgroups do not all
 become resident leaves the work to (roll call given up by the first workgroup)."""
 import threading
 
@@ -174,3 +174,19 @@ def test_wide_x_tiles_with_a_shorter_last_one(case, monkeypatch):
     for mode in ("1", "2"):
         for f, x, y in zip(("rho", "u", "b"), out["0"], out[mode]):
             assert np.array_equal(x, y), (case, mode, f, float(np.abs(x - y).max()))
+
+
+def test_roll_calls_given_up(monkeypatch):
+    """Every resident launch finds the GPU busy: the stand-in takes over, the steps already launched go to
+    it as well, later calls launch their sweeps one by one and then try again. The same fields."""
+    print("case resident given up", flush=True)
+    w, over, wall = box("x_tiles")
+    out = []
+    for mode in ("0", "3"):
+        sim = make(w, over, wall, mode, monkeypatch)
+        for n in (3, 40, 1, 64, 2):
+            sim.step(n)
+        sim.step_noalloc(2)
+        out.append([sim.get_field(f) for f in ("rho", "u", "b")])
+        sim.close()
+    assert all(np.array_equal(x, y) for x, y in zip(*out))

@@ -45,11 +45,14 @@ CASES = {
 }
 
 
-@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("mode,at_once", [(1, 0), (2, 1), (2, 3), (3, 0), (5, 2)])
 @pytest.mark.parametrize("case", sorted(CASES))
-def test_kernel_equals_plain_loops_bitwise(emu, case, mode):
-    """mode 1: every workgroup resident; 2: the roll call is given up and the stand-in does the work."""
-    nx, ny, nz, R, n_mag, lattice, alpha, magnets, cus, at_once = CASES[case]
+def test_kernel_equals_plain_loops_bitwise(emu, case, mode, at_once):
+    """mode 1: every workgroup resident; the others: the stand-in does the work, with so many of its
+    workgroups on the chip at once (0: all of them), forced (2), after a roll call that was given up, which
+    is recorded (3), and in a later step, which makes no roll call (5)."""
+    nx, ny, nz, R, n_mag, lattice, alpha, magnets, cus, every = CASES[case]
+    at_once = at_once or every
     out = run(emu, nx, ny, nz, R, n_mag, lattice, alpha, magnets, cus, mode, at_once)
     assert out.endswith(" ok") and out.startswith("planned 1"), out
     if "wide_short" in case:

@@ -26,6 +26,7 @@ def emu(tmp_path_factory):
     "odd_counts",    # the control block is read to an address it can stand at
     "copy_error",    # a failing call in the middle of a field copy leaves no copy under way
     "stall",         # a stalled step is not reported as an unstable state
+    "given_up",      # a roll call given up sends the next steps to the launch sequence
     "device",        # calls made while another GPU is the current one
 ])
 def test_scenario(emu, scenario):

@@ -191,6 +191,13 @@ mhd_status mhd_set_markers(mhd_sim *s, const double *xyz, int64_t M, const doubl
  * happening (the next 64 steps or more then launch their sweeps one by one). */
 mhd_status mhd_set_params(mhd_sim *s, const mhd_params *p);
 
+/* How the magnetic iteration of a box runs (host-only, does not wait): info[0] = 1 if it has a plan for
+ * one launch a step (mhd_set_params), 0 if its sweeps are launches of their own; info[1..3] = the
+ * cells (x, y, z) of that plan's tiles; info[4] = steps issued in that form since mhd_create,
+ * and, of the steps finished so far, info[5] = those whose workgroups could not all be on the GPU
+ * at once within 20 ms, info[6] = those done by the form that takes over then. */
+mhd_status mhd_iteration_info(mhd_sim *s, int64_t info[7]);
+
 /* Copy a field in / out (host float64, layout above; rho has 1 component, u and b 3).
  * Synchronous with respect to the host buffer. mhd_get_field also reports a deferred
  * MHD_ERR_UNSTABLE: set by the fluid update of any step whose new velocity at some cell is

@@ -22,7 +22,7 @@ from ._abi import (MHD_BEXT_NONE, MHD_BEXT_SIX_MAGNETS, MHD_BEXT_TANH_FRINGE_Y, 
                    mhd_grid_desc, mhd_params, mhd_pipe_desc)
 
 __all__ = ["Sim", "Batch", "MhdError", "mhd_workspace_size", "mhd_create", "mhd_set_markers",
-           "mhd_set_params", "mhd_set_field", "mhd_get_field", "mhd_get_time", "mhd_set_time",
+           "mhd_set_params", "mhd_iteration_info", "mhd_set_field", "mhd_get_field", "mhd_get_time", "mhd_set_time",
            "mhd_step", "mhd_step_noalloc", "mhd_get_budgets", "mhd_record_budget", "mhd_set_profiling",
            "mhd_kernel_stats", "mhd_destroy", "mhd_get_tiles", "mhd_set_tiles", "mhd_set_graph", "mhd_tune",
            "mhd_mag_residual_curve", "mhd_choose_n_mag",
@@ -77,6 +77,12 @@ def mhd_set_markers(h, xyz: np.ndarray, u_wall=None, b_wall=None):
 
 def mhd_set_params(h, p: mhd_params):
     _abi.check(_abi.lib().mhd_set_params(h, C.byref(p)), "mhd_set_params")
+
+
+def mhd_iteration_info(h) -> dict:
+    v = (C.c_int64 * 7)()
+    _abi.check(_abi.lib().mhd_iteration_info(h, v), "mhd_iteration_info")
+    return {"planned": bool(v[0]), "tile": tuple(v[1:4]), "steps": v[4], "given_up": v[5], "stand_in": v[6]}
 
 
 def mhd_set_field(h, field: int, host: np.ndarray):
@@ -305,6 +311,10 @@ class Sim:
 
     def set_params(self, params=None, **over):
         mhd_set_params(self._h, params if isinstance(params, mhd_params) else make_params(params, **over))
+
+    def iteration_info(self) -> dict:
+        """Whether the box's sweeps of a step run as one launch, and how many steps have done so."""
+        return mhd_iteration_info(self._h)
 
     def set_field(self, name: str, arr):
         a = np.ascontiguousarray(arr, dtype=np.float64).reshape(-1)

@@ -28,7 +28,7 @@ MHD_FIELD_RHO, MHD_FIELD_U, MHD_FIELD_B_INDUCED = 0, 1, 2
  MHD_K_COUNT) = range(7)
 
 EXPORTS = ("mhd_last_error", "mhd_workspace_size", "mhd_create", "mhd_set_markers",
-           "mhd_set_params", "mhd_set_field", "mhd_get_field", "mhd_get_time", "mhd_set_time",
+           "mhd_set_params", "mhd_iteration_info", "mhd_set_field", "mhd_get_field", "mhd_get_time", "mhd_set_time",
            "mhd_step", "mhd_step_noalloc", "mhd_get_budgets", "mhd_record_budget", "mhd_set_profiling",
            "mhd_kernel_stats", "mhd_destroy", "mhd_get_tiles", "mhd_set_tiles",
            "mhd_set_graph", "mhd_tune", "mhd_mag_residual_curve", "mhd_choose_n_mag",
@@ -88,6 +88,7 @@ def lib() -> C.CDLL:
                                  C.c_void_p, C.POINTER(C.c_void_p)]
         L.mhd_set_markers.argtypes = [P, _D, C.c_int64, _D, _D]
         L.mhd_set_params.argtypes = [P, C.POINTER(mhd_params)]
+        L.mhd_iteration_info.argtypes = [P, C.POINTER(C.c_int64)]
         L.mhd_set_field.argtypes = [P, C.c_int32, _D]
         L.mhd_get_field.argtypes = [P, C.c_int32, _D]
         L.mhd_get_time.argtypes = [P, C.POINTER(C.c_int64), C.POINTER(C.c_double)]

@@ -233,6 +233,7 @@ struct mhd_sim {
     int *res_host = nullptr, *res_host_dev = nullptr;
     int res_seen = 0;
     int64_t res_skip = 0, res_backoff = 0, res_since = 0;
+    int64_t res_steps = 0;  // steps issued with resident launches
     hipEvent_t res_event = nullptr;  // end of this box's last steps with resident launches
     std::shared_ptr<HostIo> io = std::make_shared<HostIo>();  // one for all boxes of a batch
     bool fused_lf = true;  // Lorentz + fluid in one launch where the storage allows (MHD_FUSED_LF=0: two)
@@ -1326,6 +1327,17 @@ mhd_status mhd_set_params(mhd_sim *s, const mhd_params *p) {
     return plan_resident(s);
 }
 
+mhd_status mhd_iteration_info(mhd_sim *s, int64_t info[7]) {
+    g_err.clear();
+    if (!s || !info) return fail(MHD_ERR_INVALID_ARG, "NULL argument");
+    const ResPlan &p = s->res_plan;
+    const int *host = s->res_host;
+    const int64_t v[7] = {p.ok && s->res_mode != 0, p.tx, p.ty, p.tz, s->res_steps, host ? __atomic_load_n(host, __ATOMIC_RELAXED) : 0,
+                          host ? __atomic_load_n(host + 1, __ATOMIC_RELAXED) : 0};
+    std::copy(v, v + 7, info);
+    return MHD_OK;
+}
+
 mhd_status mhd_set_field(mhd_sim *s, mhd_field f, const double *host) {
     g_err.clear();
     if (!s || !host) return fail(MHD_ERR_INVALID_ARG, "NULL argument");
@@ -1454,6 +1466,7 @@ mhd_status mhd_step(mhd_sim *s, int64_t n_steps, int32_t budget_every) {
         } else {
             STEPCHK(one_step(s));
         }
+        if (s->res_now) s->res_steps += 1;
         if (budget_every > 0 && s->t_host % budget_every == 0) STEPCHK(record_budget(s));
     }
     return resident.end();
@@ -1496,6 +1509,7 @@ mhd_status step_in_scratch(mhd_sim *s, int64_t n_steps, int32_t budget_every, vo
     for (int64_t i = 0; i < n_steps && st == MHD_OK; ++i) {  // direct launches: no graph holds these pointers
         if (i % kResSteps == 0) st = resident.next(n_steps - i);
         if (st == MHD_OK) st = one_step(s);
+        if (st == MHD_OK && s->res_now) s->res_steps += 1;
         if (st == MHD_OK && budget_every > 0 && s->t_host % budget_every == 0) st = record_budget(s);
     }
     s->scr = mhd_sim::Scratch{};

@@ -190,3 +190,50 @@ def test_roll_calls_given_up(monkeypatch):
         out.append([sim.get_field(f) for f in ("rho", "u", "b")])
         sim.close()
     assert all(np.array_equal(x, y) for x, y in zip(*out))
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_the_forms_compared_are_the_forms_that_ran(case, monkeypatch):
+    """mode 0 has no plan; in mode 1 every step is resident and its roll call ends in "go"; in mode 2
+    every step is done by the stand-in."""
+    print("case resident forms", case, flush=True)
+    w, over, wall = box(case)
+    for mode in ("0", "1", "2"):
+        sim = make(w, over, wall, mode, monkeypatch)
+        sim.step(3)
+        sim.set_graph(False)
+        sim.step(1)
+        sim.step_noalloc(1)
+        sim.get_field("b")
+        info = sim.iteration_info()
+        want = {"0": (False, 0, 0, 0), "1": (True, 5, 0, 0), "2": (True, 5, 0, 5)}[mode]
+        assert (info["planned"], info["steps"], info["given_up"], info["stand_in"]) == want, (case, mode, info)
+        if mode != "0" and case.startswith("x_tiles"):
+            assert info["tile"][0] < w.nx, info
+        sim.close()
+
+
+def test_steps_keep_away_from_a_busy_gpu_for_a_while(monkeypatch):
+    """A roll call given up: the other steps of its call are done by the stand-in without one, the next
+    calls launch their sweeps one by one, and then the resident launch is tried again."""
+    print("case resident keeps away", flush=True)
+    w, over, wall = box("cube_even")
+    sim = make(w, over, wall, "3", monkeypatch)
+    def after(n):
+        sim.step(n)
+        sim.get_field("b")
+        info = sim.iteration_info()
+        return info["steps"], info["given_up"], info["stand_in"]
+    assert after(3) == (3, 1, 3)
+    assert after(10) == (3, 1, 3)
+    assert after(54) == (3, 1, 3)
+    assert after(1) == (4, 2, 4)
+    assert after(128) == (4, 2, 4)
+    assert after(1) == (5, 3, 5)
+    sim.close()
+    from paper_2211_09370_amd import Sim
+    sim = Sim(128, 128, 128, 0)  # beyond the LDS
+    sim.set_params(w.params)
+    sim.step(1)
+    assert not sim.iteration_info()["planned"] and sim.iteration_info()["steps"] == 0
+    sim.close()

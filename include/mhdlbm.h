@@ -182,18 +182,18 @@ mhd_status mhd_set_markers(mhd_sim *s, const double *xyz, int64_t M, const doubl
  * marker (the scaling of Sec. 5.5 / 5.6 would be singular or negative). UNSUPPORTED if
  * tau = 3 nu / gamma + 1/2 >= 1 with gamma != 1 (the macroscopic branch has no rescaling).
  * float32 boxes whose fields fit the chip's LDS (up to about 0.9 M cells; with a wall, one made of
- * lines) run the n_mag sweeps of a step and their wall corrections as one launch, with the same
+ * lines) and whose n_mag is large enough for it to be faster (1 to 5 with a wall, more without) run the n_mag sweeps of a step and their wall corrections as one launch, with the same
  * results; not while profiling, in calls made under the caller's own stream capture, or in a
  * batch. This call and mhd_set_markers prepare that launch (about 1 ms of host time when the wall
  * is new), so that step calls only launch. The environment variable MHD_RESIDENT, read here,
  * selects: 0 = never, 1 (default) = where it fits; for tests, 2 = always the form that takes over
  * when the launch's workgroups cannot all be on the GPU at once, 3 = as 1, each time with that
- * happening (the next 64 steps or more then launch their sweeps one by one). */
+ * happening (the next 64 steps or more then launch their sweeps one by one), 4 = as 1 for any n_mag. */
 mhd_status mhd_set_params(mhd_sim *s, const mhd_params *p);
 
-/* How the magnetic iteration of a box runs (host-only, does not wait): info[0] = 1 if it has a plan for
- * one launch a step (mhd_set_params), 0 if its sweeps are launches of their own; info[1..3] = the
- * cells (x, y, z) of that plan's tiles; info[4] = steps issued in that form since mhd_create,
+/* How the magnetic iteration of a box runs (host-only, does not wait): info[0] = 1 if all of a
+ * step's sweeps are one launch (mhd_set_params), 0 if its sweeps are launches of their own; info[1..3] = the
+ * cells (x, y, z) of that launch's tiles; info[4] = steps issued in that form since mhd_create,
  * and, of the steps finished so far, info[5] = those whose workgroups could not all be on the GPU
  * at once within 20 ms, info[6] = those done by the form that takes over then. */
 mhd_status mhd_iteration_info(mhd_sim *s, int64_t info[7]);

@@ -73,6 +73,7 @@ struct ResPlan {
     int ns = 0, cz = 0, threads = 0;
     int slots = 0, mk_max = 0, km4 = 0;
     size_t lds_bytes = 0;
+    long iter_ns = 0, start_ns = 0;  // estimates: an iteration; what a launch takes beyond its iterations
     std::vector<int> tab, tab_off;  // until uploaded
 };
 
@@ -86,6 +87,10 @@ struct ResWall {
 
 // Tiles, tables and launch shape of a box for at most max_wg workgroups; ok = false if it does not fit.
 ResPlan make_resident_plan(int nx, int ny, int nz, const ResWall &wall, int max_wg);
+
+// Smallest number of sweeps a step for which plan p is faster than a launch a sweep and two a wall
+// correction (INT_MAX: none).
+int resident_min_sweeps(const ResPlan &p, int nx, int ny, int nz, bool wall);
 
 // Readies the kernels of plan p on the current GPU (once, before launches).
 hipError_t prepare_mag_resident(const ResPlan &p);

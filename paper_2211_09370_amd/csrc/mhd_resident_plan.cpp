@@ -1,6 +1,7 @@
 // Host side of the resident magnetic iteration: tiles of the cross-section, the rows, markers and
 // neighbours of each tile, and the launch shape (mhd_resident.hip describes the kernel).
 #include <algorithm>
+#include <climits>
 #include <cstring>
 #include <set>
 
@@ -183,6 +184,8 @@ ResPlan make_resident_plan(int nx, int ny, int nz, const ResWall &wall, int max_
                 p.nwg = (int)nwg;
                 if (!launch_shape(p.lw, ty, tz, p, c.cost)) continue;
                 c.cost += staged + (gx > 1 ? 700 + 9L * (ty + 2) * (tz + 2) : 0);
+                p.iter_ns = 1400 + c.cost;
+                p.start_ns = 9500 + 22 * staged / 10;
                 cand.push_back(c);
             }
     std::stable_sort(cand.begin(), cand.end(), [](const Cand &a, const Cand &b) {
@@ -195,6 +198,24 @@ ResPlan make_resident_plan(int nx, int ny, int nz, const ResWall &wall, int max_
         return p;
     }
     return ResPlan{};
+}
+
+// A step takes start_ns + n iter_ns here (without a wall, iter_ns less 1.7 us), beyond a step without
+// sweeps, and otherwise n times the launches of a sweep and of a correction: a sweep 10.4 us on small
+// boxes and 5 us more per million cells beyond 0.3 million, counting the tiles' empty places, the paired
+// sweep 11.5 us on rows of 128 cells and 14.2 us on longer ones; a correction 4.6 us and 3.2 us more per
+// million cells. D3Q27 adds about as much to both. Measured on 42 boxes of 4 k to 0.94 M cells, both
+// lattices, with a wall and without: with a wall 192 x 70 x 70 breaks even at 3.8 sweeps (2 sweeps: 125 us
+// a step here, 111 there), 100 x 75 x 75 at 1.9, 32^3 at 1; without one 32^3 at 1.6, 100 x 75 x 75 at
+// 4.6, and 128 x 80 x 80 never (12.6 us a sweep against 11.8).
+int resident_min_sweeps(const ResPlan &p, int nx, int ny, int nz, bool wall) {
+    const double cells = (double)nx * ny * nz;
+    const int tx = nx > 32 ? 64 : nx > 16 ? 32 : nx > 8 ? 16 : 8;  // tiles of the single-cell sweep
+    const double places = (double)ceil_div(nx, tx) * tx * ny * nz;
+    double seq = nx % 128 ? 10400 + 5e-3 * std::max(0.0, places - 3e5) : nx == 128 ? 11500 : 14200;
+    if (wall) seq += 4600 + 3.2e-3 * cells;
+    const double gain = seq - (double)(p.iter_ns - (wall ? 0 : 1700));
+    return gain * 1e6 > (double)p.start_ns ? (int)((double)p.start_ns / gain) + 1 : INT_MAX;
 }
 
 }  // namespace mhd

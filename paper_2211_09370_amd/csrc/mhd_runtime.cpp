@@ -221,12 +221,12 @@ struct mhd_sim {
     // Resident magnetic iteration (mhd_resident.hip): the wall as lines along x (empty tap_row: no
     // wall; wall_lines false: markers of another form), and the plan for it (plan_resident; not ok until
     // made). MHD_RESIDENT at mhd_set_params: 0 = never, 1 (default) = where the box fits, 2 = always the
-    // stand-in of a roll call given up, 3 = as 1 with every roll call given up.
+    // stand-in of a roll call given up, 3 = with every roll call given up, 4 = as 1 for any number of sweeps.
     ResWall res_wall;
     bool wall_lines = true;
     ResPlan res_plan;
     bool res_planned = false, res_now = false;
-    int res_mode = 1, cus = 0;
+    int res_mode = 1, cus = 0, res_min = 0;  // res_min: fewest sweeps a step for it (resident_min_sweeps)
     // Roll calls given up and steps done by the stand-in, as the GPU has written them to host memory;
     // the first of them seen so far, steps left that launch their sweeps one by one because of it, how
     // many those were, and resident steps since.
@@ -641,7 +641,7 @@ mhd_status resident_iteration(mhd_sim *s, const StepConst &c) {
     a.tab = a.tab_off + p.gy * p.gz + 1;
     a.sync = s->at<int>(s->L.res_sync);
     a.stalled = &s->ctrl()->stalled;
-    a.roll_ticks = s->res_mode >= 2 ? -1 : kResRollTicks;
+    a.roll_ticks = s->res_mode == 2 || s->res_mode == 3 ? -1 : kResRollTicks;
     a.record = s->res_mode != 2;
     a.host = s->res_host_dev;
     const hipError_t e = launch_mag_resident(s->stream, a, p, c.lattice == 27);
@@ -834,6 +834,7 @@ class ResidentCall {
     mhd_status next(int64_t left) {
         STEPCHK(end());
         if (s->res_mode == 0 || s->prof || !s->res_plan.ok) return MHD_OK;
+        if (s->res_mode == 1 && s->prm.n_mag < s->res_min) return MHD_OK;  // the sweeps' own launches are faster
         if (s->prm.n_mag >= INT32_MAX / (2 * kResMaxTiles)) return MHD_OK;  // the stand-in's turns are counted in 32 bits
         const int64_t n = std::min(left, kResSteps);
         const int given_up = __atomic_load_n(s->res_host, __ATOMIC_RELAXED);
@@ -937,6 +938,7 @@ mhd_status plan_resident(mhd_sim *s) {
         p.tab = std::vector<int>();
         p.tab_off = std::vector<int>();
         s->res_plan = std::move(p);
+        s->res_min = resident_min_sweeps(s->res_plan, s->g.nx, s->g.ny, s->g.nz, s->M > 0);
     }
     s->res_planned = true;
     return MHD_OK;
@@ -1332,7 +1334,8 @@ mhd_status mhd_iteration_info(mhd_sim *s, int64_t info[7]) {
     if (!s || !info) return fail(MHD_ERR_INVALID_ARG, "NULL argument");
     const ResPlan &p = s->res_plan;
     const int *host = s->res_host;
-    const int64_t v[7] = {p.ok && s->res_mode != 0, p.tx, p.ty, p.tz, s->res_steps, host ? __atomic_load_n(host, __ATOMIC_RELAXED) : 0,
+    const bool used = p.ok && s->res_mode != 0 && (s->res_mode != 1 || s->prm.n_mag >= s->res_min);
+    const int64_t v[7] = {used, p.tx, p.ty, p.tz, s->res_steps, host ? __atomic_load_n(host, __ATOMIC_RELAXED) : 0,
                           host ? __atomic_load_n(host + 1, __ATOMIC_RELAXED) : 0};
     std::copy(v, v + 7, info);
     return MHD_OK;

@@ -318,8 +318,8 @@ int main(int argc, char **argv) {
             const ResWall w = ring_wall(ny, nz, R);
             const ResPlan p = make_resident_plan(nx, ny, nz, w, wg);
             const std::string e = p.ok ? check_plan(p, nx, ny, nz, w, wg) : "";
-            printf("%d %d %d %g planned %d lw %d short %d %s\n", nx, ny, nz, R, p.ok, p.lw, p.gx > 1 && nx % p.tx != 0,
-                   e.empty() ? "ok" : e.c_str());
+            printf("%d %d %d %g planned %d lw %d short %d sweeps %d %s\n", nx, ny, nz, R, p.ok, p.lw, p.gx > 1 && nx % p.tx != 0,
+                   p.ok ? resident_min_sweeps(p, nx, ny, nz, R > 0) : 0, e.empty() ? "ok" : e.c_str());
         }
         return 0;
     }

@@ -150,6 +150,23 @@ def test_new_markers_and_parameters_between_steps(monkeypatch):
     assert all(np.array_equal(x, y) for x, y in zip(*out))
 
 
+def test_few_sweeps_are_launched_one_by_one(monkeypatch):
+    """n_mag below what makes the resident launch the faster form, at it, and changed between steps."""
+    print("case resident few sweeps", flush=True)
+    w = random_box(192, 70, 70, key=413, n_mag=1, R=33.0)
+    out = []
+    for mode in ("0", "1"):
+        sim = make(w, {}, True, mode, monkeypatch)
+        for n_mag in (1, 3, 5, 2):
+            sim.set_params(w.params, n_mag=n_mag)
+            sim.step(1)
+            assert sim.iteration_info()["planned"] == (mode == "1" and n_mag == 5), (mode, n_mag)
+        assert sim.iteration_info()["steps"] == (1 if mode == "1" else 0)
+        out.append([sim.get_field(f) for f in ("rho", "u", "b")])
+        sim.close()
+    assert all(np.array_equal(x, y) for x, y in zip(*out))
+
+
 @pytest.mark.parametrize("case", ["131x57x57", "400x42x42", "163x53x53", "497x31x31", "131x43x43 six magnets q27"])
 def test_wide_x_tiles_with_a_shorter_last_one(case, monkeypatch):
     """Tiles of more columns than a wave, the last one shorter, so that waves with and without idle
@@ -166,12 +183,14 @@ def test_wide_x_tiles_with_a_shorter_last_one(case, monkeypatch):
     else:
         w, over = random_box(nx, ny, nz, key=415, n_mag=3, R=R), {}
     out = {}
-    for mode in ("0", "1", "2"):
+    for mode in ("0", "4", "2"):
         sim = make(w, over, True, mode, monkeypatch)
         sim.step(2)
         out[mode] = [sim.get_field(f) for f in ("rho", "u", "b")]
+        info = sim.iteration_info()
+        assert info["steps"] == (0 if mode == "0" else 2) and (mode == "0" or 62 < info["tile"][0] and nx % info["tile"][0]), info
         sim.close()
-    for mode in ("1", "2"):
+    for mode in ("4", "2"):
         for f, x, y in zip(("rho", "u", "b"), out["0"], out[mode]):
             assert np.array_equal(x, y), (case, mode, f, float(np.abs(x - y).max()))
 
@@ -194,19 +213,22 @@ def test_roll_calls_given_up(monkeypatch):
 
 @pytest.mark.parametrize("case", CASES)
 def test_the_forms_compared_are_the_forms_that_ran(case, monkeypatch):
-    """mode 0 has no plan; in mode 1 every step is resident and its roll call ends in "go"; in mode 2
-    every step is done by the stand-in."""
+    """mode 0 has no plan; in mode 4 every step is resident, whatever the number of sweeps, and its roll
+    call ends in "go"; in mode 2 every step is done by the stand-in. The same fields."""
     print("case resident forms", case, flush=True)
     w, over, wall = box(case)
-    for mode in ("0", "1", "2"):
+    ref = None
+    for mode in ("0", "4", "2"):
         sim = make(w, over, wall, mode, monkeypatch)
         sim.step(3)
         sim.set_graph(False)
         sim.step(1)
         sim.step_noalloc(1)
-        sim.get_field("b")
+        got = [sim.get_field(f) for f in ("rho", "u", "b")]
+        ref = ref or got
+        assert all(np.array_equal(x, y) for x, y in zip(ref, got)), (case, mode)
         info = sim.iteration_info()
-        want = {"0": (False, 0, 0, 0), "1": (True, 5, 0, 0), "2": (True, 5, 0, 5)}[mode]
+        want = {"0": (False, 0, 0, 0), "4": (True, 5, 0, 0), "2": (True, 5, 0, 5)}[mode]
         assert (info["planned"], info["steps"], info["given_up"], info["stand_in"]) == want, (case, mode, info)
         if mode != "0" and case.startswith("x_tiles"):
             assert info["tile"][0] < w.nx, info

@@ -67,7 +67,7 @@ __device__ __forceinline__ int sweep_tile(SweepArgs &a, const PipeStep *tab, con
 template <int TX, int TY>
 constexpr int kSweepLds = 2 * 6 * (TX + 2) * (TY + 2);  // two LDS planes (floats)
 
-template <int TX, int TY, typename TU, typename TB, bool SPLIT, bool BYZ, bool Q27>
+template <int TX, int TY, typename TU, typename TB, bool SPLIT, bool BYZ, bool Q27, bool FEW = false>
 __device__ __forceinline__ void sweep_cells(const SweepArgs &a, const int lb, float *lds) {
     using LW = Lat<Q27>;
     constexpr int NT = TX * TY, HX = TX + 2, HY = TY + 2, HN = HX * HY;
@@ -252,7 +252,7 @@ __device__ __forceinline__ void sweep_cells(const SweepArgs &a, const int lb, fl
                     st_off(o2, ko, out[0][2]);
                 }
             };
-            if constexpr (TX == 64) {
+            if constexpr (TX == 64 && !FEW) {
                 // A wave is a row: 18 reads of the own column and 18 of the halo column instead of 54, and
                 // the columns beside it from the lanes beside it. Lanes beyond n_x hold staged (wrapped)
                 // cells, so the last cell's neighbour is there too.
@@ -390,12 +390,12 @@ __device__ __forceinline__ void sweep_cells(const SweepArgs &a, const int lb, fl
 #undef MHD_PLANE_DIFFS
 }
 
-template <int TX, int TY, typename TU, typename TB, bool BATCH, bool SPLIT, bool BYZ, bool Q27>
-__global__ void __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(std::is_same<TB, float>::value && !BYZ ? 4 : 1)))
+template <int TX, int TY, typename TU, typename TB, bool BATCH, bool SPLIT, bool BYZ, bool Q27, bool FEW>
+__global__ void __launch_bounds__(TX *TY) __attribute__((amdgpu_waves_per_eu(std::is_same<TB, float>::value && !BYZ && !FEW ? 4 : 1)))
 k_mag_sweep(SweepArgs a, const PipeStep *tab, const BlockMap *map, int which, int nbatch) {
     __shared__ float lds[kSweepLds<TX, TY>];
     const int lb = sweep_tile<BATCH>(a, tab, map, which, nbatch);
-    if (lb >= 0) sweep_cells<TX, TY, TU, TB, SPLIT, BYZ, Q27>(a, lb, lds);
+    if (lb >= 0) sweep_cells<TX, TY, TU, TB, SPLIT, BYZ, Q27, FEW>(a, lb, lds);
 }
 
 // -------------------------------------------------------------------------------------------
@@ -448,7 +448,7 @@ struct Pair<__hip_bfloat16> {
 template <int TY>
 constexpr int kPairLds = 2 * 6 * (TY + 2) * 132;
 
-template <int TY, typename TU, typename TB, bool SPLIT, bool BYZ, bool Q27, bool XWRAP>
+template <int TY, typename TU, typename TB, bool SPLIT, bool BYZ, bool Q27, bool XWRAP, bool FEW = false>
 __device__ __forceinline__ void sweep_pairs(const SweepArgs &a, const int lb, float *lds) {
     using LW = Lat<Q27>;
     constexpr int HY = TY + 2;        // staged rows
@@ -456,9 +456,11 @@ __device__ __forceinline__ void sweep_pairs(const SweepArgs &a, const int lb, fl
     // per row, periodic in x): x0 .. x0+127 at 0 .. 127 and no halo columns; the x neighbours of a
     // lane's two cells come from the neighbouring lanes, across the wave ends for the wrap.
     constexpr int RS = 132;
-    // float32: x0 .. x0+127 at 0 .. 127, the halo columns at 128 and 129.
+    // WAVE (float32, x neighbours from the lanes beside): x0 .. x0+127 at 0 .. 127, the halo columns at
+    // 128 and 129.
     constexpr bool F32 = std::is_same<TB, float>::value;  // shared float32 arithmetic (mhd_sweep_math.h)
-    constexpr int X0 = XWRAP || F32 ? 0 : 1;
+    constexpr bool WAVE = F32 && (XWRAP || !FEW);
+    constexpr int X0 = XWRAP || WAVE ? 0 : 1;
     float (*s_pl)[6][HY * RS] = reinterpret_cast<float (*)[6][HY * RS]>(lds);
     const int tix = lb % a.tiles_x;
     const int rest = lb / a.tiles_x;
@@ -514,7 +516,7 @@ __device__ __forceinline__ void sweep_pairs(const SweepArgs &a, const int lb, fl
     const int hx = hside ? wrapi(x0 + 128, nx) : wrapi(x0 - 1, nx);
     const int hyg = wrapi(y0 - 1 + min(hhy, HY - 1), ny);
     const unsigned hoff = (unsigned)(hx + nx * hyg);
-    const int hidx = min(hhy, HY - 1) * RS + (hside ? 129 : F32 ? 128 : 0);
+    const int hidx = min(hhy, HY - 1) * RS + (hside ? 129 : WAVE ? 128 : 0);
     // B_ext / b_scale of the staged columns
     const float bea[3] = {a.bext[xa] * ib, a.bext[nx + xa] * ib, a.bext[2 * nx + xa] * ib};
     const float beb[3] = {a.bext[xa + 1] * ib, a.bext[nx + xa + 1] * ib, a.bext[2 * nx + xa + 1] * ib};
@@ -758,7 +760,7 @@ __device__ __forceinline__ void sweep_pairs(const SweepArgs &a, const int lb, fl
             // (C = S - P) of both cells: S and B collect the in-plane sums, P the flux through
             // the planes (components x, y; zero for z, so A = C there).
             float S[2][3], B[2][3], Pz[2][2], cen[2][3];
-            // 16-bit kinds: rows y-1, y, y+1 of a field at columns xa-1 .. xa+2 (two aligned 8-byte reads per row)
+            // without WAVE: rows y-1, y, y+1 of a field at columns xa-1 .. xa+2 (two aligned 8-byte reads per row)
             auto rows = [&](int k, float (&v)[3][4]) {
 #pragma unroll
                 for (int r = 0; r < 3; ++r) {
@@ -780,7 +782,10 @@ __device__ __forceinline__ void sweep_pairs(const SweepArgs &a, const int lb, fl
                 }
             };
             float out[2][3];
-            if constexpr (F32) {
+            if constexpr (F32 && !WAVE) {
+                plane_terms<2, Q27>(columns_rows<2>(rows), W, S, B, Pz, cen);
+                march.take(W, S, B, Pz, cen, out);
+            } else if constexpr (F32) {
                 auto cells = [&](int k, float (&v)[3][2]) {
 #pragma unroll
                     for (int r = 0; r < 3; ++r) {
@@ -953,13 +958,13 @@ __device__ __forceinline__ void sweep_pairs(const SweepArgs &a, const int lb, fl
 // VGPRs, no spills), so that three 4-row workgroups share a CU on large boxes instead of two: the
 // 16-bit forms' steps on 512 x 256 x 256 then run 5-6% faster and the float32 64-pipe batch 5%.
 // The single-box float32 form is left unbounded (the bound made its step 0.4% slower).
-template <int TY, typename TU, typename TB, bool BATCH, bool SPLIT, bool BYZ, bool Q27, bool XWRAP>
+template <int TY, typename TU, typename TB, bool BATCH, bool SPLIT, bool BYZ, bool Q27, bool XWRAP, bool FEW>
 __global__ void __launch_bounds__(64 * TY)
-__attribute__((amdgpu_waves_per_eu(XWRAP || BYZ || (std::is_same<TB, float>::value && !BATCH) ? 1 : 3)))
+__attribute__((amdgpu_waves_per_eu(XWRAP || BYZ || FEW || (std::is_same<TB, float>::value && !BATCH) ? 1 : 3)))
 k_mag_sweep_pair(SweepArgs a, const PipeStep *tab, const BlockMap *map, int which, int nbatch) {
     __shared__ __align__(16) float lds[kPairLds<TY>];
     const int lb = sweep_tile<BATCH>(a, tab, map, which, nbatch);
-    if (lb >= 0) sweep_pairs<TY, TU, TB, SPLIT, BYZ, Q27, XWRAP>(a, lb, lds);
+    if (lb >= 0) sweep_pairs<TY, TU, TB, SPLIT, BYZ, Q27, XWRAP, FEW>(a, lb, lds);
 }
 
 // float32 boxes of a batch with different tile forms in one launch (256 work-items in each form):
@@ -1024,55 +1029,73 @@ static inline unsigned sweep_grid(int nblocks) { return (unsigned)(((nblocks + 7
 
 // Sweeps are launched through hipExtLaunchKernelGGL: when profiling, its start / stop events
 // are stamped when the kernel itself starts and ends (no event packets around the launch).
-template <typename TU, typename TB, bool BATCH, bool SPLIT, bool BYZ, bool Q27>
-static hipError_t sweep_typed(hipStream_t s, const SweepArgs &a, SweepLaunch L, const PipeStep *tab,
-                              const BlockMap *map, int which, int nblocks, hipEvent_t e0, hipEvent_t e1) {
+template <typename TU, typename TB, bool BATCH, bool SPLIT, bool BYZ, bool Q27, bool FEW>
+static hipError_t sweep_form(hipStream_t s, const SweepArgs &a, SweepLaunch L, const PipeStep *tab,
+                             const BlockMap *map, int which, int nblocks, hipEvent_t e0, hipEvent_t e1) {
     const dim3 grid(sweep_grid(nblocks));
     if (L.pair) {
         if constexpr (!BATCH) {
             if (a.nx == 128) {  // one tile per row: x neighbours by wave rotation
                 if constexpr (!std::is_same<TB, float>::value)
                     if (L.ty >= 8) {
-                        hipExtLaunchKernelGGL(k_mag_sweep_pair<8, TU, TB, false, SPLIT, BYZ, Q27, true>, grid, dim3(512), 0, s, e0,
+                        hipExtLaunchKernelGGL(k_mag_sweep_pair<8, TU, TB, false, SPLIT, BYZ, Q27, true, false>, grid, dim3(512), 0, s, e0,
                                               e1, 0, a, tab, map, which, nblocks);
                         return hipGetLastError();
                     }
-                hipExtLaunchKernelGGL(k_mag_sweep_pair<4, TU, TB, false, SPLIT, BYZ, Q27, true>, grid, dim3(256), 0, s, e0, e1, 0, a,
+                hipExtLaunchKernelGGL(k_mag_sweep_pair<4, TU, TB, false, SPLIT, BYZ, Q27, true, false>, grid, dim3(256), 0, s, e0, e1, 0, a,
                                       tab, map, which, nblocks);
                 return hipGetLastError();
             }
         }
         if constexpr (!std::is_same<TB, float>::value)
             if (L.ty >= 8) {
-                hipExtLaunchKernelGGL(k_mag_sweep_pair<8, TU, TB, BATCH, SPLIT, BYZ, Q27, false>, grid, dim3(512), 0, s, e0, e1, 0, a,
+                hipExtLaunchKernelGGL(k_mag_sweep_pair<8, TU, TB, BATCH, SPLIT, BYZ, Q27, false, false>, grid, dim3(512), 0, s, e0, e1, 0, a,
                                       tab, map, which, nblocks);
                 return hipGetLastError();
             }
-        hipExtLaunchKernelGGL(k_mag_sweep_pair<4, TU, TB, BATCH, SPLIT, BYZ, Q27, false>, grid, dim3(256), 0, s, e0, e1, 0, a, tab, map,
+        hipExtLaunchKernelGGL(k_mag_sweep_pair<4, TU, TB, BATCH, SPLIT, BYZ, Q27, false, FEW>, grid, dim3(256), 0, s, e0, e1, 0, a, tab, map,
                               which, nblocks);
         return hipGetLastError();
     }
     switch (L.tx) {
         case 64:
-            hipExtLaunchKernelGGL(k_mag_sweep<64, 4, TU, TB, BATCH, SPLIT, BYZ, Q27>, grid, dim3(256), 0, s, e0, e1, 0, a, tab, map,
+            hipExtLaunchKernelGGL(k_mag_sweep<64, 4, TU, TB, BATCH, SPLIT, BYZ, Q27, FEW>, grid, dim3(256), 0, s, e0, e1, 0, a, tab, map,
                                   which, nblocks);
             break;
         case 32:
-            hipExtLaunchKernelGGL(k_mag_sweep<32, 8, TU, TB, BATCH, SPLIT, BYZ, Q27>, grid, dim3(256), 0, s, e0, e1, 0, a, tab, map,
+            hipExtLaunchKernelGGL(k_mag_sweep<32, 8, TU, TB, BATCH, SPLIT, BYZ, Q27, FEW>, grid, dim3(256), 0, s, e0, e1, 0, a, tab, map,
                                   which, nblocks);
             break;
         case 16:
-            hipExtLaunchKernelGGL(k_mag_sweep<16, 16, TU, TB, BATCH, SPLIT, BYZ, Q27>, grid, dim3(256), 0, s, e0, e1, 0, a, tab, map,
-                                  which, nblocks);
+            hipExtLaunchKernelGGL(k_mag_sweep<16, 16, TU, TB, BATCH, SPLIT, BYZ, Q27, FEW>, grid, dim3(256), 0, s, e0, e1, 0, a, tab,
+                                  map, which, nblocks);
             break;
         default:
-            hipExtLaunchKernelGGL(k_mag_sweep<8, 32, TU, TB, BATCH, SPLIT, BYZ, Q27>, grid, dim3(256), 0, s, e0, e1, 0, a, tab, map,
+            hipExtLaunchKernelGGL(k_mag_sweep<8, 32, TU, TB, BATCH, SPLIT, BYZ, Q27, FEW>, grid, dim3(256), 0, s, e0, e1, 0, a, tab, map,
                                   which, nblocks);
             break;
     }
     return hipGetLastError();
 }
 
+// FEW: float32 launches whose workgroups all find a place at once. There the latency of a plane's chain
+// counts, and it is shorter where every lane reads its neighbours' columns and nothing bounds the
+// registers; beyond that, fewer reads and another workgroup on a CU count more. The unbounded forms hold
+// three workgroups of single cells on a CU (against four) and two of pairs (against three), so the line is
+// at 768 and 512 workgroups; pairs of 769 to 1024 take two rounds either way. Per sweep, many-form
+// against this: 64 x 90 x 90 (276) 12.8 -> 11.7 us, 64 x 128 x 128 (512) 13.4 -> 12.2, 64 x 150 x 150 (722)
+// 15.7 -> 15.1, but 100 x 112 x 112 (784) 18.1 -> 21.2; pairs 256 x 80 x 80 (400) 16.7 -> 15.9, 512 x 80 x
+// 80 (800) 30.4 -> 29.9, but 256 x 100 x 100 (650) 21.2 -> 27.9.
+static bool few_workgroups(bool pair, int n) { return pair ? n <= 512 || (n > 768 && n <= 1024) : n <= 768; }
+
+template <typename TU, typename TB, bool BATCH, bool SPLIT, bool BYZ, bool Q27>
+static hipError_t sweep_typed(hipStream_t s, const SweepArgs &a, SweepLaunch L, const PipeStep *tab,
+                              const BlockMap *map, int which, int nblocks, hipEvent_t e0, hipEvent_t e1) {
+    if constexpr (std::is_same<TB, float>::value)
+        if (few_workgroups(L.pair, nblocks))
+            return sweep_form<TU, TB, BATCH, SPLIT, BYZ, Q27, true>(s, a, L, tab, map, which, nblocks, e0, e1);
+    return sweep_form<TU, TB, BATCH, SPLIT, BYZ, Q27, false>(s, a, L, tab, map, which, nblocks, e0, e1);
+}
 
 template <bool BATCH, bool BYZ>
 static hipError_t sweep_kinds_yz(hipStream_t s, int kinds, const SweepArgs &a, SweepLaunch L, const PipeStep *tab,

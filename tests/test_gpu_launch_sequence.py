@@ -80,3 +80,37 @@ def test_the_8_row_sweep_agrees_with_the_other_tiles_on_ragged_rows():
             if ref is None:
                 ref = got
             assert all(np.array_equal(x, y) for x, y in zip(got, ref)), (nx, ny, nz, lattice, tiles)
+
+
+@pytest.mark.parametrize("lattice", [19, 27])
+@pytest.mark.parametrize("magnets", [False, True])
+@pytest.mark.parametrize("nx,ny,nz,tiles", [
+    (70, 30, 50, ((64, 8, 0, 4), (64, 1, 0, 4))),           # 112 and 800 workgroups: the forms for few and for many
+    (30, 40, 160, ((32, 8, 0, 4), (32, 1, 0, 4))),          # 100 and 800
+    (14, 33, 270, ((16, 8, 0, 4), (16, 1, 0, 4))),          # 102 and 810
+    (7, 33, 400, ((8, 8, 0, 4), (8, 1, 0, 4))),             # 100 and 800
+    (256, 21, 72, ((64, 8, 1, 4), (64, 1, 1, 4), (64, 2, 1, 4), (64, 72, 1, 4))),  # pairs: 108, 864, 432 and 12
+    (256, 21, 55, ((64, 1, 1, 4), (64, 8, 1, 4), (64, 8, 0, 4))),                   # 660
+])
+def test_forms_for_few_and_for_many_workgroups_agree(nx, ny, nz, tiles, magnets, lattice):
+    from paper_2211_09370_amd import Sim
+    import numpy as np
+
+    print("case few and many", nx, ny, nz, magnets, lattice, flush=True)
+    if magnets:
+        w = W.pipe_workload("few", 440, nx, ny, nz, 8.0, 50.0, 10.0, 1e-2, bext_kind=W.BEXT_SIX_MAGNETS, n_mag=3, b_amp=1e-3, noise=1e-2)
+    else:
+        w = P.random_box(nx, ny, nz, key=441, n_mag=3)
+    ref = None
+    for t in tiles:
+        s = Sim(nx, ny, nz, w.markers.shape[1])
+        s.set_markers(w.markers)
+        s.set_params(w.params, lattice=lattice)
+        for f in ("rho", "u", "b"):
+            s.set_field(f, getattr(w, f))
+        s.tiles = t
+        s.step(2)
+        got = [s.get_field(f) for f in ("rho", "u", "b")]
+        s.close()
+        ref = ref or got
+        assert all(np.array_equal(x, y) for x, y in zip(got, ref)), t

@@ -13,6 +13,7 @@
 #include <memory>
 #include <mutex>
 #include <new>
+#include <set>
 #include <string>
 #include <utility>
 #include <vector>
@@ -1877,10 +1878,26 @@ mhd_status build_plan(mhd_batch *b) {
         if ((s->prm.lattice == 27) != (b->pipes[0]->prm.lattice == 27))
             return fail(MHD_ERR_UNSUPPORTED, "all pipes of a batch must use the same lattice");
     b->q27 = b->pipes[0]->prm.lattice == 27;
-    // float32 forms of 256 work-items (all but the 8-row tiles) share one launch
+    // float32 forms of 256 work-items (all but the 8-row tiles) can share one launch. That saves about 13 us
+    // a round for every launch less, and costs the tiles of single cells a place in four on a CU (the
+    // paired form's LDS), 6.5 us for a thousand of their workgroups. Steps of 24 rounds, a round: 2 x (16, 32
+    // cells wide) 33 us apart, 20 together; 32 x (8, 16, 32, 64, 128) 278, 249; but 128 x (16, 32) 134, 141 and
+    // 128 x (8, 64) 303, 355.
     const bool f32 = b->kinds == pack_kinds(MHD_STORE_F32, MHD_STORE_F32, MHD_STORE_F32);
     auto form = [](const SweepLaunch &L) { return L.pair ? 100 + L.ty : L.tx; };
-    auto key = [&](const SweepLaunch &L) { return (f32 && form(L) != 108 ? 0 : form(L)) + 1000 * L.byz; };
+    bool shared[2] = {false, false};  // without and with the (y, z) table of B_ext
+    for (int byz = 0; byz < 2 && f32; ++byz) {
+        std::set<int> forms;
+        int64_t cells = 0;
+        for (mhd_sim *s : b->pipes) {
+            const SweepLaunch e = effective_tiles(s->sweep, s->g.nx);
+            if (form(e) == 108 || (s->byz() != nullptr) != (byz == 1)) continue;
+            forms.insert(form(e));
+            if (!e.pair) cells += sweep_workgroups(e, s->g.nx, s->g.ny, s->g.nz);
+        }
+        shared[byz] = cells <= 2000 * ((int64_t)forms.size() - 1);
+    }
+    auto key = [&](const SweepLaunch &L) { return (shared[L.byz] && form(L) != 108 ? 0 : form(L)) + 1000 * L.byz; };
     for (int p : b->order) {
         mhd_sim *s = b->pipes[p];
         SweepLaunch e = effective_tiles(s->sweep, s->g.nx);

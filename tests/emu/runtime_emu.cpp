@@ -175,7 +175,11 @@ hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { return *ms =
 const size_t emu::sizeof_ctrl = sizeof(mhd::DevCtrl);
 
 namespace mhd {  // launches: counted, nothing else
-SweepArgs make_sweep_args(const void *, const void *, void *, const float *, StepConst, SweepLaunch) { return {}; }
+SweepArgs make_sweep_args(const void *, const void *, void *, const float *, StepConst, SweepLaunch) {
+    SweepArgs a{};
+    a.nblocks = 1;
+    return a;
+}
 hipError_t launch_ctrl_begin(hipStream_t, DevCtrl *, StepConst, int *, int) { return hipSuccess; }
 hipError_t launch_step_end(hipStream_t, DevCtrl *, const double *, StepConst, double) { return hipSuccess; }
 hipError_t launch_mag_sweep(hipStream_t, int, const SweepArgs &, SweepLaunch, hipEvent_t, hipEvent_t) { return ++sweep_launches, hipSuccess; }
@@ -439,6 +443,58 @@ std::string given_up() {
     return tried > 0 && tried < 1000 / 4 ? "ok" : "a long call made " + std::to_string(tried) + " resident steps of 1000 on a busy GPU";
 }
 
+// Sweep launches of a round of a batch of n boxes of each of the given lengths (32 x 32 cross-section).
+int batch_launches(int n, std::vector<int> lengths) {
+    std::vector<mhd_pipe_desc> d;
+    for (int i = 0; i < n; ++i)
+        for (int nx : lengths) {
+            mhd_pipe_desc p{};
+            p.grid.nx = nx;
+            p.grid.ny = p.grid.nz = 32;
+            d.push_back(p);
+        }
+    size_t bytes = 0;
+    Box::check(mhd_batch_workspace_size(d.data(), (int)d.size(), &bytes));
+    char *ws = (char *)aligned_alloc(256, (bytes + 255) / 256 * 256);
+    emuStream st;
+    mhd_batch *b = nullptr;
+    Box::check(mhd_batch_create(d.data(), (int)d.size(), ws, bytes, &st, &b));
+    for (int i = 0; i < (int)d.size(); ++i) {
+        mhd_sim *s = nullptr;
+        Box::check(mhd_batch_pipe(b, i, &s));
+        mhd_params p{};
+        p.nu = 0.05;
+        p.eta = 3.0;
+        p.n_mag = 2;
+        Box::check(mhd_set_params(s, &p));
+    }
+    Box::check(mhd_batch_set_graph(b, 0));
+    const int before = sweep_launches;
+    Box::check(mhd_batch_step(b, 1, 0));
+    const int launches = (sweep_launches - before) / 2;
+    Box::check(mhd_batch_destroy(b));
+    free(ws);
+    return launches;
+}
+
+// Boxes of different tile forms share a sweep launch where that saves more than it costs: 2000 workgroups
+// of single cells a launch saved (4, 8 and 16 of a box of 8, 16 and 32 here).
+std::string batch_forms() {
+    struct {
+        int n;
+        std::vector<int> lengths;
+        int launches;
+    } cases[] = {{2, {16, 32}, 1}, {32, {16, 32}, 1}, {128, {16, 32}, 2}, {128, {8, 16, 32}, 1}, {160, {8, 16, 32}, 3}, {64, {32}, 1},
+                 {300, {32}, 1}, {8, {8, 64, 128}, 1}, {40, {64, 128}, 1}, {64, {64, 128}, 2}};
+    for (const auto &c : cases) {
+        const int got = batch_launches(c.n, c.lengths);
+        if (got != c.launches)
+            return std::to_string(c.n) + " boxes of " + std::to_string(c.lengths.size()) + " lengths from " + std::to_string(c.lengths[0]) +
+                   ": " + std::to_string(got) + " launches";
+    }
+    return "ok";
+}
+
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     std::string r = "unknown scenario";
@@ -450,6 +506,7 @@ int main(int argc, char **argv) {
     if (what == "copy_error") r = error_in_a_copy();
     if (what == "stall") r = stall_report();
     if (what == "given_up") r = given_up();
+    if (what == "batch_forms") r = batch_forms();
     if (what == "long_call") r = long_call_lets_others_in();
     puts((complaint.empty() ? r : complaint).c_str());
     fflush(stdout);

@@ -27,6 +27,7 @@ def emu(tmp_path_factory):
     "copy_error",    # a failing call in the middle of a field copy leaves no copy under way
     "stall",         # a stalled step is not reported as an unstable state
     "given_up",      # a roll call given up sends the next steps to the launch sequence
+    "batch_forms",   # tile forms of a batch share a launch where that is the faster way
     "device",        # calls made while another GPU is the current one
 ])
 def test_scenario(emu, scenario):

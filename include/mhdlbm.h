@@ -184,7 +184,7 @@ mhd_status mhd_set_markers(mhd_sim *s, const double *xyz, int64_t M, const doubl
  * float32 boxes whose fields fit the chip's LDS (up to about 0.9 M cells; with a wall, one made of
  * lines) and whose n_mag is large enough for it to be faster (1 to 5 with a wall, more without) run the n_mag sweeps of a step and their wall corrections as one launch, with the same
  * results; not while profiling, in calls made under the caller's own stream capture, or in a
- * batch. This call and mhd_set_markers prepare that launch (about 1 ms of host time when the wall
+ * batch. This call and mhd_set_markers prepare that launch (0.3 to 2 ms of host time when the wall
  * is new), so that step calls only launch. The environment variable MHD_RESIDENT, read here,
  * selects: 0 = never, 1 (default) = where it fits; for tests, 2 = always the form that takes over
  * when the launch's workgroups cannot all be on the GPU at once, 3 = as 1, each time with that

@@ -5,20 +5,18 @@
 // What bounds small boxes is the chain of launches: a sweep, an interpolation and a spreading are
 // 16 us per iteration on 8 x 32 x 32 as on 32^3, whatever the cells. Here a workgroup owns the rows
 // (x lines, or TX cells of them with a halo column at each end) of a TY x TZ tile of the
-// cross-section and keeps their b in LDS and u in registers for
-// all n_mag sweeps. Per iteration it sweeps its rows, writes those that other tiles read as b*
-// (uncorrected) to the buffer of b that the iteration's parity names, raises its flag, waits for
-// the flags of the tiles it exchanges with, reads the halo rows and the rows its markers' taps
-// need, and corrects tile and halo rows from LDS. Only that exchange goes through memory: 1.9 us a
-// round for up to 4 KB a workgroup and any number of workgroups (against 3.8 us and more for a
-// barrier over the whole grid). Per iteration, launch sequence against this: 8 x 32 x 32 16.0 ->
-// 4.1 us, 32^3 15.6 -> 5.0, 5 x 83 x 83 19 -> 4.0, 100 x 75 x 75 (D3Q27) 24 -> 12, 160 x 39 x 39
-// 17.3 -> 9.3, 436 x 34 x 34 21.7 -> 12.9, 192 x 70 x 70 (941 k cells, all the LDS) 21.5 -> 16.5.
-// Cut along x, a box that is long and narrow fills the CUs: 32^3 in 64 workgroups of whole rows
-// took 6.0 us, in 256 5.0; boxes longer than a workgroup has work-items for had to stay with the
-// launch sequence. Of the 4.1 us the sweep is 1.5 (one wave on a SIMD: its instructions' issue), the wait and the reads after it
-// 1.4, the correction 0.8 (four LDS latencies); of the 12 us the sweep is 6.5 (issue of the vector
-// instructions) and the wait for the tiles with most wall 2 to 4.
+// cross-section and keeps their b in LDS and u in registers for all n_mag sweeps. Per iteration it
+// sweeps its rows, writes those that other tiles read as b* (uncorrected) to the buffer of b that the
+// iteration's parity names, raises its flag, waits for the flags of the tiles it exchanges with,
+// reads the halo rows and the rows its markers' taps need, and corrects tile and halo rows from LDS.
+// Only that exchange goes through memory: 1.9 us a round for up to 4 KB a workgroup and any number of
+// workgroups (against 3.8 us and more for a barrier over the whole grid).
+//
+// Per iteration, launch sequence against this: 8 x 32 x 32 15.3 -> 3.8 us, 32^3 14.8 -> 4.4, 5 x 83 x 83
+// 17.2 -> 4.1, 100 x 75 x 75 (D3Q27) 20.0 -> 11.3, 160 x 39 x 39 16.8 -> 8.3, 192 x 70 x 70 (941 k cells,
+// all the LDS) 21.1 -> 14.9; a step's start and end add 7 to 25 us, so few sweeps are launched one by
+// one (resident_min_sweeps). Cut along x, a box that is long and narrow fills the CUs: 32^3 in 64
+// workgroups of whole rows took 6.0 us, in 256 5.0 (with the columns formed anew in every lane).
 //
 // The exchange needs no cache maintenance: exported rows and flags are written with agent-scope
 // (write-through) stores and read with agent-scope loads, and a workgroup waits for its stores

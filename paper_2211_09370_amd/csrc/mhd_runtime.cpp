@@ -898,7 +898,7 @@ class ResidentCall {
 
 // Plan of the resident iteration for the box's wall, its tables in the workspace, and its event: all
 // that its steps need, so that a step call only launches. Called by mhd_set_markers and mhd_set_params
-// (which wait for the stream in any case), up to 1 ms of host time where something has changed. A box
+// (which wait for the stream in any case), 0.3 to 2 ms of host time where the wall has changed. A box
 // of a batch has no steps of its own.
 mhd_status plan_resident(mhd_sim *s) {
     if (s->res_planned || !s->have_params || s->res_mode == 0 || s->owner) return MHD_OK;

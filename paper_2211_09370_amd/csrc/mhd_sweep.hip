@@ -253,9 +253,9 @@ __device__ __forceinline__ void sweep_cells(const SweepArgs &a, const int lb, fl
                 }
             };
             if constexpr (TX == 64 && !FEW) {
-                // A wave is a row: 18 reads of the own column and 18 of the halo column instead of 54, and
-                // the columns beside it from the lanes beside it. Lanes beyond n_x hold staged (wrapped)
-                // cells, so the last cell's neighbour is there too.
+                // A wave is a row: 18 reads of the own column and 18 of the halo column instead of 54 (which FEW
+                // takes), and the columns beside it from the lanes beside it. Lanes beyond n_x hold staged
+                // (wrapped) cells, so the last cell's neighbour is there too.
                 if (gy < ny) {
                     auto cells = [&](int k, float (&v)[3][1]) {
 #pragma unroll
@@ -409,8 +409,9 @@ k_mag_sweep(SweepArgs a, const PipeStep *tab, const BlockMap *map, int which, in
 // each row: of the columns beside it just d2y, the row difference sums and the centre enter, and the
 // neighbouring lanes have formed those (DPP), the wave's ends taking them from the halo columns. It
 // is bound by the plane's chain in a CU, vector instructions and LDS reads, so the fewer reads show:
-// 256 x 132^2 43.8 -> 36.8 us, 128^3 16.5 -> 16.3 us. Its arithmetic is mhd_sweep_math.h, in every
-// form the same bits. Single boxes with n_x = 128 (XWRAP: one tile spans the periodic row) stage no
+// 256 x 132^2 43.8 -> 36.8 us, 128^3 16.5 -> 16.3 us. FEW (launches of few workgroups, few_workgroups below)
+// reads the columns beside as the 16-bit kinds do. Its arithmetic is mhd_sweep_math.h, in every form
+// the same bits. Single boxes with n_x = 128 (XWRAP: one tile spans the periodic row) stage no
 // halo columns, x neighbours come by wave rotation, the ends wrapping as the row does; the batch
 // keeps the halo form, since one of its launches can mix pipes of different n_x. In float32 XWRAP
 // also stages by 16-byte loads, four cells per lane and two rows per wave, which halves the load

@@ -170,7 +170,8 @@ __device__ __forceinline__ ColumnsRows<E, ROWS> columns_rows(ROWS rows) {
 // y + 1 at the lane's columns. Two instructions a combination replace six reads or moves of raw rows
 // and the arithmetic of two columns: 256 x 132^2 (4-row tiles, 36 aligned reads a plane -> 18 and 18 of
 // one word) 43.8 -> 36.8 us a sweep, 512 x 256^2 240.2 -> 234.9, 128^3 16.5 -> 16.3, 200 x 132^2 (one
-// cell a lane) 40.5 -> 37.1. HALO: end(k, h) gives the rows of the column beyond the wave,
+// cell a lane) 40.5 -> 37.1. Launches of few workgroups are the slower for it, and form all columns (few_workgroups in
+// mhd_sweep.hip). HALO: end(k, h) gives the rows of the column beyond the wave,
 // left of lane 0 and right of lane 63 (the lanes below 32 hold the left one, the others the right);
 // without it the wave is a whole periodic row and the ends wrap.
 __device__ __forceinline__ float wave_ror1(float v) {

@@ -2,15 +2,14 @@
 // neighbouring x cells, a wave a 128-cell row, a workgroup 8 rows, and it marches along z over a chunk
 // of planes (mhd_sweep.hip describes the update; the arithmetic is mhd_sweep_math.h).
 //
-// What bounds a march of this kind is the chain of each plane in a CU: the vector instructions (220 a
-// wave and plane, 165 where x neighbours come by rotation) and around them the LDS latencies and the
-// issue of the loads. The planes go straight to LDS (global_load_lds, 16 bytes a lane, two rows an
-// instruction, no registers held), a ring of four raw planes of u and b; the flux of a plane takes
-// the place of its u, which nothing else reads. So the loads are never waited for (100 to 150 cycles
-// of 3,200 to 4,100 a plane), and what is left is arranged by who has time: two waves share a SIMD, the
-// older one is served first and ends its plane some 700 cycles before the other, so the requests,
-// the two extra rows and the halo columns are work of the first four waves, at the end of the plane,
-// and the raw values of the next plane are read ahead of the reduction and become flux after it.
+// What bounds a march of this kind is the chain of each plane in a CU: the vector instructions and
+// around them the LDS latencies and the issue of the loads. The planes go straight to LDS
+// (global_load_lds, 16 bytes a lane, two rows an instruction, no registers held), a ring of four raw
+// planes of u and b, requested three planes ahead; the flux of a plane takes the place of its u,
+// which nothing else reads. What is left is arranged by who has time: two waves share a SIMD, the
+// older one is served first and ends its plane before the other, so the requests, the two extra rows
+// and the halo columns are work of the first four waves, at the end of the plane, and the raw values
+// of the next plane are read ahead of the reduction and become flux after it.
 // Against the form that stages through registers (k_mag_sweep_pair, which the 16-bit kinds keep): 512 x
 // 256^2, 128-plane chunks 263.5 -> 240.2 us, and 234.9 us (5.14 TB/s algorithmic) since the columns beside
 // a lane's come from its neighbours; 128 x 256^2, 32 planes 57.4 -> 55.2 -> 54.0 us. With 4-row tiles

@@ -218,7 +218,9 @@ mhd_status mhd_set_time(mhd_sim *s, int64_t t, double G);
  * is captured into a HIP graph (stream capture, relaxed mode: do not enqueue other work on
  * that stream from another thread meanwhile) and every step is one graph launch; the graphs
  * are dropped when parameters, markers or tiles change. Results are the same as with direct
- * launches. */
+ * launches. Boxes that step in one launch (mhd_set_params) and share a GPU take turns in issuing
+ * their steps when several threads step them, 32 steps at most at a time, and where their launches
+ * would not fit the GPU together one waits for the other on the GPU. */
 mhd_status mhd_step(mhd_sim *s, int64_t n_steps, int32_t budget_every);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving
